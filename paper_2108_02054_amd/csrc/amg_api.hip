@@ -839,7 +839,7 @@ void partial_rebuild(amg_ctx* c, const double* val) {
     }
     {
         Trace tr(c, AMG_K_COARSE_INV, nlev - 1, cs);
-        launch_densify<T>(c->lv.back().A, c->cinv, cs);
+        launch_densify<T>(c->lv.back().A, coarse_start(c->nL, c->cinv, c->cwork), cs);
         launch_dense_inverse(c->nL, c->cinv, c->rs.scal(), c->cwork, cs);
     }
     HIP_CHECK(hipEventRecord(c->ev[3], cs));
@@ -1105,8 +1105,8 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
     if (c->nL > COARSE_GLOBAL_MAX)
         throw Fail{AMG_ERR_ARG, "coarsest level has " + std::to_string(c->nL) + " rows; too many for a dense inverse"};
     c->cinv = halloc<double>(c, (size_t)c->nL * c->nL);
-    c->cwork = c->nL > COARSE_LDS_MAX ? halloc<double>(c, COARSE_WORK_DOUBLES) : nullptr;
-    launch_densify<double>(c->lv.back().A, c->cinv, s);
+    c->cwork = c->nL > COARSE_LDS_MAX ? halloc<double>(c, coarse_work_doubles(c->nL)) : nullptr;
+    launch_densify<double>(c->lv.back().A, coarse_start(c->nL, c->cinv, c->cwork), s);
     launch_dense_inverse(c->nL, c->cinv, c->rs.scal(), c->cwork, s);
     read_red(c);
     if (host_scal(c, S_COARSE) != 0.0) throw Fail{AMG_ERR_NOT_SPD, "coarsest operator is not SPD"};

@@ -517,12 +517,14 @@ int64_t max_i64(const int64_t* in, int64_t n, hipStream_t s);  // synchronises
 // ------------------------------------------------------------------ coarse solve
 constexpr int COARSE_LDS_MAX = 128;      // dense FP64 inverse held in one workgroup's LDS
 constexpr int COARSE_GLOBAL_MAX = 2048;  // larger coarsest levels: blocked, many workgroups
-constexpr size_t COARSE_WORK_DOUBLES = 2 * 64 * 64;  // scratch of the blocked inverse
 template <typename T>
 void launch_densify(const Csr& A, double* D, hipStream_t s);
-// In-place inverse of the dense n x n coarsest operator (Gauss-Jordan, positive pivots;
-// scal[S_COARSE] = 1 when one is not).  work: COARSE_WORK_DOUBLES doubles, needed when
-// n > COARSE_LDS_MAX.
+// Inverse of the dense n x n coarsest operator into D (Gauss-Jordan, positive pivots;
+// scal[S_COARSE] = 1 when one is not).  The operator is densified into coarse_start(n, D,
+// work) first: D itself, or for some sizes above COARSE_LDS_MAX the copy in work, the
+// scratch of coarse_work_doubles(n) doubles that those sizes need.
+size_t coarse_work_doubles(int n);
+double* coarse_start(int n, double* D, double* work);
 void launch_dense_inverse(int n, double* D, double* scal, double* work, hipStream_t s);
 
 // ------------------------------------------------------------------ differentiable form

@@ -761,82 +761,202 @@ void launch_densify(const Csr& A, double* D, hipStream_t s) {
 template void launch_densify<double>(const Csr&, double*, hipStream_t);
 template void launch_densify<float>(const Csr&, double*, hipStream_t);
 
-// In-place inverse of an SPD matrix by Gauss-Jordan elimination without pivoting (the
-// pivots are the positive LDL^T pivots of an SPD matrix; a non-positive or non-finite
-// pivot reports "not SPD" in scal[S_COARSE]).  One workgroup, n <= COARSE_LDS_MAX: the
-// matrix is held in LDS (128 x 128 FP64 = 128 KiB of the 160 KiB available).
-__global__ __launch_bounds__(1024) void k_dense_inverse(int n, double* __restrict__ Mg, double* __restrict__ scal) {
-    constexpr int CAP = COARSE_LDS_MAX;
-    __shared__ double colk[CAP];
-    __shared__ double rowk[CAP];
-    __shared__ int bad;
-    __shared__ double M[COARSE_LDS_MAX * COARSE_LDS_MAX];
-    for (int e = threadIdx.x; e < n * n; e += blockDim.x) M[e] = Mg[e];
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
-    for (int k = 0; k < n; ++k) {
-        const double p = M[(size_t)k * n + k];
-        if (!(p > 0.0) || !isfinite(p)) {  // uniform: every thread reads the same pivot
-            if (threadIdx.x == 0) bad = 1;
-            break;
+// ------------------------------------------------------------------ dense inverse
+//
+// Inverse of the coarsest operator by Gauss-Jordan elimination without pivoting (the pivots
+// are the positive LDL^T pivots of an SPD matrix; a non-positive or non-finite pivot reports
+// "not SPD" in scal[S_COARSE]).  The elimination is one chain of n dependent pivots, so its
+// latency bounds every form here: 16 pivots at a time are eliminated by one wavefront in
+// registers (gj_inv16), everything else is 16 x 16 tile products on the FP64 matrix cores,
+// and the next 16 x 16 (or 64 x 64) pivot block is inverted while the rest of the matrix is
+// still being updated.
+//   up to COARSE_LDS_MAX rows: one workgroup, the matrix in its LDS (k_dense_inverse);
+//   above: 64 pivots per launch over the whole device (k_bgj_first, k_bgj_step).
+// Measured: 112 rows 415 -> 37 us and 89 rows 215 -> 30 us against a pivot-by-pivot loop in
+// LDS (two barriers and n^2 / 1024 dependent updates per pivot); 265 rows 137 -> 121 us and
+// 559 rows 311 -> 260 us (beside a solve's first kernels) against two launches per 64 pivots
+// (the pivot block inverted in one, the matrix updated in the other, neither beside the
+// other).  Left: about 5 us per 16 pivots, 58 instructions per pivot in one wavefront.
+typedef double bgj_v4 __attribute__((ext_vector_type(4)));
+constexpr int GJ_XLD = 17;  // row stride of a 16 x 16 pivot-block inverse in LDS
+
+// Value of v in lane `lane` (uniform) of the wavefront.
+__device__ __forceinline__ double gj_lane(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), lane);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Value of v in lane P of this lane's row of 16 lanes (DPP row_newbcast: no LDS round trip).
+template <int P>
+__device__ __forceinline__ double gj_row_lane(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffff), 0x150 + P, 0xf, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + P, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Pivot P of gj_inv16 and the ones after it.
+template <int P>
+__device__ __forceinline__ void gj_pivots(double (&e)[4], int i, int q, bool& ok) {
+    if constexpr (P < 16) {
+        constexpr int QP = P / 4, RP = P % 4;
+        const double piv = gj_lane(e[RP], 16 * QP + P);
+        const double col = __shfl(e[RP], 16 * QP + i);  // e_iP, from the lanes that hold column P
+        ok = ok && piv > 0.0 && isfinite(piv);
+        const double pinv = 1.0 / piv;
+        const double cf = col * pinv;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double pr = gj_row_lane<P>(e[j]);
+            e[j] = i == P ? e[j] * pinv : fma(-cf, pr, e[j]);
         }
-        const double pinv = 1.0 / p;
-        for (int t = threadIdx.x; t < n; t += blockDim.x) {
-            colk[t] = M[(size_t)t * n + k];
-            rowk[t] = (t == k) ? pinv : M[(size_t)k * n + t] * pinv;
+        if (q == QP) e[RP] = i == P ? pinv : -cf;
+        gj_pivots<P + 1>(e, i, q, ok);
+    }
+}
+
+// Inverse of the 16 x 16 tile at src (row stride ld) into X (row stride GJ_XLD), by one
+// wavefront: lane l holds columns 4 (l / 16) .. + 3 of row l % 16, so that the pivot row
+// reaches every lane within its own row of 16 lanes and a pivot costs one cross-row
+// exchange (of the pivot column) instead of 15 broadcasts.
+__device__ __forceinline__ void gj_inv16(const double* src, int ld, double* X, int* bad) {
+    const int l = threadIdx.x % 64, i = l & 15, q = l >> 4;
+    double e[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e[j] = src[i * ld + 4 * q + j];
+    bool ok = true;
+    gj_pivots<0>(e, i, q, ok);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) X[i * GJ_XLD + 4 * q + j] = e[j];
+    if (!ok && l == 0) *bad = 1;
+}
+
+// 16 x 16 tile product on the FP64 matrix cores: c + sign * (a b), a and b tiles in LDS with
+// row strides lda and ldb, c and the result in the instruction's result layout (entry r of
+// lane l is row l / 16 + 4 r, column l % 16).
+__device__ __forceinline__ bgj_v4 gj_tile_mm(const double* a, int lda, const double* b, int ldb, bgj_v4 c,
+                                             double sign) {
+    const int l = threadIdx.x % 64, i = l & 15, kk = l >> 4;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+        c = __builtin_amdgcn_mfma_f64_16x16x4f64(sign * a[i * lda + 4 * s + kk], b[(4 * s + kk) * ldb + i], c, 0, 0, 0);
+    return c;
+}
+
+__device__ __forceinline__ bgj_v4 gj_tile_load(const double* t, int ld) {
+    const int l = threadIdx.x % 64;
+    bgj_v4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = t[((l >> 4) + 4 * r) * ld + (l & 15)];
+    return v;
+}
+
+__device__ __forceinline__ void gj_tile_store(double* t, int ld, bgj_v4 v) {
+    const int l = threadIdx.x % 64;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t[((l >> 4) + 4 * r) * ld + (l & 15)] = v[r];
+}
+
+// In-place inverse of the matrix of nt x nt tiles (16 x 16 each) at D in LDS (row stride LD,
+// a multiple of 16 plus 4 doubles: the 16 rows that an operand read touches fall into
+// different banks), by the 16 wavefronts of the workgroup.  For the tile row S, with
+// X = D_SS^{-1}:
+//   A: D_SJ <- X D_SJ;  B: D_IJ <- D_IJ - D_IS D_SJ;  C: D_IS <- -D_IS X, D_SS <- X
+// (I, J != S).  In B wavefront 0 takes tile (S + 1, S + 1) first and inverts it while the
+// others update the rest.  X2: two pivot-block inverses.  A pivot that is not positive and
+// finite sets *bad; the elimination runs on (the values are then meaningless).
+constexpr int GJ_THREADS = 1024;
+constexpr int GJ_WAVES = GJ_THREADS / 64;
+template <int LD>
+__device__ void gj_invert_lds(double* D, int nt, double* X2, int* bad) {
+    const int w = threadIdx.x / 64;
+    const bgj_v4 zero = {0.0, 0.0, 0.0, 0.0};
+    auto tile = [&](int I, int J) { return D + 16 * I * LD + 16 * J; };
+    if (w == 0) gj_inv16(D, LD, X2, bad);
+    __syncthreads();
+    for (int S = 0; S < nt; ++S) {
+        double* X = X2 + (S & 1) * 16 * GJ_XLD;
+        double* Xn = X2 + ((S + 1) & 1) * 16 * GJ_XLD;
+        for (int J = w; J < nt; J += GJ_WAVES)
+            if (J != S) gj_tile_store(tile(S, J), LD, gj_tile_mm(X, GJ_XLD, tile(S, J), LD, zero, 1.0));
+        __syncthreads();
+        auto update = [&](int I, int J) {
+            gj_tile_store(tile(I, J), LD,
+                          gj_tile_mm(tile(I, S), LD, tile(S, J), LD, gj_tile_load(tile(I, J), LD), -1.0));
+        };
+        const int N = S + 1;  // the next pivot block, wavefront 0's
+        if (N < nt && w == 0) {
+            update(N, N);
+            gj_inv16(tile(N, N), LD, Xn, bad);
+        } else {
+            const int m = nt - 1;
+            const int first = N < nt ? w - 1 : w, step = N < nt ? GJ_WAVES - 1 : GJ_WAVES;
+            for (int u = first; u < m * m; u += step) {
+                const int a = u / m, b = u % m;
+                const int I = a < S ? a : a + 1, J = b < S ? b : b + 1;
+                if (I == N && J == N) continue;
+                update(I, J);
+            }
         }
         __syncthreads();
-        for (int e = threadIdx.x; e < n * n; e += blockDim.x) {
-            const int i = e / n, j = e - i * n;
-            double v;
-            if (i == k)
-                v = rowk[j];
-            else if (j == k)
-                v = -colk[i] * pinv;
-            else
-                v = M[e] - colk[i] * rowk[j];
-            M[e] = v;
+        for (int I = w; I < nt; I += GJ_WAVES) {
+            if (I != S) {
+                gj_tile_store(tile(I, S), LD, gj_tile_mm(tile(I, S), LD, X, GJ_XLD, zero, -1.0));
+            } else {
+                const int l = threadIdx.x % 64;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) tile(S, S)[(l & 15) * LD + 4 * (l >> 4) + j] = X[(l & 15) * GJ_XLD + 4 * (l >> 4) + j];
+            }
         }
         __syncthreads();
     }
+}
+
+// Up to COARSE_LDS_MAX rows, in one workgroup: the matrix, padded to whole tiles with the
+// identity, in LDS (132 x 128 FP64, 132 KiB of the 160 KiB available).
+__global__ __launch_bounds__(GJ_THREADS) void k_dense_inverse(int n, double* __restrict__ Mg,
+                                                              double* __restrict__ scal) {
+    constexpr int LD = COARSE_LDS_MAX + 4;
+    __shared__ double M[COARSE_LDS_MAX * LD];
+    __shared__ double X2[2 * 16 * GJ_XLD];
+    __shared__ int bad;
+    const int nt = (n + 15) / 16, np = 16 * nt;
+    for (int e = threadIdx.x; e < np * np; e += GJ_THREADS) {
+        const int i = e / np, j = e - i * np;
+        M[i * LD + j] = i < n && j < n ? Mg[(size_t)i * n + j] : (i == j ? 1.0 : 0.0);
+    }
+    if (threadIdx.x == 0) bad = 0;
     __syncthreads();
-    for (int e = threadIdx.x; e < n * n; e += blockDim.x) Mg[e] = M[e];
+    gj_invert_lds<LD>(M, nt, X2, &bad);
+    for (int e = threadIdx.x; e < n * n; e += GJ_THREADS) {
+        const int i = e / n, j = e - i * n;
+        Mg[e] = M[i * LD + j];
+    }
     if (threadIdx.x == 0) scal[S_COARSE] = bad ? 1.0 : 0.0;
 }
 
-// ------------------------------------------------------------------ blocked Gauss-Jordan
-//
-// Coarsest levels larger than COARSE_LDS_MAX are inverted in place by the same Gauss-Jordan
-// elimination taken a block of BGJ pivots at a time.  With X = M_KK^{-1} for the pivot
-// block K, one block step maps
+// Coarsest levels of more rows: the same elimination taken a block of BGJ pivots at a time.
+// With X = M_KK^{-1} for the pivot block K, one block step maps
 //   M_KJ <- X M_KJ,   M_IJ <- M_IJ - M_IK X M_KJ,   M_IK <- -M_IK X,   M_KK <- X
-// (I, J != K), which is the composition of the scalar steps of K's pivots.  Step k runs as
-// two launches: k_bgj_pivot inverts M_KK (one workgroup, by the same block steps 16 pivots
-// at a time: see bgj_invert_lds; every pivot checked positive) while other workgroups
-// finish step k-1 (its row block, column block and diagonal block), then k_bgj_update
-// applies the rank-BGJ update to every block (I, J) outside row and column K, forming
-// X M_KJ itself; a last k_bgj_pivot finishes the last step.  X of two consecutive steps live in two slots of a scratch
-// buffer.  The 64 x 64 x 64 block products run on the FP64 matrix cores: each of the 16
-// waves of a workgroup owns one 16 x 16 tile of the product and accumulates it over 16
-// steps of V_MFMA_F64_16X16X4F64.
+// (I, J != K), which is the composition of the scalar steps of K's pivots.  Step K is one
+// launch of one workgroup per block, from one copy of the matrix into another (every block
+// is read by its whole row and column, so an in-place step would need a second launch); the
+// workgroup of block (K + 1, K + 1), the first to be dispatched, goes on to invert its
+// result, so that the next step starts with its X.  A workgroup's 64 x 64 x 64 products
+// are split over its 16 wavefronts, one 16 x 16 tile each, 16 steps of
+// V_MFMA_F64_16X16X4F64 per product.
 constexpr int BGJ = 64;
-constexpr int BGJ_THREADS = 1024;
-constexpr int BGJ_RPT = BGJ * BGJ / BGJ_THREADS;  // tile elements per thread
-// Row stride of a tile in LDS: 68 doubles put the 16 rows that an operand read of the
-// matrix instruction touches in different banks (2-way at most), where 64 would put
-// them all in one.
-constexpr int BGJ_LD = 68;
-typedef double bgj_v4 __attribute__((ext_vector_type(4)));
+constexpr int BGJ_RPT = BGJ * BGJ / GJ_THREADS;  // tile elements per thread
+constexpr int BGJ_LD = BGJ + 4;
 
 __device__ __forceinline__ int bgj_size(int n, int b) { return min(BGJ, n - b * BGJ); }
 
-// The i-th block index other than kp.
-__device__ __forceinline__ int bgj_other(int i, int kp) { return i < kp ? i : i + 1; }
-
-// A BGJ x BGJ tile spread over the threads: thread t holds rows t / BGJ + (BGJ_THREADS /
+// A BGJ x BGJ tile spread over the threads: thread t holds rows t / BGJ + (GJ_THREADS /
 // BGJ) m (m < BGJ_RPT) of column t % BGJ.  Every global load of a tile is issued before any
 // is used.
-constexpr int BGJ_RSTEP = BGJ_THREADS / BGJ;
+constexpr int BGJ_RSTEP = GJ_THREADS / BGJ;
 
 // Block (I, J) of the row-major n x n M (zero outside the matrix).
 __device__ __forceinline__ void bgj_fetch(const double* __restrict__ M, int n, int I, int J, double (&v)[BGJ_RPT]) {
@@ -851,7 +971,7 @@ __device__ __forceinline__ void bgj_fetch(const double* __restrict__ M, int n, i
 // A tile stored densely (row stride BGJ), as X is.
 __device__ __forceinline__ void bgj_fetch_dense(const double* __restrict__ X, double (&v)[BGJ_RPT]) {
 #pragma unroll
-    for (int m = 0; m < BGJ_RPT; ++m) v[m] = X[threadIdx.x + m * BGJ_THREADS];
+    for (int m = 0; m < BGJ_RPT; ++m) v[m] = X[threadIdx.x + m * GJ_THREADS];
 }
 
 // Into LDS s (row stride BGJ_LD).
@@ -859,16 +979,6 @@ __device__ __forceinline__ void bgj_put(double* s, const double (&v)[BGJ_RPT]) {
     const int r = threadIdx.x / BGJ, q = threadIdx.x % BGJ;
 #pragma unroll
     for (int m = 0; m < BGJ_RPT; ++m) s[(r + BGJ_RSTEP * m) * BGJ_LD + q] = v[m];
-}
-
-// Writes the tile of registers v to block (I, J) of M.
-__device__ __forceinline__ void bgj_store(double* __restrict__ M, int n, int I, int J, const double (&v)[BGJ_RPT]) {
-    const int bi = bgj_size(n, I), bj = bgj_size(n, J);
-    const int r = threadIdx.x / BGJ, q = threadIdx.x % BGJ;
-    double* base = M + (size_t)(I * BGJ + r) * n + (size_t)J * BGJ + q;
-#pragma unroll
-    for (int m = 0; m < BGJ_RPT; ++m)
-        if (r + BGJ_RSTEP * m < bi && q < bj) base[(size_t)(BGJ_RSTEP * m) * n] = v[m];
 }
 
 // The 16 x 16 tile of a b owned by this wave (tile row w / 4, tile column w % 4 for wave
@@ -895,226 +1005,123 @@ __device__ __forceinline__ int bgj_out_col() {
     return 16 * (w & 3) + (l & 15);
 }
 
-// Writes sign * (this lane's product entries) to block (I, J) of M.
-__device__ __forceinline__ void bgj_store_tile(double* __restrict__ M, int n, int I, int J, bgj_v4 acc, double sign) {
-    const int bi = bgj_size(n, I), bj = bgj_size(n, J), j = bgj_out_col();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = bgj_out_row(r);
-        if (i < bi && j < bj) M[(size_t)(I * BGJ + i) * n + (size_t)J * BGJ + j] = sign * acc[r];
-    }
-}
-
-// Value of v in lane `lane` (uniform) of the wavefront.
-__device__ __forceinline__ double bgj_lane(double v, int lane) {
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), lane);
-    const unsigned hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// 16 x 16 tile product on the FP64 matrix cores: c + sign * (a b), a and b tiles of an LDS
-// matrix with row stride BGJ_LD, c and the result in the instruction's result layout (entry r
-// of lane l is row l / 16 + 4 r, column l % 16).
-__device__ __forceinline__ bgj_v4 bgj_tile_mm(const double* a, const double* b, bgj_v4 c, double sign) {
-    const int l = threadIdx.x % 64, i = l & 15, kk = l >> 4;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-        c = __builtin_amdgcn_mfma_f64_16x16x4f64(sign * a[i * BGJ_LD + 4 * s + kk], b[(4 * s + kk) * BGJ_LD + i], c, 0,
-                                                  0, 0);
-    return c;
-}
-
-__device__ __forceinline__ bgj_v4 bgj_tile_load(const double* t) {
-    const int l = threadIdx.x % 64;
-    bgj_v4 v;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = t[((l >> 4) + 4 * r) * BGJ_LD + (l & 15)];
-    return v;
-}
-
-__device__ __forceinline__ void bgj_tile_store(double* t, bgj_v4 v) {
-    const int l = threadIdx.x % 64;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) t[((l >> 4) + 4 * r) * BGJ_LD + (l & 15)] = v[r];
-}
-
-// In-place inverse of the BGJ x BGJ matrix D in LDS (row stride BGJ_LD) by Gauss-Jordan
-// taken 16 pivots at a time, by the BGJ_THREADS = 16 wavefronts of the block.  For the
-// 16-block S, wavefront 0 inverts D_SS in registers (lane i % 16 holds row i; the pivot
-// row is read from its lane with readlane, so the 16 pivot steps need no barrier); then
-// wavefront w updates tile (w / 4, w % 4) of the 4 x 4 tiling on the matrix cores:
-//   D_SJ <- X D_SJ,   D_IS <- -D_IS X,   D_IJ <- D_IJ - D_IS (X D_SJ),   D_SS <- X.
-// Only the 16-blocks that hold one of the first bk pivots are eliminated (rows and
-// columns from bk on must be those of the identity).  A pivot that is not positive and
-// finite sets *bad; the elimination runs on (the values are then meaningless).
-__device__ void bgj_invert_lds(double* D, int bk, int* bad) {
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-    const int TI = w >> 2, TJ = w & 3;
-    for (int S = 0; 16 * S < bk; ++S) {
-        double* X = D + 16 * S * BGJ_LD + 16 * S;
-        if (w == 0) {
-            const int i = l & 15;
-            double e[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) e[j] = X[i * BGJ_LD + j];
-            bool ok = true;
-#pragma unroll
-            for (int p = 0; p < 16; ++p) {
-                const double piv = bgj_lane(e[p], p);
-                ok = ok && piv > 0.0 && isfinite(piv);
-                const double pinv = 1.0 / piv;
-                // row p: e_pj / piv; other rows: e_ij - (e_ip / piv) e_pj
-                const double sc = (i == p) ? pinv : 1.0;
-                const double cf = (i == p) ? 0.0 : e[p] * pinv;
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    if (j == p) continue;
-                    const double rpj = bgj_lane(e[j], p);
-                    e[j] = fma(-cf, rpj, e[j] * sc);
-                }
-                e[p] = (i == p) ? pinv : -cf;
-            }
-            if (l < 16) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) X[i * BGJ_LD + j] = e[j];
-            }
-            if (!ok && l == 0) *bad = 1;
-        }
-        __syncthreads();
-        const bool own = TI != S || TJ != S;
-        bgj_v4 res = {0.0, 0.0, 0.0, 0.0};
-        if (TI == S && TJ != S) {
-            res = bgj_tile_mm(X, D + 16 * S * BGJ_LD + 16 * TJ, res, 1.0);
-        } else if (TJ == S && TI != S) {
-            res = bgj_tile_mm(D + 16 * TI * BGJ_LD + 16 * S, X, res, -1.0);
-        } else if (own) {
-            // T = X D_SJ in the result layout is the B operand of the next product as it
-            // stands: entry s of lane j + 16 k is T(4 s + k, j).
-            const bgj_v4 t = bgj_tile_mm(X, D + 16 * S * BGJ_LD + 16 * TJ, res, 1.0);
-            res = bgj_tile_load(D + 16 * TI * BGJ_LD + 16 * TJ);
-            const double* a = D + 16 * TI * BGJ_LD + 16 * S;
-            const int i = l & 15, kk = l >> 4;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) res = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[i * BGJ_LD + 4 * s + kk], t[s], res, 0, 0, 0);
-        }
-        __syncthreads();
-        if (own) bgj_tile_store(D + 16 * TI * BGJ_LD + 16 * TJ, res);
-        __syncthreads();
-    }
-}
-
-// Inverse of the diagonal block K of M (bk x bk, padded with the identity), written
-// densely to Xk; false (in every thread) if a pivot was not positive and finite.
-__device__ bool bgj_invert_block(const double* __restrict__ M, int n, int K, double* __restrict__ Xk, double* D,
-                                 int* bad) {
-    const int bk = bgj_size(n, K);
-    double v[BGJ_RPT];
-    bgj_fetch(M, n, K, K, v);
+// Inverse of the diagonal block K held in LDS at D (its bk rows and columns; the rest is set
+// to the identity here), written densely to X; false (in every thread) if a pivot was not
+// positive and finite.
+__device__ bool bgj_invert_block(double* D, int bk, double* X2, int* bad, double* __restrict__ X) {
     const int r = threadIdx.x / BGJ, q = threadIdx.x % BGJ;
 #pragma unroll
-    for (int m = 0; m < BGJ_RPT; ++m)
-        if (r + BGJ_RSTEP * m >= bk) v[m] = (r + BGJ_RSTEP * m == q) ? 1.0 : 0.0;
-    bgj_put(D, v);
+    for (int m = 0; m < BGJ_RPT; ++m) {
+        const int i = r + BGJ_RSTEP * m;
+        if (i >= bk || q >= bk) D[i * BGJ_LD + q] = i == q ? 1.0 : 0.0;
+    }
     if (threadIdx.x == 0) *bad = 0;
     __syncthreads();
-    bgj_invert_lds(D, bk, bad);
+    gj_invert_lds<BGJ_LD>(D, (bk + 15) / 16, X2, bad);
 #pragma unroll
-    for (int m = 0; m < BGJ_RPT; ++m) Xk[threadIdx.x + m * BGJ_THREADS] = D[(r + BGJ_RSTEP * m) * BGJ_LD + q];
+    for (int m = 0; m < BGJ_RPT; ++m) X[threadIdx.x + m * GJ_THREADS] = D[(r + BGJ_RSTEP * m) * BGJ_LD + q];
     return *bad == 0;
 }
 
-__global__ __launch_bounds__(BGJ_THREADS) void k_bgj_pivot(int n, int k, double* __restrict__ M,
-                                                           double* __restrict__ X, double* __restrict__ scal) {
+// X of block 0.
+__global__ __launch_bounds__(GJ_THREADS) void k_bgj_first(int n, const double* __restrict__ M, double* __restrict__ X,
+                                                          double* __restrict__ scal) {
+    __shared__ double D[BGJ * BGJ_LD];
+    __shared__ double X2[2 * 16 * GJ_XLD];
+    __shared__ int bad;
+    double v[BGJ_RPT];
+    bgj_fetch(M, n, 0, 0, v);
+    bgj_put(D, v);
+    __syncthreads();
+    const bool ok = bgj_invert_block(D, bgj_size(n, 0), X2, &bad, X);
+    if (threadIdx.x == 0) scal[S_COARSE] = ok ? 0.0 : 1.0;
+}
+
+// Block step k from M to Mo; X: the inverses of two consecutive pivot blocks.
+__global__ __launch_bounds__(GJ_THREADS) void k_bgj_step(int n, int k, const double* __restrict__ M,
+                                                         double* __restrict__ Mo, double* __restrict__ X,
+                                                         double* __restrict__ scal) {
     __shared__ double sa[BGJ * BGJ_LD];
     __shared__ double sb[BGJ * BGJ_LD];
+    __shared__ double st[BGJ * BGJ_LD];
+    __shared__ double X2[2 * 16 * GJ_XLD];
     __shared__ int bad;
     const int nb = (n + BGJ - 1) / BGJ;
-    const int w = blockIdx.x;
-    if (w == 0) {
-        if (k >= nb) return;
-        const bool ok = bgj_invert_block(M, n, k, X + (size_t)(k & 1) * BGJ * BGJ, sa, &bad);
-        if (threadIdx.x == 0 && (k == 0 || !ok)) scal[S_COARSE] = ok ? 0.0 : 1.0;
-        return;
+    // the next pivot block's workgroup is dispatched first (its place taken by block 0's)
+    const int next = k + 1 < nb ? (k + 1) * nb + k + 1 : 0;
+    const int id = (int)blockIdx.x == 0 ? next : (int)blockIdx.x == next ? 0 : (int)blockIdx.x;
+    const int I = id / nb, J = id % nb;
+    const int bi = bgj_size(n, I), bj = bgj_size(n, J), j = bgj_out_col();
+    const double* Xk = X + (size_t)(k & 1) * BGJ * BGJ;
+    double vx[BGJ_RPT], va[BGJ_RPT], vb[BGJ_RPT], cur[4];
+    bgj_fetch_dense(Xk, vx);
+    if (I != k) bgj_fetch(M, n, I, k, va);
+    if (J != k) bgj_fetch(M, n, k, J, vb);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = bgj_out_row(r);
+        cur[r] = (I != k && J != k && i < bi && j < bj) ? M[(size_t)(I * BGJ + i) * n + (size_t)J * BGJ + j] : 0.0;
     }
-    if (k == 0) return;
-    const int kp = k - 1;  // finish the block step of kp
-    double vx[BGJ_RPT], vb[BGJ_RPT];
-    bgj_fetch_dense(X + (size_t)(kp & 1) * BGJ * BGJ, vx);
-    if (w == 2 * nb - 1) {  // M_{kp kp} <- X
-        bgj_store(M, n, kp, kp, vx);
-        return;
-    }
-    const bool row = w < nb;
-    const int O = bgj_other(row ? w - 1 : w - nb, kp);
-    if (row) {  // M_{kp O} <- X M_{kp O}
-        bgj_fetch(M, n, kp, O, vb);
-        bgj_put(sa, vx);
+    bgj_v4 out = {0.0, 0.0, 0.0, 0.0};
+    bgj_put(sa, vx);
+    if (J != k) {
         bgj_put(sb, vb);
         __syncthreads();
-        bgj_store_tile(M, n, kp, O, bgj_mfma(sa, sb), 1.0);
-    } else {  // M_{O kp} <- -M_{O kp} X
-        bgj_fetch(M, n, O, kp, vb);
-        bgj_put(sa, vb);
-        bgj_put(sb, vx);
+        out = bgj_mfma(sa, sb);  // T = X M_KJ
+    } else {
         __syncthreads();
-        bgj_store_tile(M, n, O, kp, bgj_mfma(sa, sb), -1.0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[r] = sa[bgj_out_row(r) * BGJ_LD + j];  // X
+    }
+    if (I != k) {  // M_IJ - M_IK T, or -M_IK X in column K
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st[bgj_out_row(r) * BGJ_LD + j] = out[r];
+        __syncthreads();
+        bgj_put(sa, va);
+        __syncthreads();
+        const bgj_v4 acc = bgj_mfma(sa, st);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[r] = cur[r] - acc[r];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = bgj_out_row(r);
+        if (i < bi && j < bj) Mo[(size_t)(I * BGJ + i) * n + (size_t)J * BGJ + j] = out[r];
+    }
+    if (I == k + 1 && J == k + 1) {  // the next step's pivot block
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sb[bgj_out_row(r) * BGJ_LD + j] = out[r];
+        __syncthreads();
+        const bool ok = bgj_invert_block(sb, bi, X2, &bad, X + (size_t)((k + 1) & 1) * BGJ * BGJ);
+        if (threadIdx.x == 0 && !ok) scal[S_COARSE] = 1.0;
     }
 }
 
-// M_IJ <- M_IJ - M_IK (X M_KJ) for I, J != K = k; one workgroup per block (I, J).  All four
-// operands are fetched at once; X M_KJ goes through LDS, M_IJ stays in registers.
-__global__ __launch_bounds__(BGJ_THREADS) void k_bgj_update(int n, int k, double* __restrict__ M,
-                                                            const double* __restrict__ X) {
-    __shared__ double sx[BGJ * BGJ_LD];  // X, then M_IK
-    __shared__ double sb[BGJ * BGJ_LD];  // M_KJ
-    __shared__ double st[BGJ * BGJ_LD];  // X M_KJ
+size_t coarse_work_doubles(int n) { return n > COARSE_LDS_MAX ? 2 * (size_t)BGJ * BGJ + (size_t)n * n : 0; }
+
+// An odd number of block steps starts from the scratch copy, so that the last one ends in D.
+double* coarse_start(int n, double* D, double* work) {
     const int nb = (n + BGJ - 1) / BGJ;
-    const int w = blockIdx.x;
-    const int I = bgj_other(w / (nb - 1), k), J = bgj_other(w % (nb - 1), k);
-    const int bi = bgj_size(n, I), bj = bgj_size(n, J), j = bgj_out_col();
-    double vx[BGJ_RPT], vk[BGJ_RPT], vi[BGJ_RPT], cur[4];
-    bgj_fetch_dense(X + (size_t)(k & 1) * BGJ * BGJ, vx);
-    bgj_fetch(M, n, k, J, vk);
-    bgj_fetch(M, n, I, k, vi);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = bgj_out_row(r);
-        cur[r] = (i < bi && j < bj) ? M[(size_t)(I * BGJ + i) * n + (size_t)J * BGJ + j] : 0.0;
-    }
-    bgj_put(sx, vx);
-    bgj_put(sb, vk);
-    __syncthreads();
-    const bgj_v4 t = bgj_mfma(sx, sb);  // T = X M_KJ
-#pragma unroll
-    for (int r = 0; r < 4; ++r) st[bgj_out_row(r) * BGJ_LD + j] = t[r];
-    __syncthreads();
-    bgj_put(sx, vi);
-    __syncthreads();
-    const bgj_v4 acc = bgj_mfma(sx, st);  // M_IK T
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = bgj_out_row(r);
-        if (i < bi && j < bj) M[(size_t)(I * BGJ + i) * n + (size_t)J * BGJ + j] = cur[r] - acc[r];
-    }
+    return n > COARSE_LDS_MAX && (nb & 1) ? work + 2 * (size_t)BGJ * BGJ : D;
 }
 
 void launch_dense_inverse(int n, double* D, double* scal, double* work, hipStream_t s) {
     if (n > COARSE_GLOBAL_MAX) throw Fail{AMG_ERR_ARG, "coarsest level too large for the dense inverse"};
     if (n <= COARSE_LDS_MAX) {
-        k_dense_inverse<<<1, 1024, 0, s>>>(n, D, scal);
+        k_dense_inverse<<<1, GJ_THREADS, 0, s>>>(n, D, scal);
         HIP_LAUNCH_CHECK();
         return;
     }
     if (work == nullptr) throw Fail{AMG_ERR_ARG, "blocked coarse inverse without its scratch"};
     const int nb = (n + BGJ - 1) / BGJ;
-    for (int k = 0; k <= nb; ++k) {
-        k_bgj_pivot<<<k == 0 ? 1 : 2 * nb, BGJ_THREADS, 0, s>>>(n, k, D, work, scal);
+    double* from = coarse_start(n, D, work);
+    double* to = from == D ? work + 2 * (size_t)BGJ * BGJ : D;
+    k_bgj_first<<<1, GJ_THREADS, 0, s>>>(n, from, work, scal);
+    HIP_LAUNCH_CHECK();
+    for (int k = 0; k < nb; ++k) {
+        k_bgj_step<<<nb * nb, GJ_THREADS, 0, s>>>(n, k, from, to, work, scal);
         HIP_LAUNCH_CHECK();
-        if (k < nb && nb > 1) {
-            k_bgj_update<<<(nb - 1) * (nb - 1), BGJ_THREADS, 0, s>>>(n, k, D, work);
-            HIP_LAUNCH_CHECK();
-        }
+        std::swap(from, to);
     }
 }
 
