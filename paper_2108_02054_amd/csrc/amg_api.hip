@@ -630,6 +630,67 @@ GalShape make_posmap(amg_ctx* c, const Csr& L, const Csr& B, const Csr& C, bool 
     return gs;
 }
 
+void release_correction(amg_ctx* c, Level& L) {
+    for (void* q : {(void*)L.Q.val, (void*)L.Q.val32, (void*)L.Q.c16, (void*)L.Q.cblk}) release(c, q);
+    L.Q = Csr{};
+}
+
+// The column offsets of A_0 when its pattern is a well-filled stencil (at most DIA_MAX
+// offsets): level 0 is then kept in diagonal storage.  Empty otherwise.
+void find_stencil(amg_ctx* c) {
+    c->dia_offs.clear();
+    // (the diagonal-storage kernels fuse scalar Jacobi sweeps; block smoothers use CSR)
+    if (std::getenv("AMGMI_NO_DIA") != nullptr || c->prm.block_size > 1) return;
+    const Csr& A = c->lv[0].A;
+    if (A.nrows == 0) return;
+    std::vector<int> offs = dia_offsets(A, c->stream);
+    if ((double)A.nnz < 0.75 * (double)offs.size() * (double)A.nrows) return;
+    c->dia_offs = std::move(offs);
+}
+
+// Whether level l keeps Q_l = (I - M_l A_l) P_l, the coarse correction and the first
+// post-sweep in one pass over A_l P_l's entries, in place of a pass over P_l and one over
+// A_l.  Below level 0, and on a level 0 in CSR, it always pays (128^3 two-fluid step 8.13 ->
+// 7.73 ms, level 0 of a masked 101x83x90 grid 5.90 -> 5.41 ms).  A level 0 in diagonal
+// storage sweeps without index arrays and, with symmetric values, over half of them: there
+// plain aggregation (A P has half of A's entries: 193 -> 184 us per iteration at 128^3) and
+// grids of at most POST_ROWS_MAX rows gain, where launches count (32^3: 1.23 -> 1.13 ms per
+// step; 64^3 81.1 -> 80.3, 80^3 98.5 -> 100.2 us per iteration); above, a smoothed A P of
+// 8 (7-point) or 13 (27-point) entries per row costs more than P and the sweep (128^3 7.73
+// -> 8.41 ms; 27-point 90^3 FP64 200 -> 205 us per iteration), except for the 27-point
+// operator in FP32 (160^3: 17.72 -> 17.36 ms).
+// AMGMI_POST=sweep never does, AMGMI_POST=fused always (where the forms allow).
+constexpr int32_t POST_ROWS_MAX = 1 << 18;
+bool correction_pays(amg_ctx* c, size_t l) {
+    const Level& L = c->lv[l];
+    if (c->prm.block_size > 1 || c->prm.npost < 1 || L.galAP.g == 0) return false;
+    if (const char* e = std::getenv("AMGMI_POST")) return std::strcmp(e, "fused") == 0;
+    if (l > 0 || c->dia_offs.empty()) return true;
+    if (c->prm.aggregation == 1 || L.A.nrows <= POST_ROWS_MAX) return true;
+    return c->dia_offs.size() > 7 && mixed(c);
+}
+
+// Q_l's launch shape and storage (its pattern is A_l P_l's, its values come with the next
+// A_l P_l in the hierarchy's precision).  Rows too long for row blocks leave the level to
+// the separate prolongation and sweep.
+void configure_correction(amg_ctx* c, size_t l, hipStream_t s) {
+    Level& L = c->lv[l];
+    release_correction(c, L);
+    if (!correction_pays(c, l)) return;
+    Csr Q = L.AP;
+    Q.val = nullptr;
+    Q.val32 = nullptr;
+    Q.c16 = nullptr;
+    Q.cblk = nullptr;
+    configure(c, Q, s);
+    if (Q.rpb == 0) return;
+    if (mixed(c))
+        Q.val32 = halloc<float>(c, (size_t)Q.nnz);
+    else
+        Q.val = halloc<double>(c, (size_t)Q.nnz);
+    L.Q = Q;
+}
+
 // Launch shapes of a level's row kernels and Galerkin kernels (Ac: the next level's
 // operator, whose pattern is the second Galerkin product's), with the position maps.
 void set_groups(amg_ctx* c, Level& L, const Csr* Ac, hipStream_t s) {
@@ -716,14 +777,11 @@ void note_dia_symmetry(amg_ctx* c) {
 
 void configure_dia(amg_ctx* c) {
     release_dia(c);
-    // (the diagonal-storage kernels fuse scalar Jacobi sweeps; block smoothers use CSR)
-    if (std::getenv("AMGMI_NO_DIA") != nullptr || c->prm.block_size > 1) return;
     hipStream_t s = c->stream;
     const Csr& A = c->lv[0].A;
-    if (A.nrows == 0) return;
-    const std::vector<int> offs = dia_offsets(A, s);
+    const std::vector<int>& offs = c->dia_offs;
     const int nd = (int)offs.size();
-    if (nd == 0 || (double)A.nnz < 0.75 * (double)nd * (double)A.nrows) return;  // not a well-filled stencil
+    if (nd == 0) return;  // not a well-filled stencil
     Dia D;
     D.ndiag = nd;
     for (int d = 0; d < nd; ++d) D.off.off[d] = offs[(size_t)d];
@@ -807,7 +865,8 @@ void partial_rebuild(amg_ctx* c, const double* val) {
             const bool fused = launch_galerkin_ap<T>(L.A, L.P, L.AP, L.gAP, L.galAP, c->prm.smoother,
                                                      c->prm.jacobi_omega, blocked ? nullptr : L.mv<T>(),
                                                      (l == 0 && !ingested) ? val : nullptr, s,
-                                                     (l == 0 && direct) ? &c->dia : nullptr);
+                                                     (l == 0 && direct) ? &c->dia : nullptr,
+                                                     blocked ? nullptr : L.Q.v<T>());
             smoothed[(size_t)l] = fused && !blocked;
         }
         Trace tr(c, AMG_K_GALERKIN_RAP, l);
@@ -902,6 +961,7 @@ void alloc_reduction(amg_ctx* c) {
     const Csr& A = c->lv[0].A;
     int cap = full_grid_rows(A.nrows, A.rpb, A.g);
     if (c->prm.block_size > 1) cap = std::max(cap, node_grid(A.nrows / c->prm.block_size));
+    if (c->lv[0].Q.rpb > 0) cap = std::max(cap, (A.nrows + c->lv[0].Q.rpb - 1) / c->lv[0].Q.rpb);
     if (cap < RED_BLOCKS) cap = RED_BLOCKS;
     c->rs.cap = cap;
     c->rs.part = halloc<double>(c, RedScratch::doubles(cap));
@@ -969,12 +1029,14 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
     c->lv[0].A = A0;
     c->outer_val = A0.val;
     c->phase_pending = false;
+    std::vector<char> smoothed;  // levels whose A P kernel formed the smoother diagonal
 
     for (int l = 0;; ++l) {
         const Csr A = c->lv[(size_t)l].A;
         const int32_t nl = A.nrows;
         int32_t* diag_pos = dnew<int32_t>((size_t)nl, s);
         validate(c, A, diag_pos, l == 0 ? "input matrix" : "coarse operator");
+        if (l == 0) find_stencil(c);
         if (p.block_size > 1) node_pattern(c, c->lv[(size_t)l]);  // full blocks, node pattern
         const bool stop = tr ? (l >= tr->nlev) : (nl <= p.coarse_enough || l >= p.max_levels - 1);
         if (stop) {
@@ -1070,13 +1132,17 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
             L.R = R;
             L.AP = AP;
             set_groups(c, L, &Ac, s);
+            configure_correction(c, (size_t)l, s);
+            L.m = halloc<double>(c, (size_t)nl * p.block_size);
         }
         Level next;
         next.A = Ac;
         set_groups(c, next, nullptr, s);
         next.gRAP = lane_group((double)Ac.nnz / (Ac.nrows > 0 ? (double)Ac.nrows : 1.0));
-        launch_galerkin_ap<double>(A, P, AP, c->lv[(size_t)l].gAP, c->lv[(size_t)l].galAP, 0, 0.0,
-                                   (double*)nullptr, nullptr, s);
+        // (with the smoother diagonal, and Q_l in FP64: a mixed hierarchy forms its own below)
+        smoothed.push_back(launch_galerkin_ap<double>(
+            A, P, AP, c->lv[(size_t)l].gAP, c->lv[(size_t)l].galAP, p.smoother, p.jacobi_omega,
+            p.block_size > 1 ? nullptr : c->lv[(size_t)l].m, nullptr, s, nullptr, c->lv[(size_t)l].Q.val));
         launch_galerkin_rap<double>(R, AP, Ac, next.gRAP, c->lv[(size_t)l].galRAP, s);
         HIP_CHECK(hipStreamSynchronize(s));
         ph[3] += ms_since(t0);
@@ -1091,10 +1157,9 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
     clear_flags(c);
     for (int l = 0; l + 1 < nlev; ++l) {
         Level& L = c->lv[(size_t)l];
-        L.m = halloc<double>(c, (size_t)L.A.nrows * p.block_size);
         if (p.block_size > 1)
             launch_block_inv<double>(L, p.block_size, p.jacobi_omega, L.m, c->d_flags, s);
-        else
+        else if (!smoothed[(size_t)l])
             launch_smoother_diag<double>(L.A, p.smoother, p.jacobi_omega, L.m, s);
     }
     read_flags(c);
@@ -1163,11 +1228,13 @@ void repattern(amg_ctx* c) {
     int32_t* diag_pos = dnew<int32_t>((size_t)A.nrows, s);
     validate(c, pat, diag_pos, "new pattern");
     dfree(diag_pos, s);
+    find_stencil(c);
     if (c->prm.block_size > 1) node_pattern(c, L0);  // the block kernels need full blocks
     const int nlev = (int)c->lv.size();
     for (int l = 0; l + 1 < nlev; ++l) {
         Level& L = c->lv[(size_t)l];
         Level& N = c->lv[(size_t)l + 1];
+        release_correction(c, L);
         release_csr(c, L.AP);
         Csr AP, Ac;
         symbolic_spgemm(L.A, L.P, AP, s);
@@ -1184,6 +1251,7 @@ void repattern(amg_ctx* c) {
         N.A = Ac;
         release_posmaps(c, L);
         set_groups(c, L, &N.A, s);
+        configure_correction(c, (size_t)l, s);
         N.gRAP = lane_group((double)Ac.nnz / (Ac.nrows > 0 ? (double)Ac.nrows : 1.0));
     }
     if (mixed(c)) L0.A.val32 = halloc<float>(c, (size_t)L0.A.nnz);
@@ -1434,12 +1502,29 @@ T* vcycle_level(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* ep, int
         }
         uc = vcycle_level<T>(c, l + 1, (const T*)C.f, nullptr, nullptr, c_smooths ? 1 : 0);
     }
-    {
+    bool fused = false;
+    int swept = 0;
+    if (L.Q.nrows > 0 && !c->post_sweeps) {  // correction and first post-sweep, from r = f - A u
+        Trace tr(c, AMG_K_PROLONG, l);
+        const bool last = p.npost == 1;
+        swept = 1;
+        if (last && ep && (ep->z64 ? c->rz32 : std::is_same<T, double>::value && out)) {
+            double* z = ep->z64 ? ep->z64 : (double*)out;
+            const double* res = ep->z64 ? ep->r64 : (const double*)f;
+            ep->nb = launch_correct_rz<T>(L.Q, m, rres, uc, cur, res, z, ep->flexible, c->rs, s);
+            ep->z_done = ep->z64 != nullptr;
+            fused = true;
+            if (std::is_same<T, double>::value) cur = out;
+        } else {
+            T* dst = last && out ? out : cur;
+            launch_correct<T>(L.Q, m, rres, uc, cur, dst, s);
+            cur = dst;
+        }
+    } else {
         Trace tr(c, AMG_K_PROLONG, l);
         launch_prolong_add<T>(L.P, uc, cur, s);
     }
-    bool fused = false;
-    for (int it = 0; it < p.npost; ++it) {
+    for (int it = swept; it < p.npost; ++it) {
         const bool last = it == p.npost - 1;
         T* dst = (out && last) ? out : other;
         Trace tr(c, AMG_K_JACOBI, l);
@@ -1494,7 +1579,8 @@ void vcycle_apply(amg_ctx* c, const double* r, double* z, const RzEpilogue* ep =
         }
         // the FP32 cycle forms z and r.z itself only in the level-0 diagonal-storage sweep;
         // every other FP32 path leaves them to the widening pass below
-        const bool fuse = ep && c->rz32 && c->prm.block_size == 1 && c->dia.ndiag > 0 && c->lv.size() > 1;
+        const bool fuse = ep && c->rz32 && c->prm.block_size == 1 && c->lv.size() > 1 &&
+                          (c->dia.ndiag > 0 || L0.Q.nrows > 0);
         RzEpilogue e32{ep ? ep->flexible : 0, 0, r, z};
         const float* res = vcycle_level<float>(c, 0, (const float*)L0.f, nullptr, fuse ? &e32 : nullptr);
         if (e32.z_done) {
@@ -1700,6 +1786,14 @@ amg_status bicgstab(amg_ctx* c, const double* f, double* u, amg_solve_info* info
         HIP_CHECK(hipHostGetDevicePointer(&dptr, c->h_bi, 0));
         c->d_bi = (double*)dptr;
     }
+    // BiCGStab amplifies a change of rounding over its steps: with plain aggregation (60 steps
+    // at 96^3) or an FP32 hierarchy the last digits of the fused correction and sweep moved
+    // the step count by one to three either way, so those keep the two separate passes
+    struct Post {
+        amg_ctx* c;
+        ~Post() { c->post_sweeps = false; }
+    } post{c};
+    c->post_sweeps = mixed(c) || prm.aggregation == 1;
     Csr Aout = L0.A;  // the Krylov operator: the hierarchy's pattern, the outer values
     Aout.val = c->outer_val;
     // y = A x: on the diagonal storage when it holds the Krylov operator (the Krylov SpMV

@@ -144,6 +144,9 @@ struct Level {
     Csr A;       // A_l
     Csr P, R;    // P_l and R_l = P_l^T (empty on the coarsest level)
     Csr AP;      // cached pattern (and values) of A_l P_l, the first Galerkin factor
+    // Q_l = (I - M_l A_l) P_l on the pattern of A_l P_l (ptr and col are AP's), formed with
+    // A_l P_l: the coarse correction and the first post-sweep in one pass (nrows 0: not kept)
+    Csr Q;
     int32_t* agg = nullptr;      // aggregate of each row (setup product, kept for export)
     // block systems: node pattern of A_l (node row pointers, node columns), read by the
     // node-group kernels in place of A_l's own index arrays
@@ -235,6 +238,15 @@ template <typename T>
 void launch_smooth0_residual(const Csr& A, const T* m, const T* f, T* u, T* r, hipStream_t s);
 template <typename T>
 void launch_prolong_add(const Csr& P, const T* uc, T* u, hipStream_t s);
+// Coarse correction and first post-smoothing sweep: with r = f - A u and Q = (I - M A) P,
+// uout = u + M r + Q uc is u' + M (f - A u') for u' = u + P uc (row blocks only, Q.rpb > 0).
+template <typename T>
+void launch_correct(const Csr& Q, const T* m, const T* r, const T* uc, const T* u, T* uout, hipStream_t s);
+// The same as the last step of a level-0 cycle: z in FP64 and the partials of its product
+// with the CG residual; returns their count.
+template <typename T>
+int launch_correct_rz(const Csr& Q, const T* m, const T* r, const T* uc, const T* u, const double* res, double* z,
+                      int flexible, const RedScratch& rs, hipStream_t s);
 // Diagonal storage of the finest operator when its pattern has few distinct column
 // offsets (a stencil): entry (i, i + off[d]) at val[d * n + i], absent entries 0.  The
 // level-0 solve kernels stream it without any index arrays.
@@ -430,7 +442,7 @@ template <typename T>
 void launch_smoother_diag(const Csr& A, int kind, double omega, T* m, hipStream_t s);
 template <typename T>
 bool launch_galerkin_ap(const Csr& A, const Csr& P, const Csr& AP, int g, GalShape gs, int kind, double omega, T* m,
-                        const double* ain, hipStream_t s, const Dia* dia = nullptr);
+                        const double* ain, hipStream_t s, const Dia* dia = nullptr, T* q = nullptr);
 template <typename T>
 void launch_galerkin_rap(const Csr& R, const Csr& AP, const Csr& Ac, int g, GalShape gs, hipStream_t s);
 GalShape pick_galerkin_shape(int32_t nrows, int64_t nnzL, int64_t terms, int maxlen_c, int gforce, int tforce);
@@ -555,6 +567,7 @@ struct amg_ctx {
     int32_t nL = 0;
     int tail = 0;                 // first level of the fused coarse tail (0: none)
     amgmi::Dia dia;               // diagonal storage of A_0 (ndiag 0: CSR kernels)
+    std::vector<int> dia_offs;    // the stencil offsets it stores (empty: not a stencil)
     double* cinv = nullptr;       // dense inverse of the coarsest operator (FP64)
     double* cwork = nullptr;      // scratch of its blocked inverse (more than COARSE_LDS_MAX rows)
     // CG state
@@ -623,6 +636,8 @@ struct amg_ctx {
     // mixed precision: the last level-0 sweep writes z in FP64 with r.z (off with
     // AMGMI_NO_RZ32: a separate widening pass)
     bool rz32 = true;
+    // the cycles of this solve keep the coarse correction and the post-sweep apart (BiCGStab)
+    bool post_sweeps = false;
     bool broken = false;
     std::string err;
 };

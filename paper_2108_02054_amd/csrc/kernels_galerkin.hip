@@ -140,8 +140,9 @@ __global__ __launch_bounds__(TPB) void k_galerkin_rap(int nc, const int* __restr
 // Positions within one B row are distinct, and the LDS operations of a wavefront complete
 // in program order, so every entry of C receives its terms in the row-by-row order.  For
 // C = A P the group also forms the smoother diagonal (the row's squares added in column
-// order), and can take A's values from a new FP64 array, storing the hierarchy's copies
-// on the way.
+// order) and, from both, Q = (I - M A) P (the finished C row is still in LDS, so Q costs
+// its write only), and can take A's values from a new FP64 array, storing the hierarchy's
+// copies on the way.
 
 constexpr int WF_LOADS = 8;            // B terms per lane loaded together
 constexpr int WF_CAP_MAX = 4096;       // longest C row the form takes
@@ -163,7 +164,8 @@ __global__ __launch_bounds__(TPB) void k_galerkin_pos(
     int nrows, int cap, const int* __restrict__ Lptr, const T* __restrict__ Lval, const int* __restrict__ Lbst,
     const uint16_t* __restrict__ Ltof, const T* __restrict__ Bval, const int* __restrict__ Cptr,
     T* __restrict__ Cval, const PT* __restrict__ pos, const int64_t* __restrict__ poff,
-    const int* __restrict__ dpos, int kind, T omega, T* __restrict__ m, const double* __restrict__ lin,
+    const int* __restrict__ dpos, int kind, T omega, T* __restrict__ m, T* __restrict__ Qval,
+    const double* __restrict__ lin,
     double* __restrict__ lout64, T* __restrict__ loutT, const uint8_t* __restrict__ dslot, int64_t dn,
     double* __restrict__ dout64, T* __restrict__ doutT) {
     extern __shared__ __align__(16) unsigned char wf_smem[];
@@ -284,7 +286,26 @@ __global__ __launch_bounds__(TPB) void k_galerkin_pos(
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     for (int q = g; q < len; q += G) Cval[sb + q] = sacc[q];
-    if (m != nullptr && g == 0) m[row] = (kind == 1) ? d / ss : omega / d;
+    if (m == nullptr) return;
+    const T mi = (kind == 1) ? d / ss : omega / d;
+    if (g == 0) m[row] = mi;
+    if (Qval == nullptr || dp < 0) return;
+    // Q = P - M (A P): row i of P is the B row of the diagonal entry, whose terms' positions
+    // place it in the C row
+    const int dbs = Lbst[dp], dto = Ltof[dp];
+    const int dlen = (dp + 1 < le ? (int)Ltof[dp + 1] : nterm) - dto;
+    for (int q = g; q < len; q += G) sacc[q] = -mi * sacc[q];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int k = g; k < dlen; k += G) {
+        const int p = (int)prow[dto + k];
+        if (p < len) sacc[p] = sacc[p] + Bval[dbs + k];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int q = g; q < len; q += G) Qval[sb + q] = sacc[q];
 }
 
 // Terms per row of C = L B.
@@ -457,7 +478,7 @@ static size_t acc_smem(const GalShape& gs) {
 // Launches the position-map kernel for one product with the shape's template arguments.
 template <typename T>
 static void launch_pos(const Csr& L, const Csr& B, const Csr& C, const GalShape& gs, int kind, double omega, T* m,
-                       const double* lin, double* lout64, T* loutT, hipStream_t s, const Dia* dia = nullptr) {
+                       T* q, const double* lin, double* lout64, T* loutT, hipStream_t s, const Dia* dia = nullptr) {
     const size_t sm = acc_smem<T>(gs);
     const int* dp = m != nullptr ? gs.dpos : nullptr;
     const uint8_t* dslot = dia != nullptr ? dia->slot : nullptr;
@@ -468,7 +489,7 @@ static void launch_pos(const Csr& L, const Csr& B, const Csr& C, const GalShape&
 #define AMG_POS_LAUNCH(PT, EPL, TPL)                                                                      \
     AMG_WITH_GS1(gs.g, (k_galerkin_pos<T, GG, PT, EPL, TPL><<<row_blocks(L.nrows, GG), TPB, sm, s>>>(      \
                            L.nrows, gs.cap, L.ptr, L.v<T>(), gs.bst, gs.tof, B.v<T>(), C.ptr, C.v<T>(),     \
-                           (const PT*)gs.pos, gs.off, dp, kind, (T)omega, m, lin, lout64, loutT, dslot,     \
+                           (const PT*)gs.pos, gs.off, dp, kind, (T)omega, m, q, lin, lout64, loutT, dslot,  \
                            (int64_t)L.nrows, d64, dT)))
 #define AMG_POS_LAUNCH_T(PT, EPL)                  \
     do {                                           \
@@ -493,20 +514,21 @@ void launch_smoother_diag(const Csr& A, int kind, double omega, T* m, hipStream_
     HIP_LAUNCH_CHECK();
 }
 
-// AP = A P; with m != nullptr also the smoother diagonal of A, and with ain != nullptr
+// AP = A P; with m != nullptr also the smoother diagonal of A and, with q, the values of
+// Q = (I - M A) P on AP's pattern; and with ain != nullptr
 // the values of A are taken from ain (FP64) and stored on the way: into the diagonal
 // storage `dia` when one is given (its FP64 and, in mixed precision, FP32 arrays), else
 // into A's CSR value arrays.  Only the position-map form fuses these; it returns true when
 // it did (m and the values written).
 template <typename T>
 bool launch_galerkin_ap(const Csr& A, const Csr& P, const Csr& AP, int g, GalShape gs, int kind, double omega, T* m,
-                        const double* ain, hipStream_t s, const Dia* dia) {
+                        const double* ain, hipStream_t s, const Dia* dia, T* q) {
     if (gs.g > 0) {
         const bool to_dia = dia != nullptr && ain != nullptr;
         double* out64 = (!to_dia && ain != nullptr && ain != A.val) ? A.val : nullptr;
         T* outT = nullptr;
         if constexpr (!std::is_same<T, double>::value) outT = (!to_dia && ain != nullptr) ? A.v<T>() : nullptr;
-        launch_pos<T>(A, P, AP, gs, kind, omega, m, ain, out64, outT, s, to_dia ? dia : nullptr);
+        launch_pos<T>(A, P, AP, gs, kind, omega, m, q, ain, out64, outT, s, to_dia ? dia : nullptr);
         return true;
     }
     if (ain != nullptr) return false;  // the caller ingests the values first, then calls again
@@ -519,7 +541,7 @@ bool launch_galerkin_ap(const Csr& A, const Csr& P, const Csr& AP, int g, GalSha
 template <typename T>
 void launch_galerkin_rap(const Csr& R, const Csr& AP, const Csr& Ac, int g, GalShape gs, hipStream_t s) {
     if (gs.g > 0) {
-        launch_pos<T>(R, AP, Ac, gs, 0, 0.0, (T*)nullptr, nullptr, nullptr, (T*)nullptr, s);
+        launch_pos<T>(R, AP, Ac, gs, 0, 0.0, (T*)nullptr, (T*)nullptr, nullptr, nullptr, (T*)nullptr, s);
         return;
     }
     AMG_WITH_G(g, k_galerkin_rap<G, T><<<row_blocks(R.nrows, G), TPB, 0, s>>>(
@@ -528,9 +550,9 @@ void launch_galerkin_rap(const Csr& R, const Csr& AP, const Csr& Ac, int g, GalS
 }
 
 template bool launch_galerkin_ap<double>(const Csr&, const Csr&, const Csr&, int, GalShape, int, double, double*,
-                                         const double*, hipStream_t, const Dia*);
+                                         const double*, hipStream_t, const Dia*, double*);
 template bool launch_galerkin_ap<float>(const Csr&, const Csr&, const Csr&, int, GalShape, int, double, float*,
-                                        const double*, hipStream_t, const Dia*);
+                                        const double*, hipStream_t, const Dia*, float*);
 template void launch_galerkin_rap<double>(const Csr&, const Csr&, const Csr&, int, GalShape, hipStream_t);
 template void launch_galerkin_rap<float>(const Csr&, const Csr&, const Csr&, int, GalShape, hipStream_t);
 template void launch_smoother_diag<double>(const Csr&, int, double, double*, hipStream_t);

@@ -378,6 +378,65 @@ __global__ __launch_bounds__(RB_THREADS) void k_rb_prolong_add(int n, int rpb, c
     }
 }
 
+// Coarse correction and first post-sweep in one pass, uout = u + m r + Q uc with
+// Q = (I - M A) P and r = f - A u: a V-cycle level otherwise reads P for u + P uc and then
+// all of A for the sweep (whose neighbours need the corrected u: a second launch).  Q has
+// A P's entries, about half of A's on a coarse level (3.2 against 6.3 M + 0.7 M of P on
+// level 1 of the 128^3 series), and nothing here needs a neighbour.  uout may be u.
+template <typename T>
+__global__ __launch_bounds__(RB_THREADS) void k_rb_correct(int n, int rpb, const int* __restrict__ ptr, ColSrc cs,
+                                                           const T* __restrict__ val, const T* __restrict__ m,
+                                                           const T* __restrict__ r, const T* __restrict__ uc,
+                                                           const T* u, T* uout) {
+    __shared__ int sptr[RB_THREADS + 1];
+    __shared__ T sp[RB_CAP];
+    const int row0 = xcd_block() * rpb;
+    if (row0 >= n) return;
+    const int row1 = min(row0 + rpb, n);
+    const int tpr = rb_tpr(rpb), t = threadIdx.x / tpr, lane = threadIdx.x & (tpr - 1);
+    const bool own = t < row1 - row0 && lane == 0;
+    const int i = row0 + t;
+    const T w = own ? u[i] + m[i] * r[i] : T(0);
+    rb_load(row0, row1, ptr, cs, xcd_block(), val, [&](int j) { return uc[j]; }, sptr, sp);
+    if (t < row1 - row0) {
+        const T v = rb_rowsum(sptr, sp, t, lane, tpr);
+        if (lane == 0) uout[i] = w + v;
+    }
+}
+
+// The same on level 0 with one post-sweep: z widened to FP64, and the CG's r.z (and, for
+// flexible CG, r.z_old) partials with its residual res.
+template <typename T>
+__global__ __launch_bounds__(RB_THREADS) void k_rb_correct_rz(int n, int rpb, const int* __restrict__ ptr, ColSrc cs,
+                                                              const T* __restrict__ val, const T* __restrict__ m,
+                                                              const T* __restrict__ r, const T* __restrict__ uc,
+                                                              const T* __restrict__ u, const double* __restrict__ res,
+                                                              double* __restrict__ z, int flexible, RedScratch rs) {
+    __shared__ int sptr[RB_THREADS + 1];
+    __shared__ T sp[RB_CAP];
+    const int lb = xcd_block();
+    const int row0 = lb * rpb, row1 = min(row0 + rpb, n);
+    const int tpr = rb_tpr(rpb), t = threadIdx.x / tpr, lane = threadIdx.x & (tpr - 1);
+    const bool own = t < row1 - row0 && lane == 0;
+    const int i = row0 + t;
+    const T w = own ? u[i] + m[i] * r[i] : T(0);
+    const double ri = own ? res[i] : 0.0;
+    const double zo = own && flexible ? z[i] : 0.0;
+    rb_load(row0, row1, ptr, cs, lb, val, [&](int j) { return uc[j]; }, sptr, sp);
+    double loc[2] = {0.0, 0.0};
+    if (t < row1 - row0) {
+        const T v = rb_rowsum(sptr, sp, t, lane, tpr);
+        if (lane == 0) {
+            const double zi = (double)(w + v);
+            z[i] = zi;
+            loc[0] = ri * zi;
+            loc[1] = ri * zo;
+        }
+    }
+    double* const dst[2] = {rs.region(P_RZ), rs.region(P_RZOLD)};
+    block_store<2>(loc, dst, lb);
+}
+
 // Lane-group fallbacks (rows longer than a staged block).
 template <int G>
 __device__ __forceinline__ int group_row(int& lane) {
@@ -521,6 +580,24 @@ void launch_prolong_add(const Csr& P, const T* uc, T* u, hipStream_t s) {
                                      (const T*)nullptr, uc, u, (T*)nullptr));
     }
     HIP_LAUNCH_CHECK();
+}
+template <typename T>
+void launch_correct(const Csr& Q, const T* m, const T* r, const T* uc, const T* u, T* uout, hipStream_t s) {
+    if (Q.rpb <= 0) throw Fail{AMG_ERR_ARG, "correction without row blocks"};
+    timed_launch(k_rb_correct<T>, grid_for(Q.nrows, Q.rpb), RB_THREADS, 0, s, Q.nrows, Q.rpb, (const int*)Q.ptr,
+                 colsrc(Q), (const T*)Q.v<T>(), m, r, uc, u, uout);
+    HIP_LAUNCH_CHECK();
+}
+template <typename T>
+int launch_correct_rz(const Csr& Q, const T* m, const T* r, const T* uc, const T* u, const double* res, double* z,
+                      int flexible, const RedScratch& rs, hipStream_t s) {
+    if (Q.rpb <= 0) throw Fail{AMG_ERR_ARG, "correction without row blocks"};
+    const int nb = (int)grid_for(Q.nrows, Q.rpb);
+    if (nb > rs.cap) throw Fail{AMG_ERR_ARG, "reduction scratch too small"};
+    timed_launch(k_rb_correct_rz<T>, (unsigned)nb, RB_THREADS, 0, s, Q.nrows, Q.rpb, (const int*)Q.ptr, colsrc(Q),
+                 (const T*)Q.v<T>(), m, r, uc, u, res, z, flexible, rs);
+    HIP_LAUNCH_CHECK();
+    return nb;
 }
 template <typename T>
 void launch_coarse_gemv(int n, const double* inv, const T* f, T* u, const double* bad, hipStream_t s) {
@@ -1892,6 +1969,9 @@ void launch_vcycle_tail(const TailArgs<T>& a, hipStream_t s) {
     template void launch_jacobi<T>(const Csr&, const T*, const T*, const T*, T*, hipStream_t);      \
     template void launch_smooth0_residual<T>(const Csr&, const T*, const T*, T*, T*, hipStream_t);  \
     template void launch_prolong_add<T>(const Csr&, const T*, T*, hipStream_t);                     \
+    template void launch_correct<T>(const Csr&, const T*, const T*, const T*, const T*, T*, hipStream_t); \
+    template int launch_correct_rz<T>(const Csr&, const T*, const T*, const T*, const T*, const double*, double*, \
+                                      int, const RedScratch&, hipStream_t);                         \
     template void launch_coarse_gemv<T>(int, const double*, const T*, T*, const double*, hipStream_t); \
     template void launch_vcycle_tail<T>(const TailArgs<T>&, hipStream_t);                          \
     template void launch_dia_scatter<T>(const Csr&, const Dia&, const double*, T*, hipStream_t);    \
