@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libamgmi.so")
-SOURCES = ["amg_api.hip", "kernels_solve.hip", "kernels_galerkin.hip", "kernels_setup.hip",
+SOURCES = ["amg_api.hip", "kernels_solve.hip", "kernels_galerkin.hip", "kernels_setup.hip", "kernels_symbolic.hip",
            "kernels_logcoef.hip", "kernels_krylov.hip", "kernels_block.hip"]
 ARCH = os.environ.get("AMGMI_ARCH", "gfx950")
 CFLAGS = [
@@ -42,7 +42,7 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-def build(verbose: bool = False, jobs: int = 7) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every HIP source for gfx950 and link the shared library."""
     os.makedirs(BUILD, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:

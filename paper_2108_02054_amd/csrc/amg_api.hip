@@ -244,22 +244,14 @@ int lane_group(double avg) {
     return g;
 }
 
-// Largest power-of-two rows per block (<= RB_THREADS) whose blocks never hold more than
-// RB_CAP nonzeros; 0 when a single row is longer than that.
-int pick_rows_per_block(const int32_t* p, int32_t n) {
-    for (int rpb = RB_THREADS; rpb >= 1; rpb >>= 1) {
-        int64_t worst = 0;
-        for (int64_t r0 = 0; r0 < n; r0 += rpb) {
-            const int64_t r1 = r0 + rpb < n ? r0 + rpb : n;
-            const int64_t w = (int64_t)p[r1] - p[r0];
-            if (w > worst) worst = w;
-        }
-        if (worst <= RB_CAP) {
-            // small matrices: fewer rows per workgroup, so that about RB_MIN_BLOCKS
-            // workgroups (four per CU) share the latency of their dependent loads
-            while (rpb > 1 && ((int64_t)n + rpb - 1) / rpb < RB_MIN_BLOCKS) rpb >>= 1;
-            return rpb;
-        }
+int pick_rows_per_block(const int* most, int32_t n) {
+    for (int b = ROW_BLOCK_SIZES - 1; b >= 0; --b) {
+        if (most[b] > RB_CAP) continue;
+        // small matrices: fewer rows per workgroup, so that about RB_MIN_BLOCKS workgroups
+        // (four per CU) share the latency of their dependent loads
+        int rpb = 1 << b;
+        while (rpb > 1 && ((int64_t)n + rpb - 1) / rpb < RB_MIN_BLOCKS) rpb >>= 1;
+        return rpb;
     }
     return 0;
 }
@@ -474,33 +466,52 @@ GalForce galerkin_force() {
     return f;
 }
 
-// Launch shapes of a matrix's row kernels (reads its row pointers back once), and its
-// two-byte column indices for the row-block kernels when every block's columns fit
-// (matrices of at least C16_MIN_NNZ entries; AMGMI_NO_C16 keeps int32 everywhere).
+// Launch shapes of the matrices' row kernels, and two-byte column indices for the row-block
+// kernels of those whose blocks' columns fit (matrices of at least C16_MIN_NNZ entries;
+// AMGMI_NO_C16 keeps int32 everywhere).  The block sizes and the column spans are found on
+// the device and read back once each for all of them (reading every matrix's row pointers
+// back and scanning them on the host took 5 ms of a 128^3 setup).
 constexpr int64_t C16_MIN_NNZ = 1 << 18;
-void configure(amg_ctx* c, Csr& A, hipStream_t s) {
-    A.g = lane_group(A.nrows > 0 ? (double)A.nnz / A.nrows : 1.0);
-    std::vector<int32_t> hp((size_t)A.nrows + 1);
-    HIP_CHECK(hipMemcpyAsync(hp.data(), A.ptr, hp.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipStreamSynchronize(s));
-    A.rpb = lanes_only() ? 0 : pick_rows_per_block(hp.data(), A.nrows);
-    release(c, A.c16);
-    release(c, A.cblk);
-    A.c16 = nullptr;
-    A.cblk = nullptr;
-    if (A.rpb == 0 || A.nnz < C16_MIN_NNZ || std::getenv("AMGMI_NO_C16") != nullptr) return;
-    const int nb = (A.nrows + A.rpb - 1) / A.rpb;
-    int32_t* cblk = halloc<int32_t>(c, (size_t)nb);
-    clear_flags(c);
-    launch_c16_bases(A, cblk, c->d_flags + F_ARG, s);
-    read_flags(c);
-    if (c->h_flags[F_ARG]) {  // some block spans more than two bytes of columns
-        release(c, cblk);
-        return;
+void configure(amg_ctx* c, const std::vector<Csr*>& ms, hipStream_t s) {
+    constexpr int STAT = 16;  // per matrix: ROW_BLOCK_SIZES maxima, then the span flag
+    const size_t nm = ms.size();
+    Temps tmp(s);
+    int* d = tmp.make<int>(nm * STAT);
+    std::vector<int> h(nm * STAT, 0);
+    auto read_back = [&]() {
+        HIP_CHECK(hipMemcpyAsync(h.data(), d, h.size() * sizeof(int), hipMemcpyDeviceToHost, s));
+        HIP_CHECK(hipStreamSynchronize(s));
+    };
+    HIP_CHECK(hipMemsetAsync(d, 0, nm * STAT * sizeof(int), s));
+    for (size_t k = 0; k < nm; ++k) launch_row_blocks(*ms[k], d + k * STAT, s);
+    read_back();
+    bool any = false;
+    for (size_t k = 0; k < nm; ++k) {
+        Csr& A = *ms[k];
+        A.g = lane_group(A.nrows > 0 ? (double)A.nnz / A.nrows : 1.0);
+        A.rpb = lanes_only() ? 0 : pick_rows_per_block(&h[k * STAT], A.nrows);
+        release(c, A.c16);
+        release(c, A.cblk);
+        A.c16 = nullptr;
+        A.cblk = nullptr;
+        if (A.rpb == 0 || A.nnz < C16_MIN_NNZ || std::getenv("AMGMI_NO_C16") != nullptr) continue;
+        A.cblk = halloc<int32_t>(c, (size_t)((A.nrows + A.rpb - 1) / A.rpb));
+        launch_c16_bases(A, A.cblk, d + k * STAT + ROW_BLOCK_SIZES, s);
+        any = true;
     }
-    A.cblk = cblk;
-    A.c16 = halloc<uint16_t>(c, (size_t)A.nnz);
-    launch_c16_fill(A, cblk, A.c16, s);
+    if (!any) return;
+    read_back();
+    for (size_t k = 0; k < nm; ++k) {
+        Csr& A = *ms[k];
+        if (A.cblk == nullptr) continue;
+        if (h[k * STAT + ROW_BLOCK_SIZES]) {  // some block spans more than two bytes of columns
+            release(c, A.cblk);
+            A.cblk = nullptr;
+            continue;
+        }
+        A.c16 = halloc<uint16_t>(c, (size_t)A.nnz);
+        launch_c16_fill(A, A.cblk, A.c16, s);
+    }
 }
 
 template <typename T>
@@ -600,33 +611,39 @@ void configure_node_gal(amg_ctx* c) {
     }
 }
 
-// The launch shape and position map of C = L B (allocated with the hierarchy); with
-// diag, also the diagonal index of every row of L (for the smoother).  Rows with more
-// terms than the form takes, or C rows too long for it, leave the product to the
-// lane-group kernels.
-GalShape make_posmap(amg_ctx* c, const Csr& L, const Csr& B, const Csr& C, bool diag, const GalForce& f,
-                     hipStream_t s) {
-    if (lanes_only() || f.lanes || L.nrows == 0) return {};
+// The pattern of C = L B (tracked with the hierarchy), and the launch shape and position map
+// of its numeric phase; with diag, also the diagonal index of every row of L (for the
+// smoother).  Rows with more terms than the position-map form takes, or C rows too long for
+// it, leave the product to the lane-group kernels.
+GalShape plan_product(amg_ctx* c, const Csr& L, const Csr& B, Csr& C, bool diag, hipStream_t s) {
+    const GalForce f = galerkin_force();
     int64_t* off = halloc<int64_t>(c, (size_t)L.nrows + 1);
-    int64_t max_row = 0;
-    const int64_t terms = count_galerkin_terms(L, B, off, &max_row, s);
-    const auto Cp = to_host(C.ptr, (size_t)C.nrows + 1, s);
-    int maxlen = 0;
-    for (int32_t i = 0; i < C.nrows; ++i) maxlen = std::max(maxlen, Cp[(size_t)i + 1] - Cp[(size_t)i]);
-    GalShape gs = pick_galerkin_shape(L.nrows, L.nnz, terms, maxlen, f.g, f.t);
-    if (gs.g == 0 || !galerkin_terms_fit(max_row)) {
+    SymSizes z;
+    if (!symbolic_count(L, B, C, off, z, s)) {
         release(c, off);
+        symbolic_sorted(L, B, C, s);
+        track(c, C);
         return {};
     }
-    if (f.wide) gs.wide = 1;
-    gs.off = off;
-    gs.terms = terms;
-    const size_t n = (size_t)std::max<int64_t>(terms, 1);
-    gs.pos = gs.wide ? (void*)halloc<uint16_t>(c, n) : (void*)halloc<uint8_t>(c, n);
-    gs.bst = halloc<int32_t>(c, (size_t)std::max<int64_t>(L.nnz, 1));
-    gs.tof = halloc<uint16_t>(c, (size_t)std::max<int64_t>(L.nnz, 1));
-    if (diag) gs.dpos = halloc<int32_t>(c, (size_t)L.nrows + 1);
-    build_galerkin_posmap(L, B, C, gs, s);
+    track(c, C);
+    GalShape gs;
+    if (!lanes_only() && !f.lanes && L.nrows > 0 && galerkin_terms_fit(z.max_terms))
+        gs = pick_galerkin_shape(L.nrows, L.nnz, z.terms, z.maxlen, f.g, f.t);
+    if (gs.g > 0) {
+        if (f.wide) gs.wide = 1;
+        gs.off = off;
+        gs.terms = z.terms;
+        const size_t n = (size_t)std::max<int64_t>(z.terms, 1);
+        gs.pos = gs.wide ? (void*)halloc<uint16_t>(c, n) : (void*)halloc<uint8_t>(c, n);
+        gs.bst = halloc<int32_t>(c, (size_t)std::max<int64_t>(L.nnz, 1));
+        gs.tof = halloc<uint16_t>(c, (size_t)std::max<int64_t>(L.nnz, 1));
+        if (diag) {
+            gs.dpos = halloc<int32_t>(c, (size_t)L.nrows + 1);
+            launch_diag_index(L, gs.dpos, s);
+        }
+    }
+    symbolic_fill(L, B, C, gs, off, z, s);
+    if (gs.g == 0) release(c, off);
     return gs;
 }
 
@@ -670,39 +687,29 @@ bool correction_pays(amg_ctx* c, size_t l) {
     return c->dia_offs.size() > 7 && mixed(c);
 }
 
-// Q_l's launch shape and storage (its pattern is A_l P_l's, its values come with the next
-// A_l P_l in the hierarchy's precision).  Rows too long for row blocks leave the level to
-// the separate prolongation and sweep.
-void configure_correction(amg_ctx* c, size_t l, hipStream_t s) {
+// Launch shapes of level l's transfer operators and of `next` (A_{l+1}), and Q_l's shape and
+// storage where the level keeps it (its pattern is A_l P_l's, its values come with the next
+// A_l P_l in the hierarchy's precision; rows too long for row blocks leave the level to the
+// separate prolongation and sweep).
+void configure_level(amg_ctx* c, size_t l, Csr& next, hipStream_t s) {
     Level& L = c->lv[l];
     release_correction(c, L);
-    if (!correction_pays(c, l)) return;
+    L.gAP = lane_group((double)L.AP.nnz / (L.A.nrows > 0 ? (double)L.A.nrows : 1.0));
     Csr Q = L.AP;
     Q.val = nullptr;
     Q.val32 = nullptr;
     Q.c16 = nullptr;
     Q.cblk = nullptr;
-    configure(c, Q, s);
-    if (Q.rpb == 0) return;
+    std::vector<Csr*> ms{&L.P, &L.R, &next};
+    const bool corr = correction_pays(c, l);
+    if (corr) ms.push_back(&Q);
+    configure(c, ms, s);
+    if (!corr || Q.rpb == 0) return;
     if (mixed(c))
         Q.val32 = halloc<float>(c, (size_t)Q.nnz);
     else
         Q.val = halloc<double>(c, (size_t)Q.nnz);
     L.Q = Q;
-}
-
-// Launch shapes of a level's row kernels and Galerkin kernels (Ac: the next level's
-// operator, whose pattern is the second Galerkin product's), with the position maps.
-void set_groups(amg_ctx* c, Level& L, const Csr* Ac, hipStream_t s) {
-    configure(c, L.A, s);
-    if (L.P.nrows > 0 && Ac != nullptr) {
-        configure(c, L.P, s);
-        configure(c, L.R, s);
-        L.gAP = lane_group((double)L.AP.nnz / (L.A.nrows > 0 ? (double)L.A.nrows : 1.0));
-        const GalForce f = galerkin_force();
-        L.galAP = make_posmap(c, L.A, L.P, L.AP, true, f, s);
-        L.galRAP = make_posmap(c, L.R, L.AP, *Ac, false, f, s);
-    }
 }
 
 // The fused coarse tail starts at the first level t >= 1 from which every level down to
@@ -1036,7 +1043,10 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
         const int32_t nl = A.nrows;
         int32_t* diag_pos = dnew<int32_t>((size_t)nl, s);
         validate(c, A, diag_pos, l == 0 ? "input matrix" : "coarse operator");
-        if (l == 0) find_stencil(c);
+        if (l == 0) {
+            find_stencil(c);
+            configure(c, {&c->lv[0].A}, s);
+        }
         if (p.block_size > 1) node_pattern(c, c->lv[(size_t)l]);  // full blocks, node pattern
         const bool stop = tr ? (l >= tr->nlev) : (nl <= p.coarse_enough || l >= p.max_levels - 1);
         if (stop) {
@@ -1083,7 +1093,7 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
                 launch_strength(Nm, ndiag, eps * eps, nstrong, ntpos, niso, c->d_flags, s);
                 read_flags(c);
                 if (c->h_flags[F_PATTERN]) throw Fail{AMG_ERR_PATTERN, "pattern is not structurally symmetric"};
-                run_mis2(Nm, nstrong, niso, nstate, c->d_flags, c->h_flags, s);
+                run_mis2(Nm, nstrong, niso, nstate, s);
                 nc = run_aggregate(Nm, nstrong, ntpos, nstate, nagg, c->d_flags, c->h_flags, s) * B;
                 launch_node_expand(A, B, Nm, nstrong, nagg, strong, agg, s);
             } else {
@@ -1095,7 +1105,7 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
                 launch_strength(A, diag_pos, eps * eps, strong, tpos, iso, c->d_flags, s);
                 read_flags(c);
                 if (c->h_flags[F_PATTERN]) throw Fail{AMG_ERR_PATTERN, "pattern is not structurally symmetric"};
-                run_mis2(A, strong, iso, state, c->d_flags, c->h_flags, s);
+                run_mis2(A, strong, iso, state, s);
                 nc = run_aggregate(A, strong, tpos, state, agg, c->d_flags, c->h_flags, s);
             }
             c->lv[(size_t)l].agg = agg;
@@ -1116,10 +1126,8 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
         ph[1] += ms_since(t0);
         t0 = Clock::now();
         Csr AP, Ac;
-        symbolic_spgemm(A, P, AP, s);
-        track(c, AP);
-        symbolic_spgemm(R, AP, Ac, s);
-        track(c, Ac);
+        const GalShape galAP = plan_product(c, A, P, AP, true, s);
+        const GalShape galRAP = plan_product(c, R, AP, Ac, false, s);
         AP.val = halloc<double>(c, (size_t)AP.nnz);
         Ac.val = halloc<double>(c, (size_t)Ac.nnz);
         Ac.ncols = Ac.nrows;
@@ -1131,13 +1139,13 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
             L.P = P;
             L.R = R;
             L.AP = AP;
-            set_groups(c, L, &Ac, s);
-            configure_correction(c, (size_t)l, s);
+            L.galAP = galAP;
+            L.galRAP = galRAP;
             L.m = halloc<double>(c, (size_t)nl * p.block_size);
         }
+        configure_level(c, (size_t)l, Ac, s);
         Level next;
         next.A = Ac;
-        set_groups(c, next, nullptr, s);
         next.gRAP = lane_group((double)Ac.nnz / (Ac.nrows > 0 ? (double)Ac.nrows : 1.0));
         // (with the smoother diagonal, and Q_l in FP64: a mixed hierarchy forms its own below)
         smoothed.push_back(launch_galerkin_ap<double>(
@@ -1149,8 +1157,6 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
         dfree(diag_pos, s);
         c->lv.push_back(next);
     }
-    set_groups(c, c->lv.back(), nullptr, s);
-
     alloc_reduction(c);
     auto t0 = Clock::now();
     const int nlev = (int)c->lv.size();
@@ -1229,6 +1235,7 @@ void repattern(amg_ctx* c) {
     validate(c, pat, diag_pos, "new pattern");
     dfree(diag_pos, s);
     find_stencil(c);
+    configure(c, {&L0.A}, s);
     if (c->prm.block_size > 1) node_pattern(c, L0);  // the block kernels need full blocks
     const int nlev = (int)c->lv.size();
     for (int l = 0; l + 1 < nlev; ++l) {
@@ -1237,21 +1244,20 @@ void repattern(amg_ctx* c) {
         release_correction(c, L);
         release_csr(c, L.AP);
         Csr AP, Ac;
-        symbolic_spgemm(L.A, L.P, AP, s);
-        track(c, AP);
+        release_posmaps(c, L);
+        const GalShape galAP = plan_product(c, L.A, L.P, AP, true, s);
+        const GalShape galRAP = plan_product(c, L.R, AP, Ac, false, s);
         AP.val = halloc<double>(c, (size_t)AP.nnz);
         if (mixed(c)) AP.val32 = halloc<float>(c, (size_t)AP.nnz);
-        symbolic_spgemm(L.R, AP, Ac, s);
-        track(c, Ac);
         Ac.ncols = Ac.nrows;
         Ac.val = halloc<double>(c, (size_t)Ac.nnz);
         if (mixed(c)) Ac.val32 = halloc<float>(c, (size_t)Ac.nnz);
         L.AP = AP;
+        L.galAP = galAP;
+        L.galRAP = galRAP;
         release_csr(c, N.A);
         N.A = Ac;
-        release_posmaps(c, L);
-        set_groups(c, L, &N.A, s);
-        configure_correction(c, (size_t)l, s);
+        configure_level(c, (size_t)l, N.A, s);
         N.gRAP = lane_group((double)Ac.nnz / (Ac.nrows > 0 ? (double)Ac.nrows : 1.0));
     }
     if (mixed(c)) L0.A.val32 = halloc<float>(c, (size_t)L0.A.nnz);
@@ -1259,7 +1265,6 @@ void repattern(amg_ctx* c) {
         for (int l = 1; l < nlev; ++l) node_pattern(c, c->lv[(size_t)l]);
     for (Level& L : c->lv) release_node_gal(c, L.ngal);
     c->ngal_ready = false;
-    set_groups(c, c->lv.back(), nullptr, s);
     release(c, c->rs.part);
     alloc_reduction(c);
     configure_tail(c);

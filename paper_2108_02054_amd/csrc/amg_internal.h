@@ -222,7 +222,13 @@ constexpr int RB_CAP = 2048;
 constexpr int RB_MIN_BLOCKS = 1024;
 
 int lane_group(double avg_per_row);  // power of two in [2, 64]
-int pick_rows_per_block(const int32_t* host_ptr, int32_t nrows);  // 0: no row blocking
+// Largest power-of-two rows per block (<= RB_THREADS) whose blocks never hold more than
+// RB_CAP nonzeros; 0 (no row blocking) when a single row is longer than that.  most[b]: the
+// most entries in an aligned block of 2^b rows (launch_row_blocks raises it; cleared by the
+// caller).
+constexpr int ROW_BLOCK_SIZES = 9;
+int pick_rows_per_block(const int* most, int32_t nrows);
+void launch_row_blocks(const Csr& A, int* most, hipStream_t s);
 int red_grid_rows(int nrows, int rpb, int g);
 int full_grid_rows(int nrows, int rpb, int g);
 int red_grid_elems(int64_t n);
@@ -446,12 +452,8 @@ bool launch_galerkin_ap(const Csr& A, const Csr& P, const Csr& AP, int g, GalSha
 template <typename T>
 void launch_galerkin_rap(const Csr& R, const Csr& AP, const Csr& Ac, int g, GalShape gs, hipStream_t s);
 GalShape pick_galerkin_shape(int32_t nrows, int64_t nnzL, int64_t terms, int maxlen_c, int gforce, int tforce);
-// count_galerkin_terms writes the term offsets gs.off (nrows + 1) and returns the number
-// of terms (and the most in one row); build_galerkin_posmap fills gs.pos, gs.bst, gs.tof
-// and, if allocated, gs.dpos (all allocated by the caller in between).
-int64_t count_galerkin_terms(const Csr& L, const Csr& B, int64_t* off, int64_t* max_row, hipStream_t s);
 bool galerkin_terms_fit(int64_t max_row);
-void build_galerkin_posmap(const Csr& L, const Csr& B, const Csr& C, const GalShape& gs, hipStream_t s);
+void launch_diag_index(const Csr& A, int32_t* dpos, hipStream_t s);  // index of each diagonal entry (-1: none)
 
 // ------------------------------------------------------------------ setup
 // flags: device int[8], see SetupFlag.
@@ -459,7 +461,6 @@ enum SetupFlag {
     F_ARG = 0,
     F_PATTERN = 1,
     F_NOT_SPD = 2,
-    F_UNDECIDED = 3,
     F_NOAGG = 4,
     F_BLOCK = 5,
     F_NODEGAL = 6,   // block system: P_l is not P_node (x) I_B with unit values (no node Galerkin plan)
@@ -471,14 +472,27 @@ void launch_validate(const Csr& A, int32_t* diag_pos, int* flags, hipStream_t s)
 void launch_strength(const Csr& A, const int32_t* diag_pos, double eps2, uint8_t* strong, int32_t* tpos,
                      uint8_t* isolated, int* flags, hipStream_t s);
 // distance-2 maximal independent set; returns the number of roots (host sync per round)
-void run_mis2(const Csr& A, const uint8_t* strong, const uint8_t* isolated, uint8_t* state, int* flags,
-              int* h_flags, hipStream_t s);
+void run_mis2(const Csr& A, const uint8_t* strong, const uint8_t* isolated, uint8_t* state, hipStream_t s);
 int32_t run_aggregate(const Csr& A, const uint8_t* strong, const int32_t* tpos, const uint8_t* state,
                       int32_t* agg, int* flags, int* h_flags, hipStream_t s);
 void build_prolongator(const Csr& A, const uint8_t* strong, const int32_t* diag_pos, const int32_t* agg,
                        int32_t nc, int plain, Csr& P, hipStream_t s);
 void build_transpose(const Csr& P, Csr& R, hipStream_t s);
-void symbolic_spgemm(const Csr& A, const Csr& B, Csr& C, hipStream_t s);
+void transpose_sorted(const Csr& P, Csr& R, hipStream_t s);
+// Pattern of C = A B: symbolic_count writes C's row pointers, the offset of each row's first
+// term (off, nrows + 1) and the sizes, and allocates C.col; symbolic_fill writes the
+// columns and, when gs.pos is allocated, the plan gs.pos, gs.bst, gs.tof.  symbolic_count
+// returns false (C freed) when a row has more entries than its tables hold: then
+// symbolic_sorted forms the pattern, without a plan.
+struct SymSizes {
+    int64_t terms = 0, max_terms = 0;  // all, and the most in a row
+    int maxlen = 0;                    // longest row of C
+    double mean_b = 0.0, mean_terms = 0.0;
+};
+bool symbolic_count(const Csr& A, const Csr& B, Csr& C, int64_t* off, SymSizes& z, hipStream_t s);
+void symbolic_fill(const Csr& A, const Csr& B, const Csr& C, const GalShape& gs, const int64_t* off,
+                   const SymSizes& z, hipStream_t s);
+void symbolic_sorted(const Csr& A, const Csr& B, Csr& C, hipStream_t s);
 void exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, hipStream_t s);
 // Systems with B unknowns per node (unknown b of node I is row I*B + b): the node matrix
 // of block Frobenius norms (its arrays are dnew allocations of the caller; for a pattern
@@ -524,7 +538,6 @@ template <typename T>
 void launch_node_rap(const NodeGal& g, int B, const T* aval, const double* lin, double* a64, float* a32, T* cval,
                      hipStream_t s);
 void exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t s);
-int64_t max_i64(const int64_t* in, int64_t n, hipStream_t s);  // synchronises
 
 // ------------------------------------------------------------------ coarse solve
 constexpr int COARSE_LDS_MAX = 128;      // dense FP64 inverse held in one workgroup's LDS

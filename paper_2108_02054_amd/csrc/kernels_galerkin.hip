@@ -308,33 +308,6 @@ __global__ __launch_bounds__(TPB) void k_galerkin_pos(
     for (int q = g; q < len; q += G) Qval[sb + q] = sacc[q];
 }
 
-// Terms per row of C = L B.
-__global__ __launch_bounds__(TPB) void k_count_terms(int nrows, const int* __restrict__ Lptr,
-                                                     const int* __restrict__ Lcol, const int* __restrict__ Bptr,
-                                                     int64_t* __restrict__ cnt) {
-    const int i = xcd_block() * TPB + threadIdx.x;
-    if (i > nrows) return;
-    int64_t c = 0;
-    if (i < nrows)
-        for (int t = Lptr[i]; t < Lptr[i + 1]; ++t) c += Bptr[Lcol[t] + 1] - Bptr[Lcol[t]];
-    cnt[i] = c;  // cnt[nrows] = 0, so the exclusive scan ends with the total
-}
-
-// Per L entry: its B row start and the offset of its first term within its row's terms.
-__global__ __launch_bounds__(TPB) void k_entry_meta(int nrows, const int* __restrict__ Lptr,
-                                                    const int* __restrict__ Lcol, const int* __restrict__ Bptr,
-                                                    int* __restrict__ bst, uint16_t* __restrict__ tof) {
-    const int i = xcd_block() * TPB + threadIdx.x;
-    if (i >= nrows) return;
-    int o = 0;
-    for (int t = Lptr[i]; t < Lptr[i + 1]; ++t) {
-        const int b = Bptr[Lcol[t]];
-        bst[t] = b;
-        tof[t] = (uint16_t)o;
-        o += Bptr[Lcol[t] + 1] - b;
-    }
-}
-
 // Index of each row's diagonal entry (-1 if absent).
 __global__ __launch_bounds__(TPB) void k_diag_index(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                                                     int* __restrict__ dpos) {
@@ -351,72 +324,11 @@ __global__ __launch_bounds__(TPB) void k_diag_index(int n, const int* __restrict
     dpos[i] = (lo < ptr[i + 1] && col[lo] == i) ? lo : -1;
 }
 
-// The position map: 8 lanes per row of C, the L entries in order, the B row's terms
-// across the lanes; each column is found in the sorted C row by binary search.  A column
-// missing from the C row (which a consistent cached pattern never has) maps to the row
-// length, which the numeric kernel skips.
-template <typename PT>
-__global__ __launch_bounds__(TPB) void k_posmap(int nrows, const int* __restrict__ Lptr,
-                                                const int* __restrict__ Lcol, const int* __restrict__ Bptr,
-                                                const int* __restrict__ Bcol, const int* __restrict__ Cptr,
-                                                const int* __restrict__ Ccol, const int64_t* __restrict__ poff,
-                                                PT* __restrict__ pos) {
-    constexpr int G = 8;
-    const int g = threadIdx.x & (G - 1);
-    const int row = (xcd_block() * TPB + (int)threadIdx.x) / G;
-    if (row >= nrows) return;
-    const int cb = Cptr[row], ce = Cptr[row + 1];
-    int64_t o = poff[row];
-    for (int t = Lptr[row]; t < Lptr[row + 1]; ++t) {
-        const int j = Lcol[t];
-        const int b0 = Bptr[j], b1 = Bptr[j + 1];
-        for (int e = b0 + g; e < b1; e += G) {
-            const int J = Bcol[e];
-            int lo = cb, hi = ce;  // lower bound of J in Ccol[cb, ce)
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (Ccol[mid] < J)
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            const int p = (lo < ce && Ccol[lo] == J) ? lo - cb : ce - cb;
-            pos[o + (e - b0)] = (PT)p;
-        }
-        o += b1 - b0;
-    }
-}
-
-int64_t count_galerkin_terms(const Csr& L, const Csr& B, int64_t* off, int64_t* max_row, hipStream_t s) {
-    int64_t* cnt = dnew<int64_t>((size_t)L.nrows + 1, s);
-    k_count_terms<<<row_blocks((int64_t)L.nrows + 1, 1), TPB, 0, s>>>(L.nrows, L.ptr, L.col, B.ptr, cnt);
-    HIP_LAUNCH_CHECK();
-    exclusive_scan_i64(cnt, off, (int64_t)L.nrows + 1, s);
-    *max_row = max_i64(cnt, (int64_t)L.nrows + 1, s);
-    dfree(cnt, s);
-    int64_t total = 0;
-    HIP_CHECK(hipMemcpyAsync(&total, off + L.nrows, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipStreamSynchronize(s));
-    return total;
-}
-
 bool galerkin_terms_fit(int64_t max_row) { return max_row <= WF_TERMS_MAX; }
 
-void build_galerkin_posmap(const Csr& L, const Csr& B, const Csr& C, const GalShape& gs, hipStream_t s) {
-    if (L.nrows == 0) return;
-    k_entry_meta<<<row_blocks(L.nrows, 1), TPB, 0, s>>>(L.nrows, L.ptr, L.col, B.ptr, gs.bst, gs.tof);
-    HIP_LAUNCH_CHECK();
-    if (gs.dpos != nullptr) {
-        k_diag_index<<<row_blocks(L.nrows, 1), TPB, 0, s>>>(L.nrows, L.ptr, L.col, gs.dpos);
-        HIP_LAUNCH_CHECK();
-    }
-    if (gs.terms == 0) return;
-    if (gs.wide)
-        k_posmap<uint16_t><<<row_blocks(L.nrows, 8), TPB, 0, s>>>(L.nrows, L.ptr, L.col, B.ptr, B.col, C.ptr, C.col,
-                                                                   gs.off, (uint16_t*)gs.pos);
-    else
-        k_posmap<uint8_t><<<row_blocks(L.nrows, 8), TPB, 0, s>>>(L.nrows, L.ptr, L.col, B.ptr, B.col, C.ptr, C.col,
-                                                                  gs.off, (uint8_t*)gs.pos);
+void launch_diag_index(const Csr& A, int32_t* dpos, hipStream_t s) {
+    if (A.nrows == 0) return;
+    k_diag_index<<<row_blocks(A.nrows, 1), TPB, 0, s>>>(A.nrows, A.ptr, A.col, dpos);
     HIP_LAUNCH_CHECK();
 }
 

@@ -7,7 +7,6 @@
 // association as the definitions below, so that on the same input they are bit-exact
 // and independent of scheduling.
 #include <rocprim/device/device_radix_sort.hpp>
-#include <rocprim/device/device_reduce.hpp>
 #include <rocprim/device/device_scan.hpp>
 #include <rocprim/device/device_select.hpp>
 
@@ -24,39 +23,62 @@ static inline unsigned blocks_for(int64_t n) {
     return (unsigned)(b > 0 ? b : 1);
 }
 
+// Lanes per row of the setup's row kernels: the power of two in [4, 32] at or below the
+// mean row length (a row's entries are read side by side; with one thread per row they
+// were read a row apart, 344 against 80 us for the strength pass of the 128^3 hierarchy).
+#define AMG_ROW_LANES(A, ...)                                                               \
+    do {                                                                                    \
+        const double mean_ = (A).nrows > 0 ? (double)(A).nnz / (double)(A).nrows : 1.0;     \
+        if (mean_ >= 32.0) { constexpr int G = 32; __VA_ARGS__; }                           \
+        else if (mean_ >= 16.0) { constexpr int G = 16; __VA_ARGS__; }                      \
+        else if (mean_ >= 6.0) { constexpr int G = 8; __VA_ARGS__; }                        \
+        else { constexpr int G = 4; __VA_ARGS__; }                                          \
+    } while (0)
+
 // ------------------------------------------------------------------ input checks
 
 // Rows: monotone pointers, sorted unique in-range columns, finite values and, for a
-// square operator, a positive stored diagonal (diag_pos[i] = position of a_ii).
-__global__ void k_validate(int n, int ncols, int64_t nnz, int need_diag, const int* __restrict__ ptr,
-                           const int* __restrict__ col, const double* __restrict__ val, int* __restrict__ diag_pos,
-                           int* __restrict__ flags) {
-    const int i = blockIdx.x * TPB + threadIdx.x;
-    if (i == 0 && (ptr[0] != 0 || (int64_t)ptr[n] != nnz)) atomicOr(&flags[F_ARG], 1);
+// square operator, a positive stored diagonal (diag_pos[i] = position of a_ii).  G lanes
+// per row, so that a row's entries are read side by side.
+template <int G>
+__global__ __launch_bounds__(TPB) void k_validate(int n, int ncols, int64_t nnz, int need_diag,
+                                                  const int* __restrict__ ptr, const int* __restrict__ col,
+                                                  const double* __restrict__ val, int* __restrict__ diag_pos,
+                                                  int* __restrict__ flags) {
+    const int lane = threadIdx.x & (G - 1);
+    const int i = (int)((blockIdx.x * (int64_t)TPB + threadIdx.x) / G);
+    if (i == 0 && lane == 0 && (ptr[0] != 0 || (int64_t)ptr[n] != nnz)) atomicOr(&flags[F_ARG], 1);
     if (i >= n) return;
     const int b = ptr[i], e = ptr[i + 1];
     if (b > e || b < 0 || (int64_t)e > nnz) {
-        atomicOr(&flags[F_ARG], 1);
-        if (need_diag) diag_pos[i] = -1;
+        if (lane == 0) {
+            atomicOr(&flags[F_ARG], 1);
+            if (need_diag) diag_pos[i] = -1;
+        }
         return;
     }
-    int d = -1, prev = -1;
-    for (int k = b; k < e; ++k) {
+    int d = -1;
+    bool bad = false;
+    for (int k = b + lane; k < e; k += G) {
         const int j = col[k];
-        if (j < 0 || j >= ncols || j <= prev) atomicOr(&flags[F_ARG], 1);
-        prev = j;
-        if (val != nullptr && !isfinite(val[k])) atomicOr(&flags[F_ARG], 1);
+        const int prev = k > b ? col[k - 1] : -1;
+        if (j < 0 || j >= ncols || j <= prev) bad = true;
+        if (val != nullptr && !isfinite(val[k])) bad = true;
         if (j == i) d = k;
     }
+    if (bad) atomicOr(&flags[F_ARG], 1);
     if (!need_diag) return;
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) d = max(d, __shfl_xor(d, o, G));
+    if (lane != 0) return;
     diag_pos[i] = d;
     if (d < 0 || (val != nullptr && !(val[d] > 0.0))) atomicOr(&flags[F_NOT_SPD], 1);
 }
 
 void launch_validate(const Csr& A, int32_t* diag_pos, int* flags, hipStream_t s) {
     const int need_diag = diag_pos != nullptr ? 1 : 0;
-    k_validate<<<blocks_for(A.nrows), TPB, 0, s>>>(A.nrows, A.ncols, A.nnz, need_diag, A.ptr, A.col, A.val,
-                                                   diag_pos, flags);
+    AMG_ROW_LANES(A, (k_validate<G><<<blocks_for((int64_t)A.nrows * G), TPB, 0, s>>>(
+                         A.nrows, A.ncols, A.nnz, need_diag, A.ptr, A.col, A.val, diag_pos, flags)));
     HIP_LAUNCH_CHECK();
 }
 
@@ -65,15 +87,18 @@ void launch_validate(const Csr& A, int32_t* diag_pos, int* flags, hipStream_t s)
 // Entry k = (i,j), j != i, is strong when (a_ij * a_ji) > eps2 * |a_ii * a_jj|, with
 // eps2 = eps * eps.  tpos[k] is the position of (j,i); a missing (j,i) means the pattern is
 // not structurally symmetric.  A row without strong entries is isolated.
-__global__ void k_strength(int n, const int* __restrict__ ptr, const int* __restrict__ col,
-                           const double* __restrict__ val, const int* __restrict__ diag_pos, double eps2,
-                           uint8_t* __restrict__ strong, int* __restrict__ tpos, uint8_t* __restrict__ isolated,
-                           int* __restrict__ flags) {
-    const int i = xcd_block() * TPB + threadIdx.x;
+template <int G>
+__global__ __launch_bounds__(TPB) void k_strength(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+                                                  const double* __restrict__ val, const int* __restrict__ diag_pos,
+                                                  double eps2, uint8_t* __restrict__ strong, int* __restrict__ tpos,
+                                                  uint8_t* __restrict__ isolated, int* __restrict__ flags) {
+    const int lane = threadIdx.x & (G - 1);
+    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
     if (i >= n) return;
     const double aii = val[diag_pos[i]];
-    bool any = false;
-    for (int k = ptr[i]; k < ptr[i + 1]; ++k) {
+    int any = 0;
+    const int e = ptr[i + 1];
+    for (int k = ptr[i] + lane; k < e; k += G) {
         const int j = col[k];
         if (j == i) {
             strong[k] = 0;
@@ -100,15 +125,17 @@ __global__ void k_strength(int n, const int* __restrict__ ptr, const int* __rest
         const double rhs = eps2 * fabs(aii * ajj);
         const bool s = lhs > rhs;
         strong[k] = s ? 1 : 0;
-        any = any || s;
+        any |= s ? 1 : 0;
     }
-    isolated[i] = any ? 0 : 1;
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) any |= __shfl_xor(any, o, G);
+    if (lane == 0) isolated[i] = any ? 0 : 1;
 }
 
 void launch_strength(const Csr& A, const int32_t* diag_pos, double eps2, uint8_t* strong, int32_t* tpos,
                      uint8_t* isolated, int* flags, hipStream_t s) {
-    k_strength<<<blocks_for(A.nrows), TPB, 0, s>>>(A.nrows, A.ptr, A.col, A.val, diag_pos, eps2, strong, tpos,
-                                                   isolated, flags);
+    AMG_ROW_LANES(A, (k_strength<G><<<blocks_for((int64_t)A.nrows * G), TPB, 0, s>>>(
+                         A.nrows, A.ptr, A.col, A.val, diag_pos, eps2, strong, tpos, isolated, flags)));
     HIP_LAUNCH_CHECK();
 }
 
@@ -132,7 +159,9 @@ __global__ void k_mis_init(int n, const uint8_t* __restrict__ isolated, uint8_t*
 // m1[i] = max priority of an undecided node among i and its strong neighbours (0: none).
 __global__ void k_mis_max1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                            const uint8_t* __restrict__ strong, const uint8_t* __restrict__ state,
-                           uint64_t* __restrict__ m1) {
+                           uint64_t* __restrict__ m1,
+                           const int* __restrict__ go) {
+    if (go != nullptr && *go == 0) return;
     const int i = xcd_block() * TPB + threadIdx.x;
     if (i >= n) return;
     uint64_t m = state[i] == ST_UNDECIDED ? mix64((uint64_t)i) : 0;
@@ -153,7 +182,9 @@ __global__ void k_mis_max1(int n, const int* __restrict__ ptr, const int* __rest
 // priority nearby has been decided before.)
 __global__ void k_mis_max2(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                            const uint8_t* __restrict__ strong, const uint64_t* __restrict__ m1,
-                           uint8_t* __restrict__ state) {
+                           uint8_t* __restrict__ state,
+                           const int* __restrict__ go) {
+    if (go != nullptr && *go == 0) return;
     const int i = xcd_block() * TPB + threadIdx.x;
     if (i >= n || state[i] != ST_UNDECIDED) return;
     uint64_t m = m1[i];
@@ -168,7 +199,9 @@ __global__ void k_mis_max2(int n, const int* __restrict__ ptr, const int* __rest
 // c1[i] = i is a root or has a strong root neighbour.
 __global__ void k_mis_cover1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                              const uint8_t* __restrict__ strong, const uint8_t* __restrict__ state,
-                             uint8_t* __restrict__ c1) {
+                             uint8_t* __restrict__ c1,
+                           const int* __restrict__ go) {
+    if (go != nullptr && *go == 0) return;
     const int i = xcd_block() * TPB + threadIdx.x;
     if (i >= n) return;
     bool c = state[i] == ST_ROOT;
@@ -181,7 +214,9 @@ __global__ void k_mis_cover1(int n, const int* __restrict__ ptr, const int* __re
 // undecided raises the flag for another round.
 __global__ void k_mis_cover2(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                              const uint8_t* __restrict__ strong, const uint8_t* __restrict__ c1,
-                             uint8_t* __restrict__ state, int* __restrict__ flags) {
+                             uint8_t* __restrict__ state, int* __restrict__ left,
+                             const int* __restrict__ go) {
+    if (go != nullptr && *go == 0) return;
     const int i = xcd_block() * TPB + threadIdx.x;
     if (i >= n || state[i] != ST_UNDECIDED) return;
     bool c = c1[i] != 0;
@@ -190,29 +225,39 @@ __global__ void k_mis_cover2(int n, const int* __restrict__ ptr, const int* __re
     if (c)
         state[i] = ST_REMOVED;
     else
-        flags[F_UNDECIDED] = 1;
+        left[0] = 1;
 }
 
-void run_mis2(const Csr& A, const uint8_t* strong, const uint8_t* isolated, uint8_t* state, int* flags,
-              int* h_flags, hipStream_t s) {
+constexpr int MIS_BATCH = 8;
+
+void run_mis2(const Csr& A, const uint8_t* strong, const uint8_t* isolated, uint8_t* state, hipStream_t s) {
     const int n = A.nrows;
     uint64_t* m1 = dnew<uint64_t>((size_t)n, s);
     uint8_t* c1 = dnew<uint8_t>((size_t)n, s);
     const unsigned nb = blocks_for(n);
     k_mis_init<<<nb, TPB, 0, s>>>(n, isolated, state);
     HIP_LAUNCH_CHECK();
-    for (int round = 0;; ++round) {
-        k_mis_max1<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, m1);
-        k_mis_max2<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, m1, state);
-        k_mis_cover1<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, c1);
-        HIP_CHECK(hipMemsetAsync(flags + F_UNDECIDED, 0, sizeof(int), s));
-        k_mis_cover2<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, c1, state, flags);
+    // Rounds are queued MIS_BATCH at a time and read back once: a round whose predecessor
+    // left no undecided node returns at once (left[r]: round r left one), where reading the
+    // flag back after every round left the device idle for each of about seven per level.
+    int* left = dnew<int>(MIS_BATCH, s);
+    int h_left = 0;
+    for (int round = 0;; round += MIS_BATCH) {
+        HIP_CHECK(hipMemsetAsync(left, 0, MIS_BATCH * sizeof(int), s));
+        for (int r = 0; r < MIS_BATCH; ++r) {
+            const int* go = r == 0 ? nullptr : left + r - 1;
+            k_mis_max1<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, m1, go);
+            k_mis_max2<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, m1, state, go);
+            k_mis_cover1<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, c1, go);
+            k_mis_cover2<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, c1, state, left + r, go);
+        }
         HIP_LAUNCH_CHECK();
-        HIP_CHECK(hipMemcpyAsync(h_flags, flags, F_COUNT * sizeof(int), hipMemcpyDeviceToHost, s));
+        HIP_CHECK(hipMemcpyAsync(&h_left, left + MIS_BATCH - 1, sizeof(int), hipMemcpyDeviceToHost, s));
         HIP_CHECK(hipStreamSynchronize(s));
-        if (!h_flags[F_UNDECIDED]) break;
+        if (!h_left) break;
         if (round > 4096) throw Fail{AMG_ERR_HIP, "MIS-2 did not terminate"};
     }
+    dfree(left, s);
     dfree(m1, s);
     dfree(c1, s);
 }
@@ -285,20 +330,6 @@ void exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, hipStream_t 
 
 void exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t s) {
     scan_exclusive<int64_t, int64_t>(in, out, n, s);
-}
-
-int64_t max_i64(const int64_t* in, int64_t n, hipStream_t s) {
-    int64_t* out = dnew<int64_t>(1, s);
-    size_t bytes = 0;
-    HIP_CHECK(rocprim::reduce(nullptr, bytes, in, out, (size_t)n, rocprim::maximum<int64_t>(), s));
-    void* tmp = dalloc(bytes, s);
-    HIP_CHECK(rocprim::reduce(tmp, bytes, in, out, (size_t)n, rocprim::maximum<int64_t>(), s));
-    int64_t h = 0;
-    HIP_CHECK(hipMemcpyAsync(&h, out, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipStreamSynchronize(s));
-    dfree(tmp, s);
-    dfree(out, s);
-    return h;
 }
 
 int32_t run_aggregate(const Csr& A, const uint8_t* strong, const int32_t* tpos, const uint8_t* state, int32_t* agg,
@@ -429,104 +460,151 @@ void launch_node_expand(const Csr& A, int B, const Csr& Nm, const uint8_t* nstro
 // kept; an isolated row keeps a_ii only.  ratio_i = sum_j |aF_ij| / |d_i| (column order);
 // rho = max_i ratio_i (exact, so order free) is accumulated on the IEEE bit pattern, which
 // orders like the value for positive doubles.
-__global__ void k_filter(int n, const int* __restrict__ ptr, const int* __restrict__ col,
-                         const double* __restrict__ val, const uint8_t* __restrict__ strong,
-                         const int* __restrict__ diag_pos, const int* __restrict__ agg, double* __restrict__ dF,
-                         unsigned long long* __restrict__ rho_bits) {
-    const int i = xcd_block() * TPB + threadIdx.x;
-    if (i >= n) return;
-    const bool iso = agg[i] < 0;
-    double d = val[diag_pos[i]];
-    if (!iso)
-        for (int k = ptr[i]; k < ptr[i + 1]; ++k)
-            if (col[k] != i && !strong[k]) d += val[k];
-    double s = 0.0;
-    for (int k = ptr[i]; k < ptr[i + 1]; ++k) {
-        if (col[k] == i)
-            s += fabs(d);
-        else if (!iso && strong[k])
-            s += fabs(val[k]);
+// G lanes per row read the entries side by side; every lane then adds them all in column
+// order, each passed round from the lane that read it.
+template <int G>
+__global__ __launch_bounds__(TPB) void k_filter(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+                                                const double* __restrict__ val, const uint8_t* __restrict__ strong,
+                                                const int* __restrict__ diag_pos, const int* __restrict__ agg,
+                                                double* __restrict__ dF, unsigned long long* __restrict__ rho_bits) {
+    __shared__ unsigned long long sm[TPB / 64];
+    const int lane = threadIdx.x & (G - 1);
+    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    unsigned long long bits = 0;
+    if (i < n) {
+        const bool iso = agg[i] < 0;
+        const int b = ptr[i], e = ptr[i + 1];
+        // kind of an entry: 0 dropped, 1 weak, 2 strong, 3 diagonal
+        auto kind = [&](int k) { return k >= e ? 0 : col[k] == i ? 3 : iso ? 0 : strong[k] ? 2 : 1; };
+        double d = val[diag_pos[i]];
+        for (int c0 = b; c0 < e; c0 += G) {
+            const int k = c0 + lane, w = kind(k);
+            const double v = k < e ? val[k] : 0.0;
+            for (int t = 0; t < min(G, e - c0); ++t) {
+                const double vt = __shfl(v, t, G);
+                if (__shfl(w, t, G) == 1) d += vt;
+            }
+        }
+        double s = 0.0;
+        for (int c0 = b; c0 < e; c0 += G) {
+            const int k = c0 + lane, w = kind(k);
+            const double v = k < e ? val[k] : 0.0;
+            for (int t = 0; t < min(G, e - c0); ++t) {
+                const double vt = __shfl(v, t, G);
+                const int wt = __shfl(w, t, G);
+                if (wt == 3)
+                    s += fabs(d);
+                else if (wt == 2)
+                    s += fabs(vt);
+            }
+        }
+        if (lane == 0) dF[i] = d;
+        bits = (unsigned long long)__double_as_longlong(s / fabs(d));
     }
-    dF[i] = d;
-    const double ratio = s / fabs(d);
-    atomicMax(rho_bits, (unsigned long long)__double_as_longlong(ratio));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long x = __shfl_xor(bits, o, 64);
+        bits = x > bits ? x : bits;
+    }
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = bits;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < TPB / 64; ++k) bits = sm[k] > bits ? sm[k] : bits;
+        // (the cached read leaves the atomic to the few workgroups that raise the maximum)
+        if (bits > __hip_atomic_load(rho_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMax(rho_bits, bits);
+    }
 }
 
-// Number of distinct aggregates among the columns of row i of A_F (diagonal and strong
-// entries); that is the length of row i of A_F P_tent and of the smoothed P.
-__global__ void k_pcount(int n, const int* __restrict__ ptr, const int* __restrict__ col,
-                         const uint8_t* __restrict__ strong, const int* __restrict__ agg, int plain,
-                         int* __restrict__ cnt) {
-    const int i = xcd_block() * TPB + threadIdx.x;
+// Aggregate of every entry's column among the entries A_F keeps (diagonal and strong), -1
+// for the others; a row of an isolated node keeps none.
+template <int G>
+__global__ __launch_bounds__(TPB) void k_entry_agg(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+                                                   const uint8_t* __restrict__ strong, const int* __restrict__ agg,
+                                                   int* __restrict__ eagg) {
+    const int lane = threadIdx.x & (G - 1);
+    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
     if (i >= n) return;
-    if (agg[i] < 0) {
-        cnt[i] = 0;
-        return;
+    const bool iso = agg[i] < 0;
+    const int e = ptr[i + 1];
+    for (int k = ptr[i] + lane; k < e; k += G) {
+        const int j = col[k];
+        eagg[k] = !iso && (j == i || strong[k]) ? agg[j] : -1;
     }
-    if (plain) {
-        cnt[i] = 1;
-        return;
-    }
+}
+
+// Number of distinct aggregates among the columns of row i of A_F; that is the length of
+// row i of A_F P_tent and of the smoothed P.  first[k]: entry k is its aggregate's first.
+template <int G>
+__global__ __launch_bounds__(TPB) void k_pcount(int n, const int* __restrict__ ptr, const int* __restrict__ eagg,
+                                                uint8_t* __restrict__ first, int* __restrict__ cnt) {
+    const int lane = threadIdx.x & (G - 1);
+    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    if (i >= n) return;
     const int b = ptr[i], e = ptr[i + 1];
     int c = 0;
-    for (int k = b; k < e; ++k) {
-        const int j = col[k];
-        if (j != i && !strong[k]) continue;
-        const int a = agg[j];
-        bool seen = false;
-        for (int q = b; q < k && !seen; ++q) {
-            const int jq = col[q];
-            if ((jq == i || strong[q]) && agg[jq] == a) seen = true;
-        }
-        if (!seen) ++c;
+    for (int k = b + lane; k < e; k += G) {
+        const int a = eagg[k];
+        bool f = a >= 0;
+        for (int q = b; q < k && f; ++q) f = eagg[q] != a;
+        first[k] = f ? 1 : 0;
+        c += f ? 1 : 0;
     }
-    cnt[i] = c;
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, G);
+    if (lane == 0) cnt[i] = c;
 }
 
 // Row i of P = P_tent - (omega / d_i) * (A_F P_tent), omega = (4/3) / rho.  Columns are
 // the distinct aggregates of the row in increasing order; for column J the sum over the
-// row's entries with aggregate J is taken in column order starting from 0.
-__global__ void k_pfill(int n, const int* __restrict__ ptr, const int* __restrict__ col,
-                        const double* __restrict__ val, const uint8_t* __restrict__ strong,
-                        const int* __restrict__ agg, const double* __restrict__ dF,
-                        const unsigned long long* __restrict__ rho_bits, int plain, const int* __restrict__ Pptr,
-                        int* __restrict__ Pcol, double* __restrict__ Pval) {
-    const int i = xcd_block() * TPB + threadIdx.x;
+// row's entries with aggregate J is taken in column order starting from 0.  The lane of an
+// aggregate's first entry walks the row once for its place (the smaller aggregates' first
+// entries) and its sum.
+template <int G>
+__global__ __launch_bounds__(TPB) void k_pfill(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+                                               const double* __restrict__ val, const int* __restrict__ agg,
+                                               const int* __restrict__ eagg, const uint8_t* __restrict__ first,
+                                               const double* __restrict__ dF,
+                                               const unsigned long long* __restrict__ rho_bits,
+                                               const int* __restrict__ Pptr, int* __restrict__ Pcol,
+                                               double* __restrict__ Pval) {
+    const int lane = threadIdx.x & (G - 1);
+    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
     if (i >= n) return;
     const int ai = agg[i];
     if (ai < 0) return;
-    int pos = Pptr[i];
-    if (plain) {
-        Pcol[pos] = ai;
-        Pval[pos] = 1.0;
-        return;
-    }
+    const int p0 = Pptr[i];
     const double rho = __longlong_as_double((long long)*rho_bits);
     const double omega = (4.0 / 3.0) / rho;
-    const double scale = omega / dF[i];
+    const double di = dF[i];
+    const double scale = omega / di;
     const int b = ptr[i], e = ptr[i + 1];
-    int last = -1;
-    for (;;) {
-        int J = 0x7fffffff;
-        for (int k = b; k < e; ++k) {
-            const int j = col[k];
-            if (j != i && !strong[k]) continue;
-            const int a = agg[j];
-            if (a > last && a < J) J = a;
-        }
-        if (J == 0x7fffffff) break;
+    for (int k = b + lane; k < e; k += G) {
+        if (!first[k]) continue;
+        const int J = eagg[k];
+        int r = 0;
         double sJ = 0.0;
-        for (int k = b; k < e; ++k) {
-            const int j = col[k];
-            if (j != i && !strong[k]) continue;
-            if (agg[j] == J) sJ += (j == i) ? dF[i] : val[k];
+        for (int q = b; q < e; ++q) {
+            const int a = eagg[q];
+            if (a == J) sJ += (col[q] == i) ? di : val[q];
+            r += (a >= 0 && a < J && first[q]) ? 1 : 0;
         }
         const double pt = (J == ai) ? 1.0 : 0.0;
-        Pcol[pos] = J;
-        Pval[pos] = pt - scale * sJ;
-        ++pos;
-        last = J;
+        Pcol[p0 + r] = J;
+        Pval[p0 + r] = pt - scale * sJ;
     }
+}
+
+// Plain aggregation, P = P_tent: one unit entry per aggregated row.
+__global__ __launch_bounds__(TPB) void k_plain_count(int n, const int* __restrict__ agg, int* __restrict__ cnt) {
+    const int i = blockIdx.x * TPB + threadIdx.x;
+    if (i < n) cnt[i] = agg[i] < 0 ? 0 : 1;
+}
+__global__ __launch_bounds__(TPB) void k_plain_fill(int n, const int* __restrict__ agg, const int* __restrict__ Pptr,
+                                                    int* __restrict__ Pcol, double* __restrict__ Pval) {
+    const int i = blockIdx.x * TPB + threadIdx.x;
+    if (i >= n || agg[i] < 0) return;
+    Pcol[Pptr[i]] = agg[i];
+    Pval[Pptr[i]] = 1.0;
 }
 
 void build_prolongator(const Csr& A, const uint8_t* strong, const int32_t* diag_pos, const int32_t* agg, int32_t nc,
@@ -535,15 +613,22 @@ void build_prolongator(const Csr& A, const uint8_t* strong, const int32_t* diag_
     const unsigned nb = blocks_for(n);
     double* dF = nullptr;
     unsigned long long* rho_bits = nullptr;
-    if (!plain) {
+    int* eagg = nullptr;
+    uint8_t* first = nullptr;
+    int* cnt = dnew<int>((size_t)n + 1, s);
+    if (plain) {
+        k_plain_count<<<nb, TPB, 0, s>>>(n, agg, cnt);
+    } else {
         dF = dnew<double>((size_t)n, s);
         rho_bits = dnew<unsigned long long>(1, s);
+        eagg = dnew<int>((size_t)A.nnz, s);
+        first = dnew<uint8_t>((size_t)A.nnz, s);
         HIP_CHECK(hipMemsetAsync(rho_bits, 0, sizeof(unsigned long long), s));
-        k_filter<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, A.val, strong, diag_pos, agg, dF, rho_bits);
-        HIP_LAUNCH_CHECK();
+        AMG_ROW_LANES(A, (k_filter<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, A.col, A.val, strong, diag_pos,
+                                                                               agg, dF, rho_bits)));
+        AMG_ROW_LANES(A, (k_entry_agg<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, A.col, strong, agg, eagg)));
+        AMG_ROW_LANES(A, (k_pcount<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, eagg, first, cnt)));
     }
-    int* cnt = dnew<int>((size_t)n + 1, s);
-    k_pcount<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, agg, plain, cnt);
     HIP_LAUNCH_CHECK();
     HIP_CHECK(hipMemsetAsync(cnt + n, 0, sizeof(int), s));
     P.nrows = n;
@@ -556,11 +641,15 @@ void build_prolongator(const Csr& A, const uint8_t* strong, const int32_t* diag_
     P.nnz = nnz;
     P.col = dnew<int32_t>((size_t)nnz, s);
     P.val = dnew<double>((size_t)nnz, s);
-    k_pfill<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, A.val, strong, agg, dF, rho_bits, plain, P.ptr, P.col, P.val);
+    if (plain)
+        k_plain_fill<<<nb, TPB, 0, s>>>(n, agg, P.ptr, P.col, P.val);
+    else
+        AMG_ROW_LANES(A, (k_pfill<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(
+                             n, A.ptr, A.col, A.val, agg, eagg, first, dF, rho_bits, P.ptr, P.col, P.val)));
     HIP_LAUNCH_CHECK();
     dfree(cnt, s);
-    if (dF) dfree(dF, s);
-    if (rho_bits) dfree(rho_bits, s);
+    for (void* q : {(void*)dF, (void*)rho_bits, (void*)eagg, (void*)first})
+        if (q) dfree(q, s);
 }
 
 // ------------------------------------------------------------------ sorting helpers
@@ -636,15 +725,9 @@ static unsigned gs_blocks(int64_t n) {
     return (unsigned)(b > 0 ? b : 1);
 }
 
-// R = P^T with sorted columns: sort the entries by (column, row).
-void build_transpose(const Csr& P, Csr& R, hipStream_t s) {
+// R = P^T (its arrays allocated) by sorting the entries by (column, row).
+void transpose_sorted(const Csr& P, Csr& R, hipStream_t s) {
     const int64_t nnz = P.nnz;
-    R.nrows = P.ncols;
-    R.ncols = P.nrows;
-    R.nnz = nnz;
-    R.ptr = dnew<int32_t>((size_t)R.nrows + 1, s);
-    R.col = dnew<int32_t>((size_t)nnz, s);
-    R.val = dnew<double>((size_t)nnz, s);
     uint64_t* k0 = dnew<uint64_t>((size_t)nnz, s);
     uint64_t* k1 = dnew<uint64_t>((size_t)nnz, s);
     int* i0 = dnew<int>((size_t)nnz, s);
@@ -695,9 +778,10 @@ __global__ void k_spgemm_expand(int n, const int* __restrict__ Aptr, const int* 
     }
 }
 
-// Pattern of C = A B (structural: every product term creates its entry), sorted columns:
-// expand all candidate (row, column) pairs, sort, and keep the unique ones.
-void symbolic_spgemm(const Csr& A, const Csr& B, Csr& C, hipStream_t s) {
+// Pattern of C = A B (structural: every product term creates its entry), sorted columns, for
+// products with rows too long for symbolic_count's tables: expand all candidate (row,
+// column) pairs, sort, and keep the unique ones.
+void symbolic_sorted(const Csr& A, const Csr& B, Csr& C, hipStream_t s) {
     const int n = A.nrows;
     int64_t* ub = dnew<int64_t>((size_t)n + 1, s);
     int64_t* off = dnew<int64_t>((size_t)n + 1, s);

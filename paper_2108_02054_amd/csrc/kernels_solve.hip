@@ -142,45 +142,6 @@ __device__ __forceinline__ void rb_load(int row0, int row1, const int* __restric
     }
 }
 
-// One base per row block: the smallest column of its rows (rows are sorted, so the
-// first entry of each); *wide = 1 when a block's columns span more than two bytes.
-__global__ __launch_bounds__(TPB) void k_c16_bases(int n, int rpb, const int* __restrict__ ptr,
-                                                   const int* __restrict__ col, int* __restrict__ cblk,
-                                                   int* __restrict__ wide) {
-    const int b = blockIdx.x * TPB + threadIdx.x;
-    const int nb = (n + rpb - 1) / rpb;
-    if (b >= nb) return;
-    const int r0 = b * rpb, r1 = min(r0 + rpb, n);
-    int lo = INT_MAX, hi = INT_MIN;
-    for (int r = r0; r < r1; ++r)
-        if (ptr[r] < ptr[r + 1]) {
-            lo = min(lo, col[ptr[r]]);
-            hi = max(hi, col[ptr[r + 1] - 1]);
-        }
-    if (lo > hi) lo = hi = 0;  // no entries
-    cblk[b] = lo;
-    if ((int64_t)hi - lo > 65535) wide[0] = 1;
-}
-
-__global__ __launch_bounds__(TPB) void k_c16_fill(int n, int rpb, const int* __restrict__ ptr,
-                                                  const int* __restrict__ col, const int* __restrict__ cblk,
-                                                  uint16_t* __restrict__ c16) {
-    const int r = blockIdx.x * TPB + threadIdx.x;
-    if (r >= n) return;
-    const int base = cblk[r / rpb];
-    for (int k = ptr[r]; k < ptr[r + 1]; ++k) c16[k] = (uint16_t)(col[k] - base);
-}
-
-void launch_c16_bases(const Csr& A, int32_t* cblk, int* wide, hipStream_t s) {
-    const int nb = (A.nrows + A.rpb - 1) / A.rpb;
-    timed_launch(k_c16_bases, (unsigned)((nb + TPB - 1) / TPB), TPB, 0, s, A.nrows, A.rpb, A.ptr, A.col, cblk, wide);
-    HIP_LAUNCH_CHECK();
-}
-void launch_c16_fill(const Csr& A, const int32_t* cblk, uint16_t* c16, hipStream_t s) {
-    timed_launch(k_c16_fill, (unsigned)((A.nrows + TPB - 1) / TPB), TPB, 0, s, A.nrows, A.rpb, A.ptr, A.col, cblk, c16);
-    HIP_LAUNCH_CHECK();
-}
-
 // Threads per staged row: a block of rpb rows gives each row RB_THREADS / rpb threads
 // (at most a wavefront), which add strided subsets of the row and combine them with a
 // fixed butterfly; with one thread per row the sum is in plain column order.

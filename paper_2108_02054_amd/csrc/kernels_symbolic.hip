@@ -1,0 +1,514 @@
+// kernels_symbolic.hip -- patterns of the setup (Algorithm 1): the sparsity of a Galerkin
+// product with its plan for the numeric phase, the transpose R = P^T, and the launch shapes
+// of a matrix's row kernels.  Integer work only; every result is independent of scheduling.
+#include <algorithm>
+
+#include "amg_internal.h"
+
+namespace amgmi {
+
+constexpr int TPB = 256;
+
+// Orders a wavefront's own LDS accesses (they complete in program order; this keeps the
+// compiler from moving them).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int G>
+__device__ __forceinline__ int group_sum_i(int v) {
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, G);
+    return v;
+}
+
+// Raises *p to v.  Thousands of workgroups share one cell: the cached read first leaves the
+// atomic to the few that raise it (a stale value only costs an atomic).
+__device__ __forceinline__ void raise_max(int* p, int v) {
+    if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMax(p, v);
+}
+
+// ------------------------------------------------------------------ symbolic product
+//
+// Pattern of C = A B (structural: every product term creates its entry), sorted columns,
+// and the numeric phase's plan: the position of every term's column in its C row.  A group
+// of G lanes owns a row of C and collects the columns its terms reach in a hash table in
+// LDS (open addressing, integer compare-and-swap).  Two passes: k_sym_count counts the
+// row's entries and terms; k_sym_fill collects them again, ranks the distinct columns (the
+// rank is the place in the sorted row), and writes the columns and, term by term, the
+// positions, which is the same walk once more.  Bound by the gathers of the B rows, read
+// three times; nothing per term is written but its one- or two-byte position.  The former
+// form wrote a 64-bit (row, column) key per term, radix-sorted the keys, kept the unique
+// ones and found each term's position by a binary search in the finished row: 16.5 ms of
+// a 128^3 setup (108 M terms at level 0).
+
+constexpr int SYM_H_MIN = 64, SYM_H_MAX = 8192;  // table slots per row
+constexpr size_t SYM_SMEM = 32768;               // LDS per workgroup aimed at
+
+__device__ __forceinline__ unsigned sym_hash(int c, int shift) { return ((unsigned)c * 2654435761u) >> shift; }
+
+// Inserts column c; 1 when it was not there, -1 when the table is full.
+__device__ __forceinline__ int sym_insert(int* tab, int H, int shift, int c) {
+    unsigned h = sym_hash(c, shift);
+    for (int p = 0; p < H; ++p, h = (h + 1) & (unsigned)(H - 1)) {
+        int cur = __hip_atomic_load(&tab[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        if (cur == c) return 0;
+        if (cur == -1) {
+            cur = atomicCAS(&tab[h], -1, c);
+            if (cur == -1) return 1;
+            if (cur == c) return 0;
+        }
+    }
+    return -1;
+}
+
+// Walks the terms of the A row [b, e): the group's lanes take 1 << lg lanes per B row, so
+// several B rows at a time, the first term of four such steps in flight together.
+// f(A entry - b, term within the B row, column); entry(k, first term's offset, B row start)
+// once per A entry, before its terms.  Returns the row's terms.
+template <int G, class E, class F>
+__device__ __forceinline__ int sym_walk(int lane, int lg, int b, int e, const int* __restrict__ Acol,
+                                        const int* __restrict__ Bptr, const int* __restrict__ Bcol, E entry, F f) {
+    const int per = G >> lg, sub = lane >> lg, q0 = lane & ((1 << lg) - 1), step = 1 << lg;
+    int carry = 0;
+    for (int c0 = b; c0 < e; c0 += G) {
+        const int k = c0 + lane;
+        int b0 = 0, len = 0;
+        if (k < e) {
+            const int j = Acol[k];
+            b0 = Bptr[j];
+            len = Bptr[j + 1] - b0;
+        }
+        int incl = len;
+#pragma unroll
+        for (int o = 1; o < G; o <<= 1) {
+            const int t = __shfl_up(incl, o, G);
+            if (lane >= o) incl += t;
+        }
+        const int to = carry + incl - len;
+        carry += __shfl(incl, G - 1, G);
+        if (k < e) entry(k, to, b0);
+        const int nt = min(G, e - c0);
+        constexpr int U = 4;
+        for (int e0 = 0; e0 < nt; e0 += U * per) {
+            int bb[U], ll[U], tt[U], cc[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int x = e0 + u * per + sub, xs = x < G ? x : G - 1;
+                bb[u] = __shfl(b0, xs, G);
+                tt[u] = __shfl(to, xs, G);
+                ll[u] = __shfl(len, xs, G);
+                if (x >= nt) ll[u] = 0;
+                if (q0 < ll[u]) cc[u] = Bcol[bb[u] + q0];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (q0 < ll[u]) f(tt[u] + q0, cc[u]);
+                for (int q = q0 + step; q < ll[u]; q += step) f(tt[u] + q, Bcol[bb[u] + q]);
+            }
+        }
+    }
+    return carry;
+}
+
+// cnt[i], terms[i] (both with a zero at n, so that exclusive scans end in the totals);
+// stat: {overflow, most terms in a row, longest row}.
+template <int G>
+__global__ __launch_bounds__(TPB) void k_sym_count(int n, int lg, int H, int shift, const int* __restrict__ Aptr,
+                                                   const int* __restrict__ Acol, const int* __restrict__ Bptr,
+                                                   const int* __restrict__ Bcol, int* __restrict__ cnt,
+                                                   int64_t* __restrict__ terms, int* __restrict__ stat) {
+    extern __shared__ __align__(16) unsigned char sym_smem[];
+    const int lane = threadIdx.x & (G - 1), gi = threadIdx.x / G;
+    int* tab = reinterpret_cast<int*>(sym_smem) + (size_t)gi * H;
+    const int row = xcd_block() * ((int)blockDim.x / G) + gi;
+    if (row > n) return;  // groups leave whole
+    if (row == n) {
+        if (lane == 0) {
+            cnt[n] = 0;
+            terms[n] = 0;
+        }
+        return;
+    }
+    for (int s = lane; s < H; s += G) tab[s] = -1;
+    wave_fence();
+    int u = 0, full = 0;
+    const int nterm = sym_walk<G>(lane, lg, Aptr[row], Aptr[row + 1], Acol, Bptr, Bcol, [](int, int, int) {},
+                                  [&](int, int c) {
+                                      const int r = sym_insert(tab, H, shift, c);
+                                      u += r > 0;
+                                      full |= r < 0;
+                                  });
+    u = group_sum_i<G>(u);
+    full = group_sum_i<G>(full);
+    if (lane == 0) {
+        cnt[row] = u;
+        terms[row] = nterm;
+        raise_max(&stat[0], full ? 1 : 0);
+        raise_max(&stat[1], nterm);
+        raise_max(&stat[2], u);
+    }
+}
+
+__global__ void k_sym_totals(int n, const int* __restrict__ ptr, const int64_t* __restrict__ off,
+                             const int* __restrict__ stat, int64_t* __restrict__ out) {
+    out[0] = ptr[n];
+    out[1] = off[n];
+    for (int k = 0; k < 3; ++k) out[2 + k] = stat[k];
+}
+
+// Columns of row i of C in order, and with pos the plan: per A entry its B row start and
+// first term's offset, per term its column's position in the C row.
+template <int G, typename PT>
+__global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shift, const int* __restrict__ Aptr,
+                                                  const int* __restrict__ Acol, const int* __restrict__ Bptr,
+                                                  const int* __restrict__ Bcol, const int* __restrict__ Cptr,
+                                                  int* __restrict__ Ccol, const int64_t* __restrict__ off,
+                                                  int* __restrict__ bst, uint16_t* __restrict__ tof,
+                                                  PT* __restrict__ pos) {
+    extern __shared__ __align__(16) unsigned char sym_smem[];
+    const int lane = threadIdx.x & (G - 1), gi = threadIdx.x / G;
+    unsigned char* base = sym_smem + (size_t)gi * 8 * H;
+    int* tab = reinterpret_cast<int*>(base);
+    uint16_t* rank = reinterpret_cast<uint16_t*>(base + (size_t)4 * H);  // of the column in each slot
+    uint16_t* list = reinterpret_cast<uint16_t*>(base + (size_t)6 * H);  // the occupied slots
+    const int row = xcd_block() * ((int)blockDim.x / G) + gi;
+    if (row >= n) return;
+    for (int s = lane; s < H; s += G) tab[s] = -1;
+    wave_fence();
+    const int b = Aptr[row], e = Aptr[row + 1];
+    sym_walk<G>(
+        lane, lg, b, e, Acol, Bptr, Bcol,
+        [&](int k, int to, int b0) {
+            if (pos != nullptr) {
+                bst[k] = b0;
+                tof[k] = (uint16_t)to;
+            }
+        },
+        [&](int, int c) { sym_insert(tab, H, shift, c); });
+    wave_fence();
+    int u = 0;
+    const int shiftg = (threadIdx.x & 63) & ~(G - 1);
+    const unsigned long long mine = G == 64 ? ~0ull : ((1ull << G) - 1);
+    for (int s0 = 0; s0 < H; s0 += G) {  // H is a multiple of 64
+        const bool occ = tab[s0 + lane] != -1;
+        const unsigned long long m = (__ballot(occ) >> shiftg) & mine;
+        if (occ) list[u + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)(s0 + lane);
+        u += __popcll(m);
+    }
+    wave_fence();
+    const int cb = Cptr[row], len = Cptr[row + 1] - cb;
+    for (int x0 = 0; x0 < u; x0 += G) {
+        const int x = x0 + lane;
+        const int slot = x < u ? list[x] : 0;
+        const int c = x < u ? tab[slot] : -1;
+        int r = 0;
+        for (int y0 = 0; y0 < u; y0 += G) {
+            const int v = y0 + lane < u ? tab[list[y0 + lane]] : 0x7fffffff;
+            const int ny = min(G, u - y0);
+            for (int t = 0; t < ny; ++t) r += __shfl(v, t, G) < c;
+        }
+        if (x < u && r < len) {
+            Ccol[cb + r] = c;
+            rank[slot] = (uint16_t)r;
+        }
+    }
+    if (pos == nullptr) return;
+    wave_fence();
+    PT* prow = pos + off[row];
+    sym_walk<G>(lane, lg, b, e, Acol, Bptr, Bcol, [](int, int, int) {}, [&](int t, int c) {
+        unsigned h = sym_hash(c, shift);
+        for (int p = 0; p < H && tab[h] != c; ++p) h = (h + 1) & (unsigned)(H - 1);
+        prow[t] = (PT)rank[h];
+    });
+}
+
+static int log2_ceil(double v) {
+    int l = 0;
+    while (l < 30 && (double)(1 << l) < v) ++l;
+    return l;
+}
+
+// Lanes per row from the mean number of terms (a lane for every four to eight of them, and
+// wide groups for large tables, whose clearing and compaction they share).
+static int sym_group(double mean_terms, int H) {
+    int g = mean_terms <= 32.0 ? 8 : mean_terms <= 160.0 ? 16 : mean_terms <= 640.0 ? 32 : 64;
+    while (g < 64 && H > 32 * g) g <<= 1;
+    return g;
+}
+
+#define AMG_WITH_SYM_G(g, ...)                                              \
+    do {                                                                    \
+        switch (g) {                                                        \
+            case 8: { constexpr int G = 8; __VA_ARGS__; } break;            \
+            case 16: { constexpr int G = 16; __VA_ARGS__; } break;          \
+            case 32: { constexpr int G = 32; __VA_ARGS__; } break;          \
+            default: { constexpr int G = 64; __VA_ARGS__; } break;          \
+        }                                                                   \
+    } while (0)
+
+// Threads per workgroup: whole wavefronts, as many rows as SYM_SMEM holds.
+static int sym_threads(int g, size_t row_bytes) {
+    int t = TPB;
+    while (t > 64 && (size_t)(t / g) * row_bytes > SYM_SMEM) t >>= 1;
+    return t;
+}
+
+bool symbolic_count(const Csr& A, const Csr& B, Csr& C, int64_t* off, SymSizes& z, hipStream_t s) {
+    const int n = A.nrows;
+    C.nrows = n;
+    C.ncols = B.ncols;
+    C.ptr = dnew<int32_t>((size_t)n + 1, s);
+    int32_t* cnt = dnew<int32_t>((size_t)n + 1, s);
+    int64_t* terms = dnew<int64_t>((size_t)n + 1, s);
+    int* stat = dnew<int>(4, s);
+    int64_t* tot = dnew<int64_t>(5, s);
+    const double mean_b = B.nrows > 0 ? (double)B.nnz / (double)B.nrows : 0.0;
+    z.mean_b = mean_b;
+    z.mean_terms = n > 0 ? (double)A.nnz / (double)n * mean_b : 0.0;
+    const int lg_b = std::min(log2_ceil(mean_b), 6);
+    bool fits = false;
+    int64_t h[5] = {0, 0, 0, 0, 0};
+    // rows keep a small share of their terms as distinct columns: start from half the mean
+    // number of terms and enlarge the table when some row overflows it
+    for (int H = std::min(SYM_H_MAX, std::max(SYM_H_MIN, 1 << log2_ceil(0.5 * z.mean_terms)));;) {
+        const int g = sym_group(z.mean_terms, H), lg = std::min(lg_b, log2_ceil(g));
+        const int t = sym_threads(g, (size_t)4 * H), rows = t / g, shift = 32 - log2_ceil(H);
+        HIP_CHECK(hipMemsetAsync(stat, 0, 4 * sizeof(int), s));
+        AMG_WITH_SYM_G(g, (k_sym_count<G><<<(unsigned)(n / rows + 1), t, (size_t)rows * 4 * H, s>>>(
+                              n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, cnt, terms, stat)));
+        HIP_LAUNCH_CHECK();
+        exclusive_scan_i32(cnt, C.ptr, (int64_t)n + 1, s);
+        exclusive_scan_i64(terms, off, (int64_t)n + 1, s);
+        k_sym_totals<<<1, 1, 0, s>>>(n, C.ptr, off, stat, tot);
+        HIP_LAUNCH_CHECK();
+        HIP_CHECK(hipMemcpyAsync(h, tot, sizeof(h), hipMemcpyDeviceToHost, s));
+        HIP_CHECK(hipStreamSynchronize(s));
+        fits = h[2] == 0;
+        if (fits || H == SYM_H_MAX || h[1] >= ((int64_t)1 << 31)) break;
+        H = std::min(SYM_H_MAX, 4 * H);
+    }
+    dfree(cnt, s);
+    dfree(terms, s);
+    dfree(stat, s);
+    dfree(tot, s);
+    z.terms = h[1];
+    z.max_terms = h[3];
+    z.maxlen = (int)h[4];
+    if (z.terms >= ((int64_t)1 << 31)) {
+        dfree(C.ptr, s);
+        C.ptr = nullptr;
+        throw Fail{AMG_ERR_ARG, "Galerkin product too large for int32 indexing"};
+    }
+    if (!fits) {
+        dfree(C.ptr, s);
+        C.ptr = nullptr;
+        return false;
+    }
+    C.nnz = h[0];
+    C.col = dnew<int32_t>((size_t)C.nnz, s);
+    return true;
+}
+
+void symbolic_fill(const Csr& A, const Csr& B, const Csr& C, const GalShape& gs, const int64_t* off,
+                   const SymSizes& z, hipStream_t s) {
+    const int n = A.nrows;
+    if (n == 0) return;
+    const int H = std::min(SYM_H_MAX, std::max(SYM_H_MIN, 1 << log2_ceil(1.5 * z.maxlen)));
+    const int g = sym_group(z.mean_terms, H), lg = std::min(std::min(log2_ceil(z.mean_b), 6), log2_ceil(g));
+    const int t = sym_threads(g, (size_t)8 * H), rows = t / g, shift = 32 - log2_ceil(H);
+    const unsigned nb = (unsigned)((n + rows - 1) / rows);
+    if (gs.wide)
+        AMG_WITH_SYM_G(g, (k_sym_fill<G, uint16_t><<<nb, t, (size_t)rows * 8 * H, s>>>(
+                              n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, C.ptr, C.col, off, gs.bst, gs.tof,
+                              (uint16_t*)gs.pos)));
+    else
+        AMG_WITH_SYM_G(g, (k_sym_fill<G, uint8_t><<<nb, t, (size_t)rows * 8 * H, s>>>(
+                              n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, C.ptr, C.col, off, gs.bst, gs.tof,
+                              (uint8_t*)gs.pos)));
+    HIP_LAUNCH_CHECK();
+}
+
+// ------------------------------------------------------------------ transpose
+//
+// R = P^T with sorted columns: the entries of each column of P are counted, scattered in
+// any order into the column's row of R, and each row of R is then put in order by the rank
+// of its (distinct) row indices.  Rows of R longer than TR_ROW_MAX would make the ranking
+// quadratic: such a matrix is sorted as a whole.
+
+constexpr int TR_ROW_MAX = 2048;
+
+__global__ __launch_bounds__(TPB) void k_tr_count(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+                                                  int* __restrict__ cnt) {
+    const int i = xcd_block() * TPB + threadIdx.x;
+    if (i >= n) return;
+    for (int k = ptr[i]; k < ptr[i + 1]; ++k) atomicAdd(&cnt[col[k]], 1);
+}
+
+// cnt holds each column's count and counts down to its first place.
+__global__ __launch_bounds__(TPB) void k_tr_scatter(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+                                                    const int* __restrict__ Rptr, int* __restrict__ cnt,
+                                                    int2* __restrict__ tmp) {
+    const int i = xcd_block() * TPB + threadIdx.x;
+    if (i >= n) return;
+    for (int k = ptr[i]; k < ptr[i + 1]; ++k) {
+        const int J = col[k];
+        tmp[Rptr[J] + atomicSub(&cnt[J], 1) - 1] = make_int2(i, k);
+    }
+}
+
+template <int G>
+__global__ __launch_bounds__(TPB) void k_tr_order(int nc, const int* __restrict__ Rptr, const int2* __restrict__ tmp,
+                                                  const double* __restrict__ v, int* __restrict__ Rcol,
+                                                  double* __restrict__ Rval) {
+    const int lane = threadIdx.x & (G - 1);
+    const int row = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    if (row >= nc) return;
+    const int b = Rptr[row], u = Rptr[row + 1] - b;
+    for (int x0 = 0; x0 < u; x0 += G) {
+        const int x = x0 + lane;
+        const int2 t = x < u ? tmp[b + x] : make_int2(-1, 0);
+        int r = 0;
+        for (int y0 = 0; y0 < u; y0 += G) {
+            const int w = y0 + lane < u ? tmp[b + y0 + lane].x : 0x7fffffff;
+            const int ny = min(G, u - y0);
+            for (int k = 0; k < ny; ++k) r += __shfl(w, k, G) < t.x;
+        }
+        if (x < u) {
+            Rcol[b + r] = t.x;
+            Rval[b + r] = v[t.y];
+        }
+    }
+}
+
+__global__ __launch_bounds__(TPB) void k_max_len(int n, const int* __restrict__ cnt, int* __restrict__ out) {
+    __shared__ int sm[TPB / 64];
+    const int i = blockIdx.x * TPB + threadIdx.x;
+    int v = i < n ? cnt[i] : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < TPB / 64; ++k) v = max(v, sm[k]);
+        raise_max(out, v);
+    }
+}
+
+void build_transpose(const Csr& P, Csr& R, hipStream_t s) {
+    const int64_t nnz = P.nnz;
+    R.nrows = P.ncols;
+    R.ncols = P.nrows;
+    R.nnz = nnz;
+    R.ptr = dnew<int32_t>((size_t)R.nrows + 1, s);
+    R.col = dnew<int32_t>((size_t)nnz, s);
+    R.val = dnew<double>((size_t)nnz, s);
+    const unsigned nb = (unsigned)std::max<int64_t>(1, ((int64_t)P.nrows + TPB - 1) / TPB);
+    int* cnt = dnew<int>((size_t)R.nrows + 2, s);  // counts, a zero, and the longest
+    HIP_CHECK(hipMemsetAsync(cnt, 0, ((size_t)R.nrows + 2) * sizeof(int), s));
+    k_tr_count<<<nb, TPB, 0, s>>>(P.nrows, P.ptr, P.col, cnt);
+    k_max_len<<<(unsigned)std::max<int64_t>(1, ((int64_t)R.nrows + TPB - 1) / TPB), TPB, 0, s>>>(R.nrows, cnt,
+                                                                                                  cnt + R.nrows + 1);
+    HIP_LAUNCH_CHECK();
+    exclusive_scan_i32(cnt, R.ptr, (int64_t)R.nrows + 1, s);
+    int longest = 0;
+    HIP_CHECK(hipMemcpyAsync(&longest, cnt + R.nrows + 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_CHECK(hipStreamSynchronize(s));
+    if (longest > TR_ROW_MAX) {
+        dfree(cnt, s);
+        transpose_sorted(P, R, s);
+        return;
+    }
+    int2* tmp = dnew<int2>((size_t)nnz, s);
+    k_tr_scatter<<<nb, TPB, 0, s>>>(P.nrows, P.ptr, P.col, R.ptr, cnt, tmp);
+    const double mean = R.nrows > 0 ? (double)nnz / R.nrows : 0.0;
+    const int g = mean <= 12.0 ? 8 : mean <= 24.0 ? 16 : 32;
+    AMG_WITH_SYM_G(g, (k_tr_order<G><<<(unsigned)std::max<int64_t>(1, ((int64_t)R.nrows * G + TPB - 1) / TPB), TPB, 0,
+                                       s>>>(R.nrows, R.ptr, tmp, P.val, R.col, R.val)));
+    HIP_LAUNCH_CHECK();
+    dfree(cnt, s);
+    dfree(tmp, s);
+}
+
+// ------------------------------------------------------------------ launch shapes
+
+// most[b] is raised to the largest number of entries in 2^b consecutive rows (aligned at
+// multiples of 2^b), for b = 0 .. 8.
+static_assert(RB_THREADS == 256, "one workgroup reads the rows of the largest block");
+__global__ __launch_bounds__(TPB) void k_row_blocks(int n, const int* __restrict__ ptr, int* __restrict__ most) {
+    __shared__ int sp[RB_THREADS + 1];
+    __shared__ int sm[TPB / 64];
+    const int r0 = blockIdx.x * RB_THREADS;
+    for (int i = threadIdx.x; i <= RB_THREADS; i += TPB) sp[i] = ptr[min(r0 + i, n)];
+    __syncthreads();
+    for (int b = 0; b < ROW_BLOCK_SIZES; ++b) {
+        const int nbk = RB_THREADS >> b;
+        int v = (int)threadIdx.x < nbk ? sp[(threadIdx.x + 1) << b] - sp[threadIdx.x << b] : 0;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+        if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int k = 1; k < TPB / 64; ++k) v = max(v, sm[k]);
+            raise_max(&most[b], v);
+        }
+        __syncthreads();
+    }
+}
+
+void launch_row_blocks(const Csr& A, int* most, hipStream_t s) {
+    k_row_blocks<<<(unsigned)std::max<int64_t>(1, ((int64_t)A.nrows + RB_THREADS - 1) / RB_THREADS), TPB, 0, s>>>(
+        A.nrows, A.ptr, most);
+    HIP_LAUNCH_CHECK();
+}
+
+// One base per row block: the smallest column of its rows (rows are sorted, so the
+// first entry of each); *wide = 1 when a block's columns span more than two bytes.  A
+// wavefront per block.
+__global__ __launch_bounds__(TPB) void k_c16_bases(int n, int rpb, const int* __restrict__ ptr,
+                                                   const int* __restrict__ col, int* __restrict__ cblk,
+                                                   int* __restrict__ wide) {
+    const int b = (blockIdx.x * TPB + threadIdx.x) >> 6, lane = threadIdx.x & 63;
+    const int r0 = b * rpb, r1 = min(r0 + rpb, n);
+    if (r0 >= n) return;
+    int lo = 0x7fffffff, hi = -1;
+    for (int r = r0 + lane; r < r1; r += 64) {
+        const int k0 = ptr[r], k1 = ptr[r + 1];
+        if (k0 < k1) {
+            lo = min(lo, col[k0]);
+            hi = max(hi, col[k1 - 1]);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, __shfl_xor(lo, o, 64));
+        hi = max(hi, __shfl_xor(hi, o, 64));
+    }
+    if (lane != 0) return;
+    if (hi < 0) lo = hi = 0;  // no entries
+    cblk[b] = lo;
+    if (hi - lo > 65535) wide[0] = 1;
+}
+
+// A workgroup per row block, its entries in order.
+__global__ __launch_bounds__(TPB) void k_c16_fill(int n, int rpb, const int* __restrict__ ptr,
+                                                  const int* __restrict__ col, const int* __restrict__ cblk,
+                                                  uint16_t* __restrict__ c16) {
+    const int b = xcd_block();
+    const int r0 = b * rpb, base = cblk[b], k1 = ptr[min(r0 + rpb, n)];
+    for (int k = ptr[r0] + threadIdx.x; k < k1; k += TPB) c16[k] = (uint16_t)(col[k] - base);
+}
+
+void launch_c16_bases(const Csr& A, int32_t* cblk, int* wide, hipStream_t s) {
+    const int64_t nb = (A.nrows + A.rpb - 1) / A.rpb;
+    k_c16_bases<<<(unsigned)((nb * 64 + TPB - 1) / TPB), TPB, 0, s>>>(A.nrows, A.rpb, A.ptr, A.col, cblk, wide);
+    HIP_LAUNCH_CHECK();
+}
+void launch_c16_fill(const Csr& A, const int32_t* cblk, uint16_t* c16, hipStream_t s) {
+    k_c16_fill<<<(unsigned)((A.nrows + A.rpb - 1) / A.rpb), TPB, 0, s>>>(A.nrows, A.rpb, A.ptr, A.col, cblk, c16);
+    HIP_LAUNCH_CHECK();
+}
+
+}  // namespace amgmi
