@@ -1663,15 +1663,22 @@ amg_status pcg(amg_ctx* c, const double* f, double* u, amg_solve_info* info) {
         return AMG_OK;
     }
     RzEpilogue ep{p.flexible_cg, 0};
+    // the scratch as the CG's own kernels get it: with the partials of r.z and p.q that they
+    // add themselves (small grids)
+    RedScratch rs = c->rs;
+    int pq_blocks = 0;  // workgroups of the kernel that uses beta
     auto precondition = [&](int first, int ready) {
         vcycle_apply(c, rc, c->z, &ep, ready);
-        launch_fin_rz(ep.nb, p.flexible_cg, first, c->rs, s);
+        const int users = pq_blocks > 0 ? pq_blocks : ep.nb;
+        rs.nrz = !p.flexible_cg && (int64_t)users * ep.nb <= FOLD_WORK ? ep.nb : 0;
+        if (rs.nrz == 0) launch_fin_rz(ep.nb, p.flexible_cg, first, c->rs, s);
     };
     // The x, r update can start the next preconditioner application: on a level-0
-    // diagonal storage (FP64) it also forms the first V-cycle sweep and its residual; in
-    // mixed precision it stores r in FP32 for the V-cycle.
+    // diagonal storage (FP64) it also forms the first V-cycle sweep and its residual, on a
+    // level 0 in CSR the first sweep; in mixed precision it stores r in FP32 for the V-cycle.
     const bool fuse_dia = !mixed(c) && c->dia.ndiag > 0 && p.npre == 1 && c->lv.size() > 1;
     const bool fuse_cast = mixed(c);
+    const bool fuse_sweep = !mixed(c) && p.npre > 0 && p.block_size == 1 && c->lv.size() > 1;  // level 0 in CSR
     precondition(1, 0);
     double* pold = c->pa;
     double* pnew = c->pb;
@@ -1686,26 +1693,30 @@ amg_status pcg(amg_ctx* c, const double* f, double* u, amg_solve_info* info) {
             // the diagonal storage holds the hierarchy's A_0, which is the Krylov operator
             // except after an operator-only update (full reuse)
             if (c->dia.ndiag > 0 && c->outer_val == L0.A.val)
-                nb_pq = launch_dia_cg_pq(n, c->dia, c->z, pold, pnew, c->q, it == 1, c->rs, s);
+                nb_pq = launch_dia_cg_pq(n, c->dia, c->z, pold, pnew, c->q, it == 1, rs, s);
             else if (p.block_size > 1)  // the Krylov operator has the pattern of A_0
-                nb_pq = launch_node_cg_pq(L0, p.block_size, c->outer_val, c->z, pold, pnew, c->q, it == 1, c->rs, s);
+                nb_pq = launch_node_cg_pq(L0, p.block_size, c->outer_val, c->z, pold, pnew, c->q, it == 1, rs, s);
             else
-                nb_pq = launch_cg_pq(L0.A, c->outer_val, c->z, pold, pnew, c->q, it == 1, c->rs, s);
+                nb_pq = launch_cg_pq(L0.A, c->outer_val, c->z, pold, pnew, c->q, it == 1, rs, s);
         }
-        launch_fin_pq(nb_pq, c->rs, s);
+        pq_blocks = nb_pq;
+        const int upd_blocks = fuse_dia ? nb_pq : red_grid_elems(n);  // of the kernel that uses alpha
+        rs.npq = (int64_t)upd_blocks * nb_pq <= FOLD_WORK ? nb_pq : 0;
+        if (rs.npq == 0) launch_fin_pq(nb_pq, c->rs, s);
         int ready = 0;
         {
             Trace tr(c, AMG_K_CG_UPDATE, 0);
             if (fuse_dia) {
                 nb = launch_dia_update_smooth0(n, c->dia, pnew, c->q, c->x, rc, ra, L0.m, (double*)L0.u,
-                                               (double*)L0.r, c->rs, s);
+                                               (double*)L0.r, rs, s);
                 std::swap(rc, ra);
                 ready = 2;
             } else if (fuse_cast) {
-                nb = launch_cg_update_cast(n, pnew, c->q, c->x, rc, (float*)L0.f, c->rs, s);
+                nb = launch_cg_update_cast(n, pnew, c->q, c->x, rc, (float*)L0.f, rs, s);
                 ready = 1;
             } else {
-                nb = launch_cg_update(n, pnew, c->q, c->x, rc, c->rs, s);
+                nb = launch_cg_update(n, pnew, c->q, c->x, rc, fuse_sweep ? L0.m : nullptr, (double*)L0.u, rs, s);
+                ready = fuse_sweep ? 1 : 0;
             }
         }
         // Read ||r||^2 back, but queue the next preconditioner application first so the

@@ -205,6 +205,9 @@ struct RedScratch {
     // device address of the host mirror (mapped, coherent pinned memory): the CG update
     // kernels write their ||r||^2 partials and the breakdown flag there directly
     double* host = nullptr;
+    // partials of r.z (p.q) that the next consumer of beta (alpha) adds itself; 0: k_fin_rz
+    // (k_fin_pq) has formed the scalars
+    int nrz = 0, npq = 0;
     __host__ __device__ double* region(int k) const {
         if (k <= P_PQ) return part + (size_t)k * cap;
         if (k == P_RR) return part + 3 * (size_t)cap + S_COUNT;
@@ -440,8 +443,8 @@ void launch_fin_rz(int nb, int flexible, int first, const RedScratch& rs, hipStr
 void launch_fin_pq(int nb, const RedScratch& rs, hipStream_t s);
 int launch_cg_pq(const Csr& A, const double* val, const double* z, const double* pold, double* pnew, double* q,
                  int first, const RedScratch& rs, hipStream_t s);
-int launch_cg_update(int n, const double* p, const double* q, double* x, double* r, const RedScratch& rs,
-                     hipStream_t s);
+int launch_cg_update(int n, const double* p, const double* q, double* x, double* r, const double* m, double* u,
+                     const RedScratch& rs, hipStream_t s);
 
 // ------------------------------------------------------------------ Galerkin / smoother
 template <typename T>
@@ -565,6 +568,68 @@ __device__ inline int xcd_block() {
     const int per = nb >> 3, rem = nb & 7;
     const int x = b & 7, i = b >> 3;
     return x * per + (x < rem ? x : rem) + i;
+}
+
+// ------------------------------------------------------------------ CG scalars
+//
+// beta and alpha come from partials that the kernel before wrote.  On a large grid a
+// one-workgroup kernel adds them (k_fin_rz, k_fin_pq); on a small one every workgroup of the
+// consuming kernel adds them itself, in the same order, which costs it about 1 us where the
+// extra launch of a dependent kernel costs 3 to 5 (32^3: 22 iterations of 10 launches, 1.14
+// -> 1.08 ms per step).  FOLD_WORK bounds the partials read that way (workgroups times
+// partials): 64^3 reads 512 x 512 and gains, 128^3 would read 4096 x 4096, 134 MB.
+constexpr int64_t FOLD_WORK = 1 << 21;
+
+// Sum of p[0..nb) by every workgroup of 256 threads in a fixed order.
+__device__ inline double fold_sum(const double* __restrict__ p, int nb) {
+    __shared__ double sm[4];
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    int i = threadIdx.x;
+    for (; i + 3 * 256 < nb; i += 4 * 256) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] += p[i + u * 256];
+    }
+    for (int u = 0; i < nb; i += 256, ++u) a[u & 3] += p[i];
+    double s = (a[0] + a[1]) + (a[2] + a[3]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = s;
+    __syncthreads();
+    return (sm[0] + sm[1]) + (sm[2] + sm[3]);
+}
+
+// beta of p = z + beta p_old (0 on the first iteration); workgroup 0 keeps rho = r.z for the
+// alpha that follows.  Nothing else in the consuming kernel reads the slots written here.
+__device__ inline double cg_beta(const RedScratch& rs, bool first) {
+    double* sc = rs.scal();
+    if (rs.nrz == 0) return first ? 0.0 : sc[S_BETA];
+    const double rz = fold_sum(rs.region(P_RZ), rs.nrz);
+    const double beta = first ? 0.0 : rz / sc[S_RHO_USED];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc[S_BETA] = beta;
+        sc[S_RHO] = rz;
+    }
+    return beta;
+}
+
+// alpha = rho / p.q, or bad (p.q <= 0 or a non-finite rho: breakdown) and alpha = 0.
+__device__ inline double cg_alpha(const RedScratch& rs, bool& bad) {
+    double* sc = rs.scal();
+    if (rs.npq == 0) {
+        bad = sc[S_FLAG] != 0.0;
+        return sc[S_ALPHA];
+    }
+    const double pq = fold_sum(rs.region(P_PQ), rs.npq);
+    const double rho = sc[S_RHO];
+    bad = !(pq > 0.0) || !isfinite(rho);
+    const double alpha = bad ? 0.0 : rho / pq;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc[S_RHO_USED] = rho;
+        sc[S_PQ] = pq;
+        sc[S_ALPHA] = alpha;
+        sc[S_FLAG] = bad ? 1.0 : 0.0;
+    }
+    return alpha;
 }
 
 }  // namespace amgmi

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(TPB_B) void k_node_sweep_rz(int nn, const int* __re
 __global__ __launch_bounds__(TPB_B) void k_node_pupdate(int n, const double* __restrict__ z,
                                                         const double* __restrict__ pold, double* __restrict__ pnew,
                                                         int first, RedScratch rs) {
-    const double beta = first ? 0.0 : rs.scal()[S_BETA];
+    const double beta = cg_beta(rs, first != 0);
     const int i = xcd_block() * TPB_B + threadIdx.x;
     if (i < n) pnew[i] = first ? z[i] : __builtin_fma(beta, pold[i], z[i]);
 }

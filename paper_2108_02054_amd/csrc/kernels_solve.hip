@@ -783,7 +783,7 @@ __global__ __launch_bounds__(TPB) void k_dia_cg_pq(int n, int nd, DiaOff o, cons
                                                    const double* __restrict__ z, const double* __restrict__ pold,
                                                    double* __restrict__ pnew, double* __restrict__ q,
                                                    RedScratch rs) {
-    const double beta = FIRST ? 0.0 : rs.scal()[S_BETA];
+    const double beta = cg_beta(rs, FIRST);
     auto pv = [&](int j) { return FIRST ? z[j] : __builtin_fma(beta, pold[j], z[j]); };
     const int lb = xcd_block();
     const int i = lb * TPB + threadIdx.x;
@@ -899,9 +899,8 @@ __global__ __launch_bounds__(TPB) void k_dia_update_smooth0(int n, int nd, DiaOf
                                                             const double* __restrict__ r, double* __restrict__ rn,
                                                             const double* __restrict__ m, double* __restrict__ u,
                                                             double* __restrict__ rv, RedScratch rs) {
-    const double* sc = rs.scal();
-    const bool bad = sc[S_FLAG] != 0.0;
-    const double alpha = sc[S_ALPHA];
+    bool bad;
+    const double alpha = cg_alpha(rs, bad);
     // on breakdown r_new = r - 0 q (r up to the sign of a zero entry; the solve stops there)
     const double step = bad ? 0.0 : alpha;
     auto rnew = [&](int j) { return __builtin_fma(-step, q[j], r[j]); };
@@ -1119,7 +1118,7 @@ template <bool SYM, bool FIRST>
 __global__ __launch_bounds__(TPB) void k_m7_cg_pq(int n, int a, int b, const double* __restrict__ v,
                                                   const double* __restrict__ z, const double* __restrict__ pold,
                                                   double* __restrict__ pnew, double* __restrict__ q, RedScratch rs) {
-    const double beta = FIRST ? 0.0 : rs.scal()[S_BETA];
+    const double beta = cg_beta(rs, FIRST);
     double loc[1] = {0.0};
     march7<SYM, double>(
         n, a, b, v, [&](int j) { return FIRST ? z[j] : __builtin_fma(beta, pold[j], z[j]); },
@@ -1139,9 +1138,8 @@ __global__ __launch_bounds__(TPB) void k_m7_update_smooth0(int n, int a, int b, 
                                                            const double* __restrict__ r, double* __restrict__ rn,
                                                            const double* __restrict__ m, double* __restrict__ u,
                                                            double* __restrict__ rv, RedScratch rs) {
-    const double* sc = rs.scal();
-    const bool bad = sc[S_FLAG] != 0.0;
-    const double alpha = sc[S_ALPHA];
+    bool bad;
+    const double alpha = cg_alpha(rs, bad);
     const double step = bad ? 0.0 : alpha;
     double loc[1] = {0.0};
     march7<SYM, double>(
@@ -1435,7 +1433,7 @@ template <int ND, bool SYM, int R, bool FIRST>
 __global__ __launch_bounds__(TPB) void k_w_cg_pq(int n, int nd, DiaOff o, WinPlan w, const double* __restrict__ v,
                                                  const double* __restrict__ z, const double* __restrict__ pold,
                                                  double* __restrict__ pnew, double* __restrict__ q, RedScratch rs) {
-    const double beta = FIRST ? 0.0 : rs.scal()[S_BETA];
+    const double beta = cg_beta(rs, FIRST);
     double loc[1] = {0.0};
     win_any<R, ND, SYM, double>(
         n, nd, o, w, v, [&](int j) { return FIRST ? z[j] : __builtin_fma(beta, pold[j], z[j]); },
@@ -1455,9 +1453,8 @@ __global__ __launch_bounds__(TPB) void k_w_update_smooth0(int n, int nd, DiaOff 
                                                           const double* __restrict__ r, double* __restrict__ rn,
                                                           const double* __restrict__ m, double* __restrict__ u,
                                                           double* __restrict__ rv, RedScratch rs) {
-    const double* sc = rs.scal();
-    const bool bad = sc[S_FLAG] != 0.0;
-    const double alpha = sc[S_ALPHA];
+    bool bad;
+    const double alpha = cg_alpha(rs, bad);
     const double step = bad ? 0.0 : alpha;
     double loc[1] = {0.0};
     win_any<R, ND, SYM, double>(
@@ -1947,7 +1944,8 @@ AMG_INST(float)
 //
 // Scalars flow through partial sums: the kernels that form r.z and p.q write one partial
 // per block (full grids, indexed by logical block), a one-block finalize kernel adds them
-// in order and forms beta or alpha on the device; ||r||^2 and ||f||^2 come from bounded
+// in order and forms beta or alpha on the device (on small grids the kernel that uses it
+// does: cg_beta, cg_alpha); ||r||^2 and ||f||^2 come from bounded
 // grids (at most RED_BLOCKS partials) that the host adds after its one copy per iteration.
 
 int red_grid_elems(int64_t n) {
@@ -1968,7 +1966,7 @@ int red_grid_rows(int nrows, int rpb, int g) {
 // r = f - A x, with ||r||^2 and ||f||^2 partials (bounded grid, host-summed).
 template <int G>
 __global__ __launch_bounds__(RB_THREADS) void k_cg_init(int n, int rpb, const int* __restrict__ ptr,
-                                                        const int* __restrict__ col, const double* __restrict__ val,
+                                                        ColSrc cs, const double* __restrict__ val,
                                                         const double* __restrict__ f, const double* __restrict__ x,
                                                         double* __restrict__ r, RedScratch rs) {
     __shared__ int sptr[RB_THREADS + 1];
@@ -1980,7 +1978,7 @@ __global__ __launch_bounds__(RB_THREADS) void k_cg_init(int n, int rpb, const in
         const int tpr = rb_tpr(rpb), t = threadIdx.x / tpr, lane = threadIdx.x & (tpr - 1);
         for (int rb = rb0; rb < rb1; ++rb) {
             const int row0 = rb * rpb, row1 = min(row0 + rpb, n);
-            rb_load(row0, row1, ptr, col, val, [&](int j) { return x[j]; }, sptr, sp);
+            rb_load(row0, row1, ptr, cs, rb, val, [&](int j) { return x[j]; }, sptr, sp);
             if (t < row1 - row0) {
                 const double v = rb_rowsum(sptr, sp, t, lane, tpr);
                 if (lane == 0) {
@@ -1999,7 +1997,7 @@ __global__ __launch_bounds__(RB_THREADS) void k_cg_init(int n, int rpb, const in
         for (int row = (blockIdx.x * TPB + (int)threadIdx.x) / G; row < n; row += groups) {
             const int b = ptr[row], e = ptr[row + 1];
             double s = 0.0;
-            for (int k = b + lane; k < e; k += G) s += val[k] * x[col[k]];
+            for (int k = b + lane; k < e; k += G) s += val[k] * x[cs.col[k]];
             s = group_sum<G>(s);
             if (lane == 0) {
                 const double fi = f[row], ri = fi - s;
@@ -2018,7 +2016,7 @@ __global__ __launch_bounds__(RB_THREADS) void k_cg_init(int n, int rpb, const in
 // flexible CG, r.z_old with z_old read from z before it is overwritten.  Full grid.
 template <int G>
 __global__ __launch_bounds__(RB_THREADS) void k_jacobi_rz(int n, int rpb, const int* __restrict__ ptr,
-                                                          const int* __restrict__ col, const double* __restrict__ val,
+                                                          ColSrc cs, const double* __restrict__ val,
                                                           const double* __restrict__ m, const double* __restrict__ r,
                                                           const double* __restrict__ u, double* __restrict__ z,
                                                           int flexible, RedScratch rs) {
@@ -2035,7 +2033,7 @@ __global__ __launch_bounds__(RB_THREADS) void k_jacobi_rz(int n, int rpb, const 
     const int lb = xcd_block();
     if (rpb > 0) {
         const int row0 = lb * rpb, row1 = min(row0 + rpb, n);
-        rb_load(row0, row1, ptr, col, val, [&](int j) { return u[j]; }, sptr, sp);
+        rb_load(row0, row1, ptr, cs, lb, val, [&](int j) { return u[j]; }, sptr, sp);
         const int tpr = rb_tpr(rpb), t = threadIdx.x / tpr, lane = threadIdx.x & (tpr - 1);
         if (t < row1 - row0) {
             const double v = rb_rowsum(sptr, sp, t, lane, tpr);
@@ -2047,7 +2045,7 @@ __global__ __launch_bounds__(RB_THREADS) void k_jacobi_rz(int n, int rpb, const 
         if (row < n) {
             const int b = ptr[row], e = ptr[row + 1];
             double s = 0.0;
-            for (int k = b + lane; k < e; k += G) s += val[k] * u[col[k]];
+            for (int k = b + lane; k < e; k += G) s += val[k] * u[cs.col[k]];
             s = group_sum<G>(s);
             if (lane == 0) emit(row, s);
         }
@@ -2112,19 +2110,19 @@ __global__ __launch_bounds__(FIN_THREADS) void k_fin_pq(int nb, RedScratch rs) {
 // so q is A applied to exactly the stored p_new.
 template <int G>
 __global__ __launch_bounds__(RB_THREADS) void k_cg_pq(int n, int rpb, const int* __restrict__ ptr,
-                                                      const int* __restrict__ col, const double* __restrict__ val,
+                                                      ColSrc cs, const double* __restrict__ val,
                                                       const double* __restrict__ z, const double* __restrict__ pold,
                                                       double* __restrict__ pnew, double* __restrict__ q, int first,
                                                       RedScratch rs) {
     __shared__ int sptr[RB_THREADS + 1];
     __shared__ double sp[RB_CAP];
-    const double beta = first ? 0.0 : rs.scal()[S_BETA];
+    const double beta = cg_beta(rs, first != 0);
     auto pv = [&](int j) { return first ? z[j] : __builtin_fma(beta, pold[j], z[j]); };
     double loc[1] = {0.0};
     const int lb = xcd_block();
     if (rpb > 0) {
         const int row0 = lb * rpb, row1 = min(row0 + rpb, n);
-        rb_load(row0, row1, ptr, col, val, pv, sptr, sp);
+        rb_load(row0, row1, ptr, cs, lb, val, pv, sptr, sp);
         const int tpr = rb_tpr(rpb), t = threadIdx.x / tpr, lane = threadIdx.x & (tpr - 1);
         if (t < row1 - row0) {
             const double qi = rb_rowsum(sptr, sp, t, lane, tpr);
@@ -2142,7 +2140,7 @@ __global__ __launch_bounds__(RB_THREADS) void k_cg_pq(int n, int rpb, const int*
         if (row < n) {
             const int b = ptr[row], e = ptr[row + 1];
             double s = 0.0;
-            for (int k = b + lane; k < e; k += G) s += val[k] * pv(col[k]);
+            for (int k = b + lane; k < e; k += G) s += val[k] * pv(cs.col[k]);
             s = group_sum<G>(s);
             if (lane == 0) {
                 const double pi = pv(row);
@@ -2157,11 +2155,15 @@ __global__ __launch_bounds__(RB_THREADS) void k_cg_pq(int n, int rpb, const int*
 }
 
 // x += alpha p; r -= alpha q; ||r||^2 partials (bounded grid).  On breakdown nothing moves.
+// With m also the cycle's first sweep u = m r, so that the residual after it gathers one
+// vector per entry instead of m and r (masked 101x83x90: residual 19.1 -> 12.9 us, update 7.9
+// -> 9.3 us).
 __global__ __launch_bounds__(TPB) void k_cg_update(int n, const double* __restrict__ p, const double* __restrict__ q,
-                                                   double* __restrict__ x, double* __restrict__ r, RedScratch rs) {
-    const double* sc = rs.scal();
-    const bool bad = sc[S_FLAG] != 0.0;
-    const double alpha = sc[S_ALPHA];
+                                                   double* __restrict__ x, double* __restrict__ r,
+                                                   const double* __restrict__ m, double* __restrict__ u,
+                                                   RedScratch rs) {
+    bool bad;
+    const double alpha = cg_alpha(rs, bad);
     double loc[1] = {0.0};
     for (int i = blockIdx.x * TPB + threadIdx.x; i < n; i += gridDim.x * TPB) {
         double ri = r[i];
@@ -2170,6 +2172,7 @@ __global__ __launch_bounds__(TPB) void k_cg_update(int n, const double* __restri
             ri = __builtin_fma(-alpha, q[i], ri);
             r[i] = ri;
         }
+        if (m != nullptr) u[i] = m[i] * ri;
         loc[0] += ri * ri;
     }
     double* const dst[1] = {rr_dest(rs, bad)};
@@ -2181,9 +2184,8 @@ __global__ __launch_bounds__(TPB) void k_cg_update_cast(int n, const double* __r
                                                         const double* __restrict__ q, double* __restrict__ x,
                                                         double* __restrict__ r, float* __restrict__ r32,
                                                         RedScratch rs) {
-    const double* sc = rs.scal();
-    const bool bad = sc[S_FLAG] != 0.0;
-    const double alpha = sc[S_ALPHA];
+    bool bad;
+    const double alpha = cg_alpha(rs, bad);
     double loc[1] = {0.0};
     for (int i = blockIdx.x * TPB + threadIdx.x; i < n; i += gridDim.x * TPB) {
         double ri = r[i];
@@ -2202,7 +2204,7 @@ __global__ __launch_bounds__(TPB) void k_cg_update_cast(int n, const double* __r
 int launch_cg_init(const Csr& A, const double* val, const double* f, const double* x, double* r, const RedScratch& rs,
                    hipStream_t s) {
     const int nb = red_grid_rows(A.nrows, A.rpb, A.g);
-    AMG_WITH_G(A.g, timed_launch(k_cg_init<G>, nb, RB_THREADS, 0, s, A.nrows, A.rpb, A.ptr, A.col, val, f, x, r, rs));
+    AMG_WITH_G(A.g, timed_launch(k_cg_init<G>, nb, RB_THREADS, 0, s, A.nrows, A.rpb, A.ptr, colsrc(A), val, f, x, r, rs));
     HIP_LAUNCH_CHECK();
     return nb;
 }
@@ -2210,7 +2212,7 @@ int launch_jacobi_rz(const Csr& A, const double* m, const double* r, const doubl
                      const RedScratch& rs, hipStream_t s) {
     const int nb = full_grid_rows(A.nrows, A.rpb, A.g);
     if (nb > rs.cap) throw Fail{AMG_ERR_ARG, "reduction scratch too small"};
-    AMG_WITH_G(A.g, timed_launch(k_jacobi_rz<G>, nb, RB_THREADS, 0, s, A.nrows, A.rpb, A.ptr, A.col, A.val, m, r, u, z, flexible, rs));
+    AMG_WITH_G(A.g, timed_launch(k_jacobi_rz<G>, nb, RB_THREADS, 0, s, A.nrows, A.rpb, A.ptr, colsrc(A), A.val, m, r, u, z, flexible, rs));
     HIP_LAUNCH_CHECK();
     return nb;
 }
@@ -2239,15 +2241,15 @@ int launch_cg_pq(const Csr& A, const double* val, const double* z, const double*
                  int first, const RedScratch& rs, hipStream_t s) {
     const int nb = full_grid_rows(A.nrows, A.rpb, A.g);
     if (nb > rs.cap) throw Fail{AMG_ERR_ARG, "reduction scratch too small"};
-    AMG_WITH_G(A.g, timed_launch(k_cg_pq<G>, nb, RB_THREADS, 0, s, A.nrows, A.rpb, (const int*)A.ptr, (const int*)A.col,
+    AMG_WITH_G(A.g, timed_launch(k_cg_pq<G>, nb, RB_THREADS, 0, s, A.nrows, A.rpb, (const int*)A.ptr, colsrc(A),
                                  val, z, pold, pnew, q, first, rs));
     HIP_LAUNCH_CHECK();
     return nb;
 }
-int launch_cg_update(int n, const double* p, const double* q, double* x, double* r, const RedScratch& rs,
-                     hipStream_t s) {
+int launch_cg_update(int n, const double* p, const double* q, double* x, double* r, const double* m, double* u,
+                     const RedScratch& rs, hipStream_t s) {
     const int nb = red_grid_elems(n);
-    timed_launch(k_cg_update, nb, TPB, 0, s, n, p, q, x, r, rs);
+    timed_launch(k_cg_update, nb, TPB, 0, s, n, p, q, x, r, m, u, rs);
     HIP_LAUNCH_CHECK();
     return nb;
 }
