@@ -450,6 +450,7 @@ bool lanes_only() {
 struct GalForce {
     int lanes = 0;  // 1: lane-group kernels
     int wide = 0;   // 1: two-byte positions
+    int pos = 0;    // 1: position-map form also for small products
     int g = 0;
     int t = 0;      // B terms per lane and entry (1 or 2)
 };
@@ -459,6 +460,7 @@ GalForce galerkin_force() {
     if (e == nullptr) return f;
     if (std::strncmp(e, "lanes", 5) == 0) f.lanes = 1;
     if (std::strncmp(e, "pos16", 5) == 0) f.wide = 1;
+    if (std::strncmp(e, "pos", 3) == 0) f.pos = 1;
     if (const char* c = std::strchr(e, ':')) {
         f.g = std::atoi(c + 1);
         if (const char* c2 = std::strchr(c + 1, ':')) f.t = std::atoi(c2 + 1);
@@ -523,7 +525,7 @@ std::vector<T> to_host(const T* d, size_t n, hipStream_t s) {
 }
 
 void release_posmap(amg_ctx* c, GalShape& gs) {
-    for (void* p : {gs.pos, (void*)gs.off, (void*)gs.bst, (void*)gs.tof, (void*)gs.dpos}) release(c, p);
+    for (void* p : {gs.pos, (void*)gs.off, (void*)gs.bst, (void*)gs.tof, (void*)gs.dpos, (void*)gs.inv}) release(c, p);
     gs = GalShape{};
 }
 
@@ -615,7 +617,8 @@ void configure_node_gal(amg_ctx* c) {
 // of its numeric phase; with diag, also the diagonal index of every row of L (for the
 // smoother).  Rows with more terms than the position-map form takes, or C rows too long for
 // it, leave the product to the lane-group kernels.
-GalShape plan_product(amg_ctx* c, const Csr& L, const Csr& B, Csr& C, bool diag, hipStream_t s) {
+// own: the product may take the owner form (it does not ingest new values of L).
+GalShape plan_product(amg_ctx* c, const Csr& L, const Csr& B, Csr& C, bool diag, bool own, hipStream_t s) {
     const GalForce f = galerkin_force();
     int64_t* off = halloc<int64_t>(c, (size_t)L.nrows + 1);
     SymSizes z;
@@ -627,8 +630,14 @@ GalShape plan_product(amg_ctx* c, const Csr& L, const Csr& B, Csr& C, bool diag,
     }
     track(c, C);
     GalShape gs;
-    if (!lanes_only() && !f.lanes && L.nrows > 0 && galerkin_terms_fit(z.max_terms))
+    const bool plan = !lanes_only() && !f.lanes && L.nrows > 0;
+    if (plan && own && !f.pos && pick_owner_form(L.nrows, L.nnz, z, gs)) {
+        gs.terms = z.terms;
+        gs.inv = halloc<uint8_t>(c, (size_t)L.nnz * gs.inv_w);
+        gs.bst = halloc<int32_t>(c, (size_t)std::max<int64_t>(L.nnz, 1));
+    } else if (plan && galerkin_terms_fit(z.max_terms)) {
         gs = pick_galerkin_shape(L.nrows, L.nnz, z.terms, z.maxlen, f.g, f.t);
+    }
     if (gs.g > 0) {
         if (f.wide) gs.wide = 1;
         gs.off = off;
@@ -637,10 +646,10 @@ GalShape plan_product(amg_ctx* c, const Csr& L, const Csr& B, Csr& C, bool diag,
         gs.pos = gs.wide ? (void*)halloc<uint16_t>(c, n) : (void*)halloc<uint8_t>(c, n);
         gs.bst = halloc<int32_t>(c, (size_t)std::max<int64_t>(L.nnz, 1));
         gs.tof = halloc<uint16_t>(c, (size_t)std::max<int64_t>(L.nnz, 1));
-        if (diag) {
-            gs.dpos = halloc<int32_t>(c, (size_t)L.nrows + 1);
-            launch_diag_index(L, gs.dpos, s);
-        }
+    }
+    if (gs.planned() && diag) {
+        gs.dpos = halloc<int32_t>(c, (size_t)L.nrows + 1);
+        launch_diag_index(L, gs.dpos, s);
     }
     symbolic_fill(L, B, C, gs, off, z, s);
     if (gs.g == 0) release(c, off);
@@ -680,7 +689,7 @@ void find_stencil(amg_ctx* c) {
 constexpr int32_t POST_ROWS_MAX = 1 << 18;
 bool correction_pays(amg_ctx* c, size_t l) {
     const Level& L = c->lv[l];
-    if (c->prm.block_size > 1 || c->prm.npost < 1 || L.galAP.g == 0) return false;
+    if (c->prm.block_size > 1 || c->prm.npost < 1 || !L.galAP.planned()) return false;
     if (const char* e = std::getenv("AMGMI_POST")) return std::strcmp(e, "fused") == 0;
     if (l > 0 || c->dia_offs.empty()) return true;
     if (c->prm.aggregation == 1 || L.A.nrows <= POST_ROWS_MAX) return true;
@@ -1126,8 +1135,8 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
         ph[1] += ms_since(t0);
         t0 = Clock::now();
         Csr AP, Ac;
-        const GalShape galAP = plan_product(c, A, P, AP, true, s);
-        const GalShape galRAP = plan_product(c, R, AP, Ac, false, s);
+        const GalShape galAP = plan_product(c, A, P, AP, true, l > 0, s);
+        const GalShape galRAP = plan_product(c, R, AP, Ac, false, true, s);
         AP.val = halloc<double>(c, (size_t)AP.nnz);
         Ac.val = halloc<double>(c, (size_t)Ac.nnz);
         Ac.ncols = Ac.nrows;
@@ -1245,8 +1254,8 @@ void repattern(amg_ctx* c) {
         release_csr(c, L.AP);
         Csr AP, Ac;
         release_posmaps(c, L);
-        const GalShape galAP = plan_product(c, L.A, L.P, AP, true, s);
-        const GalShape galRAP = plan_product(c, L.R, AP, Ac, false, s);
+        const GalShape galAP = plan_product(c, L.A, L.P, AP, true, l > 0, s);
+        const GalShape galRAP = plan_product(c, L.R, AP, Ac, false, true, s);
         AP.val = halloc<double>(c, (size_t)AP.nnz);
         if (mixed(c)) AP.val32 = halloc<float>(c, (size_t)AP.nnz);
         Ac.ncols = Ac.nrows;

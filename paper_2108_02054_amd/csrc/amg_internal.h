@@ -122,6 +122,12 @@ struct GalShape {
     uint16_t* tof = nullptr;    // per L entry: its first term's offset within the row
     int32_t* dpos = nullptr;    // per L row: index of its diagonal entry (C = A P only)
     int64_t terms = 0;
+    // owner form of a small product (own > 0: lanes across the positions of a C row, own_rows
+    // threads per row): per L entry and position p of its C row the entry of its B row there,
+    // inv[k * inv_w + p] (1-based, 0: none), in place of pos, off and tof
+    int own = 0, own_rows = 0, inv_w = 0;
+    uint8_t* inv = nullptr;
+    bool planned() const { return g > 0 || own > 0; }
 };
 
 // Galerkin product of a block system whose transfer operator is P_l = P_node (x) I_B with
@@ -454,6 +460,8 @@ bool launch_galerkin_ap(const Csr& A, const Csr& P, const Csr& AP, int g, GalSha
                         const double* ain, hipStream_t s, const Dia* dia = nullptr, T* q = nullptr);
 template <typename T>
 void launch_galerkin_rap(const Csr& R, const Csr& AP, const Csr& Ac, int g, GalShape gs, hipStream_t s);
+// Whether C = L B takes the owner form, with its lanes, threads per row and row width set.
+bool pick_owner_form(int64_t nrows, int64_t nnzL, const struct SymSizes& z, GalShape& gs);
 GalShape pick_galerkin_shape(int32_t nrows, int64_t nnzL, int64_t terms, int maxlen_c, int gforce, int tforce);
 bool galerkin_terms_fit(int64_t max_row);
 void launch_diag_index(const Csr& A, int32_t* dpos, hipStream_t s);  // index of each diagonal entry (-1: none)
@@ -490,6 +498,7 @@ void transpose_sorted(const Csr& P, Csr& R, hipStream_t s);
 struct SymSizes {
     int64_t terms = 0, max_terms = 0;  // all, and the most in a row
     int maxlen = 0;                    // longest row of C
+    int max_b = 0;                     // longest B row met
     double mean_b = 0.0, mean_terms = 0.0;
 };
 bool symbolic_count(const Csr& A, const Csr& B, Csr& C, int64_t* off, SymSizes& z, hipStream_t s);

@@ -308,6 +308,204 @@ __global__ __launch_bounds__(TPB) void k_galerkin_pos(
     for (int q = g; q < len; q += G) Qval[sb + q] = sacc[q];
 }
 
+// ------------------------------------------------------------------ owner form
+//
+// Small products (the coarse levels, and every level of a small problem) are bound by the
+// chain of dependent steps along their longest rows, not by bytes: the position-map form
+// stages a chunk of L entries, waits for a batch of B terms, and adds the terms through LDS
+// one L entry after another.  Here lane g of a row's G lanes owns the positions g, g + G, ...
+// of the C row: for an L entry it reads which entry of the B row falls there (one byte,
+// cached at setup) and that entry's value.  Each sum takes its terms in the order of the L
+// row, as the row-by-row product does.  Loads are unconditional, at clamped places: with a
+// branch per load these kernels were bound by their instructions.
+//   k_galerkin_own1: G lanes per row, the sums in registers.
+//   k_galerkin_own: a workgroup per row.  Its S groups of G lanes form the products of U
+//     entries each into LDS (0 for an absent term) and the first group adds each position's
+//     in order: a sum that starts from +0 is never -0, so adding the +0 of an absent term
+//     changes nothing.
+// Measured (position-map form / k_galerkin_own / k_galerkin_own1): R (A P) of 102 rows 35.4 /
+// 14.5 / 22.4 us, of 559 rows 48.6 / 24.5 / 32.9, of 1527 rows 40.5 / 33.8 / 34.4, of 4554
+// rows 47.6 / 84.9 / 71.5; A P of 1080 rows 62.7 / 27.0 / 32.2, of 3109 rows 31.9 / 20.2 /
+// 14.0, of 10086 rows 42.9 / 99 / 72.8 (times with about 5 us of event overhead).
+
+// G lanes alone per row, their sums in registers: for rows enough to fill the device without
+// splitting them.
+template <typename T, int G, int K>
+__global__ __launch_bounds__(TPB) void k_galerkin_own1(int nrows, int W, int last_b, const int* __restrict__ Lptr,
+                                                       const T* __restrict__ Lval, const int* __restrict__ Lbst,
+                                                       const T* __restrict__ Bval, const int* __restrict__ Cptr,
+                                                       T* __restrict__ Cval, const uint8_t* __restrict__ inv,
+                                                       const int* __restrict__ dpos, int kind, T omega,
+                                                       T* __restrict__ m, T* __restrict__ Qval) {
+    constexpr int U = 8;
+    const int g = threadIdx.x & (G - 1);
+    const int row = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    if (row >= nrows) return;
+    const int lb = Lptr[row], nl = Lptr[row + 1] - lb;
+    const int sb = Cptr[row], len = Cptr[row + 1] - sb;
+    const int dp = m != nullptr ? dpos[row] - lb : -1;
+    const T* Lv = Lval + lb;
+    const int* Lb = Lbst + lb;
+    const uint8_t* iv = inv + (size_t)lb * W;
+    T acc[K], d = 0, ss = 0;
+    int pos[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        acc[k] = 0;
+        pos[k] = min(g + k * G, W - 1);
+    }
+    T lv[U];
+    int bs[U], jj[U][K];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = min(c0 + u, nl - 1);
+            lv[u] = Lv[t];
+            bs[u] = Lb[t];
+#pragma unroll
+            for (int k = 0; k < K; ++k) jj[u][k] = iv[t * W + pos[k]];
+        }
+    };
+    if (nl > 0) fetch(0);
+    for (int c0 = 0; c0 < nl; c0 += U) {
+        T bv[U][K], lc[U];
+        bool on[U][K];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            lc[u] = lv[u];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                on[u][k] = jj[u][k] > 0 && c0 + u < nl;
+                bv[u][k] = Bval[min(bs[u] + max(jj[u][k] - 1, 0), last_b)];
+            }
+        }
+        if (c0 + U < nl) fetch(c0 + U);  // in flight while this batch is added
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) acc[k] = on[u][k] ? acc[k] + lc[u] * bv[u][k] : acc[k];
+            if (m != nullptr && c0 + u < nl) {  // the row's squares in column order
+                if (c0 + u == dp) d = lc[u];
+                ss = ss + lc[u] * lc[u];
+            }
+        }
+    }
+    const T mi = (kind == 1) ? d / ss : omega / d;
+    if (m != nullptr && g == 0) m[row] = mi;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int p = g + k * G;
+        if (p >= len) continue;
+        Cval[sb + p] = acc[k];
+        if (m == nullptr || Qval == nullptr || dp < 0) continue;
+        const int j = iv[dp * W + p];  // Q = P - M (A P): row i of P is the diagonal entry's B row
+        const T q = -mi * acc[k];
+        Qval[sb + p] = j > 0 ? q + Bval[Lb[dp] + j - 1] : q;
+    }
+}
+
+template <typename T, int G, int K, int U>
+__global__ __launch_bounds__(TPB) void k_galerkin_own(int nrows, int W, int last_b, const int* __restrict__ Lptr,
+                                                      const T* __restrict__ Lval, const int* __restrict__ Lbst,
+                                                      const T* __restrict__ Bval, const int* __restrict__ Cptr,
+                                                      T* __restrict__ Cval, const uint8_t* __restrict__ inv,
+                                                      const int* __restrict__ dpos, int kind, T omega,
+                                                      T* __restrict__ m, T* __restrict__ Qval) {
+    constexpr int S = TPB / G, E = S * U;  // groups, entries per chunk
+    extern __shared__ __align__(16) unsigned char own_smem[];
+    T* prod = reinterpret_cast<T*>(own_smem);  // two chunks of products, then of L values
+    T* elv = prod + (size_t)2 * E * W;
+    const int g = threadIdx.x & (G - 1), sub = threadIdx.x / G;
+    const int row = blockIdx.x;
+    const int lb = Lptr[row], nl = Lptr[row + 1] - lb;
+    const int sb = Cptr[row], len = Cptr[row + 1] - sb;
+    const int dp = m != nullptr ? dpos[row] - lb : -1;
+    const T* Lv = Lval + lb;
+    const int* Lb = Lbst + lb;
+    const uint8_t* iv = inv + (size_t)lb * W;
+    T acc[K], d = 0, ss = 0;
+    int pos[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        acc[k] = 0;
+        pos[k] = min(g + k * G, W - 1);
+    }
+    T lv[U];
+    int bs[U], jj[U][K];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = min(c0 + sub * U + u, nl - 1);
+            lv[u] = Lv[t];
+            bs[u] = Lb[t];
+#pragma unroll
+            for (int k = 0; k < K; ++k) jj[u][k] = iv[t * W + pos[k]];
+        }
+    };
+    if (nl > 0) fetch(0);
+    int buf = 0;
+    for (int c0 = 0; c0 < nl; c0 += E, buf ^= 1) {
+        T bv[U][K], lc[U];
+        bool on[U][K];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            lc[u] = lv[u];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                on[u][k] = jj[u][k] > 0;
+                bv[u][k] = Bval[min(bs[u] + max(jj[u][k] - 1, 0), last_b)];
+            }
+        }
+        if (c0 + E < nl) fetch(c0 + E);  // in flight while this chunk is added
+        T* pb = prod + (size_t)buf * E * W;
+        T* eb = elv + buf * E;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = sub * U + u;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const T x = on[u][k] ? lc[u] * bv[u][k] : T(0);
+                if (g + k * G < W) pb[e * W + g + k * G] = x;
+            }
+            if (m != nullptr && g == 0) eb[e] = lc[u];
+        }
+        __syncthreads();  // (the other buffer is written next: its readers passed this point)
+        if (sub == 0) {
+            const int ne = min(E, nl - c0);
+            for (int e0 = 0; e0 < ne; e0 += U) {
+                T x[U][K];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int k = 0; k < K; ++k) x[u][k] = pb[(e0 + u) * W + pos[k]];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int k = 0; k < K; ++k) acc[k] = e0 + u < ne ? acc[k] + x[u][k] : acc[k];
+            }
+            if (m != nullptr)
+                for (int e = 0; e < ne; ++e) {  // the row's squares in column order
+                    const T v = eb[e];
+                    if (c0 + e == dp) d = v;
+                    ss = ss + v * v;
+                }
+        }
+    }
+    if (sub != 0) return;
+    const T mi = (kind == 1) ? d / ss : omega / d;
+    if (m != nullptr && g == 0) m[row] = mi;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int p = g + k * G;
+        if (p >= len) continue;
+        Cval[sb + p] = acc[k];
+        if (m == nullptr || Qval == nullptr || dp < 0) continue;
+        const int j = iv[dp * W + p];  // Q = P - M (A P): row i of P is the diagonal entry's B row
+        const T q = -mi * acc[k];
+        Qval[sb + p] = j > 0 ? q + Bval[Lb[dp] + j - 1] : q;
+    }
+}
+
 // Index of each row's diagonal entry (-1 if absent).
 __global__ __launch_bounds__(TPB) void k_diag_index(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                                                     int* __restrict__ dpos) {
@@ -357,6 +555,9 @@ void launch_diag_index(const Csr& A, int32_t* dpos, hipStream_t s) {
 // gforce and tforce force G and TPL where the LDS allows.  The position map itself is
 // built by the caller.
 constexpr int32_t TPL2_MIN_ROWS = 1 << 16;
+constexpr int64_t OWN_BYTES = 64 << 20;
+constexpr int OWN_LEN_MAX = 248;  // two chunks of 16 products per position within 64 KiB
+constexpr int64_t OWN_ROWS_WG = 1024, OWN_ROWS = 4096;
 GalShape pick_galerkin_shape(int32_t nrows, int64_t nnzL, int64_t terms, int maxlen, int gforce, int tforce) {
     if (maxlen > WF_CAP_MAX) return {};
     const double mean_b = nnzL > 0 ? (double)terms / (double)nnzL : 1.0;
@@ -380,6 +581,18 @@ GalShape pick_galerkin_shape(int32_t nrows, int64_t nnzL, int64_t terms, int max
     gs.wide = maxlen > 255 ? 1 : 0;
     gs.tpl = tpl;
     return gs;
+}
+
+bool pick_owner_form(int64_t nrows, int64_t nnzL, const SymSizes& z, GalShape& gs) {
+    if (z.max_b > 254 || z.maxlen > OWN_LEN_MAX || z.maxlen == 0 || nrows == 0) return false;
+    const int w = (z.maxlen + 7) / 8 * 8;
+    int G = 8;
+    while (G < 64 && G < z.maxlen) G <<= 1;
+    if (nnzL * w > OWN_BYTES || nrows > OWN_ROWS) return false;
+    gs.own = G;
+    gs.own_rows = nrows <= OWN_ROWS_WG ? TPB : G;
+    gs.inv_w = w;
+    return true;
 }
 
 template <typename T>
@@ -421,6 +634,37 @@ static void launch_pos(const Csr& L, const Csr& B, const Csr& C, const GalShape&
 }
 
 template <typename T>
+static void launch_own(const Csr& L, const Csr& B, const Csr& C, const GalShape& gs, int kind, double omega, T* m,
+                       T* q, hipStream_t s) {
+    const int* dp = m != nullptr ? gs.dpos : nullptr;
+    const int k = (gs.inv_w + gs.own - 1) / gs.own;
+    auto go = [&](auto kern, unsigned nbk, size_t smem) {
+        kern<<<nbk, TPB, smem, s>>>(L.nrows, gs.inv_w, (int)(B.nnz - 1), L.ptr, L.v<T>(), gs.bst, B.v<T>(), C.ptr,
+                                    C.v<T>(), gs.inv, dp, kind, (T)omega, m, q);
+    };
+    if (gs.own_rows == TPB) {
+        const int u = k > 2 ? 4 : 8;
+        const size_t sm = (size_t)2 * (TPB / gs.own) * u * (gs.inv_w + 1) * sizeof(T);
+        const unsigned nbk = (unsigned)L.nrows;
+        if (gs.own == 8) go(k_galerkin_own<T, 8, 1, 8>, nbk, sm);
+        else if (gs.own == 16) go(k_galerkin_own<T, 16, 1, 8>, nbk, sm);
+        else if (gs.own == 32) go(k_galerkin_own<T, 32, 1, 8>, nbk, sm);
+        else if (k == 1) go(k_galerkin_own<T, 64, 1, 8>, nbk, sm);
+        else if (k == 2) go(k_galerkin_own<T, 64, 2, 8>, nbk, sm);
+        else go(k_galerkin_own<T, 64, 4, 4>, nbk, sm);
+    } else {
+        const unsigned nbk = row_blocks(L.nrows, gs.own);
+        if (gs.own == 8) go(k_galerkin_own1<T, 8, 1>, nbk, 0);
+        else if (gs.own == 16) go(k_galerkin_own1<T, 16, 1>, nbk, 0);
+        else if (gs.own == 32) go(k_galerkin_own1<T, 32, 1>, nbk, 0);
+        else if (k == 1) go(k_galerkin_own1<T, 64, 1>, nbk, 0);
+        else if (k == 2) go(k_galerkin_own1<T, 64, 2>, nbk, 0);
+        else go(k_galerkin_own1<T, 64, 4>, nbk, 0);
+    }
+    HIP_LAUNCH_CHECK();
+}
+
+template <typename T>
 void launch_smoother_diag(const Csr& A, int kind, double omega, T* m, hipStream_t s) {
     k_smoother_diag<T><<<row_blocks(A.nrows, 1), TPB, 0, s>>>(A.nrows, A.ptr, A.col, A.v<T>(), kind, (T)omega, m);
     HIP_LAUNCH_CHECK();
@@ -435,6 +679,11 @@ void launch_smoother_diag(const Csr& A, int kind, double omega, T* m, hipStream_
 template <typename T>
 bool launch_galerkin_ap(const Csr& A, const Csr& P, const Csr& AP, int g, GalShape gs, int kind, double omega, T* m,
                         const double* ain, hipStream_t s, const Dia* dia, T* q) {
+    if (gs.own > 0) {
+        if (ain != nullptr) throw Fail{AMG_ERR_ARG, "owner-form product cannot take new values of A"};
+        launch_own<T>(A, P, AP, gs, kind, omega, m, q, s);
+        return true;
+    }
     if (gs.g > 0) {
         const bool to_dia = dia != nullptr && ain != nullptr;
         double* out64 = (!to_dia && ain != nullptr && ain != A.val) ? A.val : nullptr;
@@ -452,6 +701,10 @@ bool launch_galerkin_ap(const Csr& A, const Csr& P, const Csr& AP, int g, GalSha
 
 template <typename T>
 void launch_galerkin_rap(const Csr& R, const Csr& AP, const Csr& Ac, int g, GalShape gs, hipStream_t s) {
+    if (gs.own > 0) {
+        launch_own<T>(R, AP, Ac, gs, 0, 0.0, (T*)nullptr, (T*)nullptr, s);
+        return;
+    }
     if (gs.g > 0) {
         launch_pos<T>(R, AP, Ac, gs, 0, 0.0, (T*)nullptr, (T*)nullptr, nullptr, nullptr, (T*)nullptr, s);
         return;

@@ -66,8 +66,9 @@ __device__ __forceinline__ int sym_insert(int* tab, int H, int shift, int c) {
 
 // Walks the terms of the A row [b, e): the group's lanes take 1 << lg lanes per B row, so
 // several B rows at a time, the first term of four such steps in flight together.
-// f(A entry - b, term within the B row, column); entry(k, first term's offset, B row start)
-// once per A entry, before its terms.  Returns the row's terms.
+// f(A entry, term within its B row, term within the row, column); entry(A entry, first
+// term's offset, B row start, B row length) once per A entry, before its terms.  Returns the
+// row's terms.
 template <int G, class E, class F>
 __device__ __forceinline__ int sym_walk(int lane, int lg, int b, int e, const int* __restrict__ Acol,
                                         const int* __restrict__ Bptr, const int* __restrict__ Bcol, E entry, F f) {
@@ -89,7 +90,7 @@ __device__ __forceinline__ int sym_walk(int lane, int lg, int b, int e, const in
         }
         const int to = carry + incl - len;
         carry += __shfl(incl, G - 1, G);
-        if (k < e) entry(k, to, b0);
+        if (k < e) entry(k, to, b0, len);
         const int nt = min(G, e - c0);
         constexpr int U = 4;
         for (int e0 = 0; e0 < nt; e0 += U * per) {
@@ -105,8 +106,9 @@ __device__ __forceinline__ int sym_walk(int lane, int lg, int b, int e, const in
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (q0 < ll[u]) f(tt[u] + q0, cc[u]);
-                for (int q = q0 + step; q < ll[u]; q += step) f(tt[u] + q, Bcol[bb[u] + q]);
+                const int ke = c0 + e0 + u * per + sub;
+                if (q0 < ll[u]) f(ke, q0, tt[u] + q0, cc[u]);
+                for (int q = q0 + step; q < ll[u]; q += step) f(ke, q, tt[u] + q, Bcol[bb[u] + q]);
             }
         }
     }
@@ -114,7 +116,7 @@ __device__ __forceinline__ int sym_walk(int lane, int lg, int b, int e, const in
 }
 
 // cnt[i], terms[i] (both with a zero at n, so that exclusive scans end in the totals);
-// stat: {overflow, most terms in a row, longest row}.
+// stat: {overflow, most terms in a row, longest row, longest B row met}.
 template <int G>
 __global__ __launch_bounds__(TPB) void k_sym_count(int n, int lg, int H, int shift, const int* __restrict__ Aptr,
                                                    const int* __restrict__ Acol, const int* __restrict__ Bptr,
@@ -134,21 +136,25 @@ __global__ __launch_bounds__(TPB) void k_sym_count(int n, int lg, int H, int shi
     }
     for (int s = lane; s < H; s += G) tab[s] = -1;
     wave_fence();
-    int u = 0, full = 0;
-    const int nterm = sym_walk<G>(lane, lg, Aptr[row], Aptr[row + 1], Acol, Bptr, Bcol, [](int, int, int) {},
-                                  [&](int, int c) {
+    int u = 0, full = 0, mb = 0;
+    const int nterm = sym_walk<G>(lane, lg, Aptr[row], Aptr[row + 1], Acol, Bptr, Bcol,
+                                  [&](int, int, int, int len) { mb = max(mb, len); },
+                                  [&](int, int, int, int c) {
                                       const int r = sym_insert(tab, H, shift, c);
                                       u += r > 0;
                                       full |= r < 0;
                                   });
     u = group_sum_i<G>(u);
     full = group_sum_i<G>(full);
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) mb = max(mb, __shfl_xor(mb, o, G));
     if (lane == 0) {
         cnt[row] = u;
         terms[row] = nterm;
         raise_max(&stat[0], full ? 1 : 0);
         raise_max(&stat[1], nterm);
         raise_max(&stat[2], u);
+        raise_max(&stat[3], mb);
     }
 }
 
@@ -156,18 +162,20 @@ __global__ void k_sym_totals(int n, const int* __restrict__ ptr, const int64_t* 
                              const int* __restrict__ stat, int64_t* __restrict__ out) {
     out[0] = ptr[n];
     out[1] = off[n];
-    for (int k = 0; k < 3; ++k) out[2 + k] = stat[k];
+    for (int k = 0; k < 4; ++k) out[2 + k] = stat[k];
 }
 
-// Columns of row i of C in order, and with pos the plan: per A entry its B row start and
-// first term's offset, per term its column's position in the C row.
+// Columns of row i of C in order, and the plan: per A entry its B row start (bst) and, with
+// pos, its first term's offset and per term its column's position in the C row; with inv,
+// per A entry k and position p of the C row the B row's entry there, inv[k W + p] = entry + 1
+// (inv cleared by the caller: 0 for none).
 template <int G, typename PT>
 __global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shift, const int* __restrict__ Aptr,
                                                   const int* __restrict__ Acol, const int* __restrict__ Bptr,
                                                   const int* __restrict__ Bcol, const int* __restrict__ Cptr,
                                                   int* __restrict__ Ccol, const int64_t* __restrict__ off,
                                                   int* __restrict__ bst, uint16_t* __restrict__ tof,
-                                                  PT* __restrict__ pos) {
+                                                  PT* __restrict__ pos, uint8_t* __restrict__ inv, int W) {
     extern __shared__ __align__(16) unsigned char sym_smem[];
     const int lane = threadIdx.x & (G - 1), gi = threadIdx.x / G;
     unsigned char* base = sym_smem + (size_t)gi * 8 * H;
@@ -181,13 +189,11 @@ __global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shif
     const int b = Aptr[row], e = Aptr[row + 1];
     sym_walk<G>(
         lane, lg, b, e, Acol, Bptr, Bcol,
-        [&](int k, int to, int b0) {
-            if (pos != nullptr) {
-                bst[k] = b0;
-                tof[k] = (uint16_t)to;
-            }
+        [&](int k, int to, int b0, int) {
+            if (bst != nullptr) bst[k] = b0;
+            if (tof != nullptr) tof[k] = (uint16_t)to;
         },
-        [&](int, int c) { sym_insert(tab, H, shift, c); });
+        [&](int, int, int, int c) { sym_insert(tab, H, shift, c); });
     wave_fence();
     int u = 0;
     const int shiftg = (threadIdx.x & 63) & ~(G - 1);
@@ -215,13 +221,16 @@ __global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shif
             rank[slot] = (uint16_t)r;
         }
     }
-    if (pos == nullptr) return;
+    if (pos == nullptr && inv == nullptr) return;
     wave_fence();
-    PT* prow = pos + off[row];
-    sym_walk<G>(lane, lg, b, e, Acol, Bptr, Bcol, [](int, int, int) {}, [&](int t, int c) {
+    PT* prow = pos != nullptr ? pos + off[row] : nullptr;
+    sym_walk<G>(lane, lg, b, e, Acol, Bptr, Bcol, [](int, int, int, int) {}, [&](int k, int q, int t, int c) {
         unsigned h = sym_hash(c, shift);
         for (int p = 0; p < H && tab[h] != c; ++p) h = (h + 1) & (unsigned)(H - 1);
-        prow[t] = (PT)rank[h];
+        if (prow != nullptr)
+            prow[t] = (PT)rank[h];
+        else
+            inv[(size_t)k * W + rank[h]] = (uint8_t)(q + 1);
     });
 }
 
@@ -264,13 +273,13 @@ bool symbolic_count(const Csr& A, const Csr& B, Csr& C, int64_t* off, SymSizes& 
     int32_t* cnt = dnew<int32_t>((size_t)n + 1, s);
     int64_t* terms = dnew<int64_t>((size_t)n + 1, s);
     int* stat = dnew<int>(4, s);
-    int64_t* tot = dnew<int64_t>(5, s);
+    int64_t* tot = dnew<int64_t>(6, s);
     const double mean_b = B.nrows > 0 ? (double)B.nnz / (double)B.nrows : 0.0;
     z.mean_b = mean_b;
     z.mean_terms = n > 0 ? (double)A.nnz / (double)n * mean_b : 0.0;
     const int lg_b = std::min(log2_ceil(mean_b), 6);
     bool fits = false;
-    int64_t h[5] = {0, 0, 0, 0, 0};
+    int64_t h[6] = {0, 0, 0, 0, 0, 0};
     // rows keep a small share of their terms as distinct columns: start from half the mean
     // number of terms and enlarge the table when some row overflows it
     for (int H = std::min(SYM_H_MAX, std::max(SYM_H_MIN, 1 << log2_ceil(0.5 * z.mean_terms)));;) {
@@ -297,6 +306,7 @@ bool symbolic_count(const Csr& A, const Csr& B, Csr& C, int64_t* off, SymSizes& 
     z.terms = h[1];
     z.max_terms = h[3];
     z.maxlen = (int)h[4];
+    z.max_b = (int)h[5];
     if (z.terms >= ((int64_t)1 << 31)) {
         dfree(C.ptr, s);
         C.ptr = nullptr;
@@ -317,17 +327,18 @@ void symbolic_fill(const Csr& A, const Csr& B, const Csr& C, const GalShape& gs,
     const int n = A.nrows;
     if (n == 0) return;
     const int H = std::min(SYM_H_MAX, std::max(SYM_H_MIN, 1 << log2_ceil(1.5 * z.maxlen)));
+    if (gs.inv != nullptr) HIP_CHECK(hipMemsetAsync(gs.inv, 0, (size_t)A.nnz * gs.inv_w, s));
     const int g = sym_group(z.mean_terms, H), lg = std::min(std::min(log2_ceil(z.mean_b), 6), log2_ceil(g));
     const int t = sym_threads(g, (size_t)8 * H), rows = t / g, shift = 32 - log2_ceil(H);
     const unsigned nb = (unsigned)((n + rows - 1) / rows);
     if (gs.wide)
         AMG_WITH_SYM_G(g, (k_sym_fill<G, uint16_t><<<nb, t, (size_t)rows * 8 * H, s>>>(
                               n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, C.ptr, C.col, off, gs.bst, gs.tof,
-                              (uint16_t*)gs.pos)));
+                              (uint16_t*)gs.pos, gs.inv, gs.inv_w)));
     else
         AMG_WITH_SYM_G(g, (k_sym_fill<G, uint8_t><<<nb, t, (size_t)rows * 8 * H, s>>>(
                               n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, C.ptr, C.col, off, gs.bst, gs.tof,
-                              (uint8_t*)gs.pos)));
+                              (uint8_t*)gs.pos, gs.inv, gs.inv_w)));
     HIP_LAUNCH_CHECK();
 }
 

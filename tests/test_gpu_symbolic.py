@@ -83,6 +83,51 @@ def test_product_patterns(name):
     g.close()
 
 
+@pytest.mark.parametrize("rows,per_row,couplings,span", [
+    (5, 1, 3, 5), (60, 2, 6, 9), (1024, 2, 5, 30), (1025, 2, 5, 30), (4096, 3, 4, 40), (4097, 3, 4, 40),
+    (300, 12, 40, 120), (300, 30, 60, 240), (2000, 12, 30, 130), (2000, 20, 50, 250)])
+def test_small_products_match_position_map(monkeypatch, rows, per_row, couplings, span):
+    """The small products' owner form (a workgroup per row, G lanes per row; 8 to 248 columns
+    in a row) against the position-map form, bit for bit, in FP64 and FP32."""
+    from paper_2108_02054_amd import AMG
+    g = np.random.default_rng(rows)
+    n, mid = 6 * rows, rows
+    near = lambda a, d, m: np.clip(a + g.integers(-d, d + 1, len(a)), 0, m - 1)  # noqa: E731
+    i = np.repeat(np.arange(n), 3)
+    A = spd_from(n, i, near(i, 8, n), 3)
+    agg = np.arange(n) // 6
+    r = np.repeat(np.arange(n), per_row)
+    P0 = sp.coo_matrix((np.ones(len(r) + n), (np.r_[r, np.arange(n)], np.r_[near(agg[r], span // 4, mid), agg])),
+                       shape=(n, mid)).tocsr()
+    P0.data[:] = g.uniform(0.2, 1.0, P0.nnz)
+    P0.sort_indices()
+    nc = max(2, mid // 3)
+    agg1 = np.arange(mid) * nc // mid
+    r = np.repeat(np.arange(mid), 2)
+    P1 = sp.coo_matrix((np.ones(len(r) + mid), (np.r_[r, np.arange(mid)], np.r_[near(agg1[r], max(1, span // 8), nc), agg1])),
+                       shape=(mid, nc)).tocsr()
+    P1.data[:] = g.uniform(0.2, 1.0, P1.nnz)
+    P1.sort_indices()
+    args = lambda: [(T(P.indptr.astype(np.int32)), T(P.indices.astype(np.int32)), T(P.data), P.shape[1])  # noqa: E731
+                    for P in (P0, P1)]
+    print(f"case owner form rows={rows} per_row={per_row} span={span}", flush=True)
+    for precision in (0, 1):
+        got = []
+        for form in (None, "pos"):
+            if form:
+                monkeypatch.setenv("AMGMI_GALERKIN", form)
+            else:
+                monkeypatch.delenv("AMGMI_GALERKIN", raising=False)
+            h = AMG(T(A.indptr.astype(np.int32)), T(A.indices.astype(np.int32)), T(A.data), transfer=args(),
+                    precision=precision, smoother=rows % 2, coarse_enough=2048)
+            h.rebuild(T(1.25 * A.data))
+            got.append([h.level(l) for l in range(3)])
+            h.close()
+        for a, b in zip(*got):
+            assert np.array_equal(a["A"][2], b["A"][2])
+            assert a["m"] is None or np.array_equal(a["m"], b["m"])
+
+
 def test_v_cycle_of_long_restriction_rows():
     """One aggregate of 5000 rows: its row of R is longer than the ranked transpose takes."""
     from paper_2108_02054_amd import AMG
