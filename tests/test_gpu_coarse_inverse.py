@@ -1,12 +1,22 @@
 """The dense inverse of the coarsest operator at the edges of its tiles: 16-pivot blocks in
 one workgroup up to 128 rows, 64-pivot blocks over the device above (an odd or an even
 number of block steps, a ragged last block)."""
+import gc
+
 import numpy as np
 import pytest
 
 from tests.gpu_util import T, rel_max
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def no_garbage():
+    """Device memory held by reference cycles of an earlier test is given back first."""
+    gc.collect()
+    yield
+    gc.collect()
 
 
 def band_spd(n, seed):

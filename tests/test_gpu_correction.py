@@ -1,5 +1,7 @@
 """The coarse correction and the first post-sweep in one pass (Q = (I - M A) P on A P's
 pattern) against the separate prolongation and sweep, and against the oracle's V-cycle."""
+import gc
+
 import numpy as np
 import pytest
 
@@ -7,6 +9,14 @@ from tests.gpu_util import T, both, rel_max
 from workloads import lognormal_27pt, two_fluid_7pt
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def no_garbage():
+    """Device memory held by reference cycles of an earlier test is given back first."""
+    gc.collect()
+    yield
+    gc.collect()
 
 
 def problem(kind):

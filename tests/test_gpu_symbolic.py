@@ -1,6 +1,8 @@
 """Galerkin patterns, transposes and launch shapes formed on the device, at the edges of
 their row forms: short rows, rows that overflow the first hash tables, rows beyond the
 largest (sorted instead), long rows of R, rows with no entries in P."""
+import gc
+
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -8,6 +10,14 @@ import scipy.sparse as sp
 from tests.gpu_util import T, rel_max
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def no_garbage():
+    """Device memory held by reference cycles of an earlier test is given back first."""
+    gc.collect()
+    yield
+    gc.collect()
 
 
 def spd_from(n, i, j, seed):
