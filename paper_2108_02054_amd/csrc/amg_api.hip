@@ -1208,7 +1208,10 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
     alloc_cg(c);
     configure_tail(c);
     configure_dia(c);
+    // (whether A_0's values are symmetric: products before the first solve read half of them)
+    HIP_CHECK(hipMemcpyAsync(c->h_red, c->rs.scal(), S_COUNT * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
+    note_dia_symmetry(c);
     ph[6] = ms_since(t_all);
     std::memcpy(c->phase_ms, ph, sizeof(ph));
 }

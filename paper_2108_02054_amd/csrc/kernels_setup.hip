@@ -151,19 +151,25 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 
 enum : uint8_t { ST_UNDECIDED = 0, ST_ROOT = 1, ST_REMOVED = 2, ST_ISOLATED = 3 };
 
-__global__ void k_mis_init(int n, const uint8_t* __restrict__ isolated, uint8_t* __restrict__ state) {
+__global__ void k_mis_init(int n, const uint8_t* __restrict__ isolated, uint8_t* __restrict__ state,
+                           uint64_t* __restrict__ m1, uint8_t* __restrict__ c1) {
     const int i = blockIdx.x * TPB + threadIdx.x;
-    if (i < n) state[i] = isolated[i] ? ST_ISOLATED : ST_UNDECIDED;
+    if (i >= n) return;
+    state[i] = isolated[i] ? ST_ISOLATED : ST_UNDECIDED;
+    m1[i] = 1;
+    c1[i] = 0;
 }
 
-// m1[i] = max priority of an undecided node among i and its strong neighbours (0: none).
+// m1[i] = max priority of an undecided node among i and its strong neighbours (0: none, and
+// then none in any later round either: the row is not read again, which leaves a few rounds'
+// worth of work in six or seven).
 __global__ void k_mis_max1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                            const uint8_t* __restrict__ strong, const uint8_t* __restrict__ state,
                            uint64_t* __restrict__ m1,
                            const int* __restrict__ go) {
     if (go != nullptr && *go == 0) return;
     const int i = xcd_block() * TPB + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || m1[i] == 0) return;
     uint64_t m = state[i] == ST_UNDECIDED ? mix64((uint64_t)i) : 0;
     for (int k = ptr[i]; k < ptr[i + 1]; ++k) {
         if (!strong[k]) continue;
@@ -196,18 +202,18 @@ __global__ void k_mis_max2(int n, const int* __restrict__ ptr, const int* __rest
     if (m == mix64((uint64_t)i)) state[i] = ST_ROOT;
 }
 
-// c1[i] = i is a root or has a strong root neighbour.
+// c1[i] = i is a root or has a strong root neighbour: a new root (a root outside c1, since a
+// node next to an earlier one has been removed) marks itself and its neighbours; strength is
+// symmetric, and no other root is near enough to write the same marks.
 __global__ void k_mis_cover1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                              const uint8_t* __restrict__ strong, const uint8_t* __restrict__ state,
-                             uint8_t* __restrict__ c1,
-                           const int* __restrict__ go) {
+                             uint8_t* __restrict__ c1, const int* __restrict__ go) {
     if (go != nullptr && *go == 0) return;
     const int i = xcd_block() * TPB + threadIdx.x;
-    if (i >= n) return;
-    bool c = state[i] == ST_ROOT;
-    for (int k = ptr[i]; k < ptr[i + 1] && !c; ++k)
-        if (strong[k] && state[col[k]] == ST_ROOT) c = true;
-    c1[i] = c ? 1 : 0;
+    if (i >= n || state[i] != ST_ROOT || c1[i]) return;
+    c1[i] = 1;
+    for (int k = ptr[i]; k < ptr[i + 1]; ++k)
+        if (strong[k]) c1[col[k]] = 1;
 }
 
 // Undecided nodes within strong distance 2 of a root are removed; any node still
@@ -235,7 +241,7 @@ void run_mis2(const Csr& A, const uint8_t* strong, const uint8_t* isolated, uint
     uint64_t* m1 = dnew<uint64_t>((size_t)n, s);
     uint8_t* c1 = dnew<uint8_t>((size_t)n, s);
     const unsigned nb = blocks_for(n);
-    k_mis_init<<<nb, TPB, 0, s>>>(n, isolated, state);
+    k_mis_init<<<nb, TPB, 0, s>>>(n, isolated, state, m1, c1);
     HIP_LAUNCH_CHECK();
     // Rounds are queued MIS_BATCH at a time and read back once: a round whose predecessor
     // left no undecided node returns at once (left[r]: round r left one), where reading the
@@ -283,29 +289,38 @@ __global__ void k_agg_pass1(int n, const int* __restrict__ ptr, const int* __res
 
 // Pass 2: a node left over joins the pass-1 aggregate of its strong neighbour j with the
 // largest a_ij * a_ji (ties: the smaller aggregate id).
-__global__ void k_agg_pass2(int n, const int* __restrict__ ptr, const int* __restrict__ col,
-                            const double* __restrict__ val, const uint8_t* __restrict__ strong,
-                            const int* __restrict__ tpos, const uint8_t* __restrict__ state,
-                            const int* __restrict__ agg1, int* __restrict__ agg, int* __restrict__ flags) {
-    const int i = xcd_block() * TPB + threadIdx.x;
+template <int G>
+__global__ __launch_bounds__(TPB) void k_agg_pass2(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+                                                   const double* __restrict__ val, const uint8_t* __restrict__ strong,
+                                                   const int* __restrict__ tpos, const uint8_t* __restrict__ state,
+                                                   const int* __restrict__ agg1, int* __restrict__ agg,
+                                                   int* __restrict__ flags) {
+    const int lane = threadIdx.x & (G - 1);
+    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
     if (i >= n) return;
     const int a1 = agg1[i];
     if (a1 >= 0 || state[i] == ST_ISOLATED) {
-        agg[i] = a1;
+        if (lane == 0) agg[i] = a1;
         return;
     }
     int best = -1;
     double best_w = 0.0;
-    for (int k = ptr[i]; k < ptr[i + 1]; ++k) {
-        if (!strong[k]) continue;
-        const int aj = agg1[col[k]];
-        if (aj < 0) continue;
-        const double w = val[k] * val[tpos[k]];
-        if (best < 0 || w > best_w || (w == best_w && aj < best)) {
+    auto take = [&](int aj, double w) {
+        if (aj >= 0 && (best < 0 || w > best_w || (w == best_w && aj < best))) {
             best = aj;
             best_w = w;
         }
+    };
+    const int e = ptr[i + 1];
+    for (int k = ptr[i] + lane; k < e; k += G)
+        if (strong[k]) take(agg1[col[k]], val[k] * val[tpos[k]]);
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) {
+        const int aj = __shfl_xor(best, o, G);
+        const double w = __shfl_xor(best_w, o, G);
+        take(aj, w);
     }
+    if (lane != 0) return;
     if (best < 0) atomicOr(&flags[F_NOAGG], 1);
     agg[i] = best;
 }
@@ -344,7 +359,8 @@ int32_t run_aggregate(const Csr& A, const uint8_t* strong, const int32_t* tpos, 
     HIP_CHECK(hipMemsetAsync(isr + n, 0, sizeof(int), s));
     scan_exclusive<int, int>(isr, id, n + 1, s);
     k_agg_pass1<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, id, agg1);
-    k_agg_pass2<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, A.val, strong, tpos, state, agg1, agg, flags);
+    AMG_ROW_LANES(A, (k_agg_pass2<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, A.col, A.val, strong, tpos,
+                                                                              state, agg1, agg, flags)));
     HIP_LAUNCH_CHECK();
     int32_t nc = 0;
     HIP_CHECK(hipMemcpyAsync(&nc, id + n, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -477,9 +493,11 @@ __global__ __launch_bounds__(TPB) void k_filter(int n, const int* __restrict__ p
         // kind of an entry: 0 dropped, 1 weak, 2 strong, 3 diagonal
         auto kind = [&](int k) { return k >= e ? 0 : col[k] == i ? 3 : iso ? 0 : strong[k] ? 2 : 1; };
         double d = val[diag_pos[i]];
+        const int k0 = b + lane, w0 = kind(k0);  // the row's first G entries, read once
+        const double v0 = k0 < e ? val[k0] : 0.0;
         for (int c0 = b; c0 < e; c0 += G) {
-            const int k = c0 + lane, w = kind(k);
-            const double v = k < e ? val[k] : 0.0;
+            const int k = c0 + lane, w = c0 == b ? w0 : kind(k);
+            const double v = c0 == b ? v0 : k < e ? val[k] : 0.0;
             for (int t = 0; t < min(G, e - c0); ++t) {
                 const double vt = __shfl(v, t, G);
                 if (__shfl(w, t, G) == 1) d += vt;
@@ -487,8 +505,8 @@ __global__ __launch_bounds__(TPB) void k_filter(int n, const int* __restrict__ p
         }
         double s = 0.0;
         for (int c0 = b; c0 < e; c0 += G) {
-            const int k = c0 + lane, w = kind(k);
-            const double v = k < e ? val[k] : 0.0;
+            const int k = c0 + lane, w = c0 == b ? w0 : kind(k);
+            const double v = c0 == b ? v0 : k < e ? val[k] : 0.0;
             for (int t = 0; t < min(G, e - c0); ++t) {
                 const double vt = __shfl(v, t, G);
                 const int wt = __shfl(w, t, G);
@@ -533,20 +551,28 @@ __global__ __launch_bounds__(TPB) void k_entry_agg(int n, const int* __restrict_
 }
 
 // Number of distinct aggregates among the columns of row i of A_F; that is the length of
-// row i of A_F P_tent and of the smoothed P.  first[k]: entry k is its aggregate's first.
+// row i of A_F P_tent and of the smoothed P.  key[k] = 2 * aggregate + 1 for an aggregate's
+// first entry, 2 * aggregate for its others, -1 for entries A_F drops.
 template <int G>
 __global__ __launch_bounds__(TPB) void k_pcount(int n, const int* __restrict__ ptr, const int* __restrict__ eagg,
-                                                uint8_t* __restrict__ first, int* __restrict__ cnt) {
+                                                int* __restrict__ key, int* __restrict__ cnt) {
     const int lane = threadIdx.x & (G - 1);
     const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
     if (i >= n) return;
     const int b = ptr[i], e = ptr[i + 1];
     int c = 0;
-    for (int k = b + lane; k < e; k += G) {
-        const int a = eagg[k];
+    for (int c0 = b; c0 < e; c0 += G) {
+        const int k = c0 + lane;
+        const int a = k < e ? eagg[k] : -1;
         bool f = a >= 0;
-        for (int q = b; q < k && f; ++q) f = eagg[q] != a;
-        first[k] = f ? 1 : 0;
+        for (int c1 = b; c1 <= c0; c1 += G) {  // against the entries before it
+            const int aq = c1 == c0 ? a : eagg[c1 + lane];
+            for (int t = 0; t < G; ++t) {
+                const int at = __shfl(aq, t, G);  // (outside any condition: every lane passes its own on)
+                f = f && !(at == a && c1 + t < k);
+            }
+        }
+        if (k < e) key[k] = a < 0 ? -1 : 2 * a + (f ? 1 : 0);
         c += f ? 1 : 0;
     }
 #pragma unroll
@@ -557,13 +583,12 @@ __global__ __launch_bounds__(TPB) void k_pcount(int n, const int* __restrict__ p
 // Row i of P = P_tent - (omega / d_i) * (A_F P_tent), omega = (4/3) / rho.  Columns are
 // the distinct aggregates of the row in increasing order; for column J the sum over the
 // row's entries with aggregate J is taken in column order starting from 0.  The lane of an
-// aggregate's first entry walks the row once for its place (the smaller aggregates' first
-// entries) and its sum.
+// aggregate's first entry forms its place (the smaller aggregates' first entries) and its
+// sum from the row's entries passed round the group.
 template <int G>
 __global__ __launch_bounds__(TPB) void k_pfill(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                                                const double* __restrict__ val, const int* __restrict__ agg,
-                                               const int* __restrict__ eagg, const uint8_t* __restrict__ first,
-                                               const double* __restrict__ dF,
+                                               const int* __restrict__ key, const double* __restrict__ dF,
                                                const unsigned long long* __restrict__ rho_bits,
                                                const int* __restrict__ Pptr, int* __restrict__ Pcol,
                                                double* __restrict__ Pval) {
@@ -578,16 +603,24 @@ __global__ __launch_bounds__(TPB) void k_pfill(int n, const int* __restrict__ pt
     const double di = dF[i];
     const double scale = omega / di;
     const int b = ptr[i], e = ptr[i + 1];
-    for (int k = b + lane; k < e; k += G) {
-        if (!first[k]) continue;
-        const int J = eagg[k];
+    for (int c0 = b; c0 < e; c0 += G) {
+        const int kk = c0 + lane < e ? key[c0 + lane] : -1;
+        const bool mine = kk >= 0 && (kk & 1);
+        const int J = kk >> 1;
         int r = 0;
         double sJ = 0.0;
-        for (int q = b; q < e; ++q) {
-            const int a = eagg[q];
-            if (a == J) sJ += (col[q] == i) ? di : val[q];
-            r += (a >= 0 && a < J && first[q]) ? 1 : 0;
+        for (int c1 = b; c1 < e; c1 += G) {
+            const int q = c1 + lane;
+            const int kq = q < e ? key[q] : -1;
+            const double vq = q < e ? (col[q] == i ? di : val[q]) : 0.0;
+            for (int t = 0; t < min(G, e - c1); ++t) {
+                const int kt = __shfl(kq, t, G);
+                const double vt = __shfl(vq, t, G);
+                if (kt >= 0 && (kt >> 1) == J) sJ += vt;
+                r += kt >= 0 && (kt & 1) && (kt >> 1) < J ? 1 : 0;
+            }
         }
+        if (!mine) continue;
         const double pt = (J == ai) ? 1.0 : 0.0;
         Pcol[p0 + r] = J;
         Pval[p0 + r] = pt - scale * sJ;
@@ -614,7 +647,7 @@ void build_prolongator(const Csr& A, const uint8_t* strong, const int32_t* diag_
     double* dF = nullptr;
     unsigned long long* rho_bits = nullptr;
     int* eagg = nullptr;
-    uint8_t* first = nullptr;
+    int* key = nullptr;
     int* cnt = dnew<int>((size_t)n + 1, s);
     if (plain) {
         k_plain_count<<<nb, TPB, 0, s>>>(n, agg, cnt);
@@ -622,12 +655,12 @@ void build_prolongator(const Csr& A, const uint8_t* strong, const int32_t* diag_
         dF = dnew<double>((size_t)n, s);
         rho_bits = dnew<unsigned long long>(1, s);
         eagg = dnew<int>((size_t)A.nnz, s);
-        first = dnew<uint8_t>((size_t)A.nnz, s);
+        key = dnew<int>((size_t)A.nnz, s);
         HIP_CHECK(hipMemsetAsync(rho_bits, 0, sizeof(unsigned long long), s));
         AMG_ROW_LANES(A, (k_filter<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, A.col, A.val, strong, diag_pos,
                                                                                agg, dF, rho_bits)));
         AMG_ROW_LANES(A, (k_entry_agg<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, A.col, strong, agg, eagg)));
-        AMG_ROW_LANES(A, (k_pcount<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, eagg, first, cnt)));
+        AMG_ROW_LANES(A, (k_pcount<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, eagg, key, cnt)));
     }
     HIP_LAUNCH_CHECK();
     HIP_CHECK(hipMemsetAsync(cnt + n, 0, sizeof(int), s));
@@ -645,10 +678,10 @@ void build_prolongator(const Csr& A, const uint8_t* strong, const int32_t* diag_
         k_plain_fill<<<nb, TPB, 0, s>>>(n, agg, P.ptr, P.col, P.val);
     else
         AMG_ROW_LANES(A, (k_pfill<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(
-                             n, A.ptr, A.col, A.val, agg, eagg, first, dF, rho_bits, P.ptr, P.col, P.val)));
+                             n, A.ptr, A.col, A.val, agg, key, dF, rho_bits, P.ptr, P.col, P.val)));
     HIP_LAUNCH_CHECK();
     dfree(cnt, s);
-    for (void* q : {(void*)dF, (void*)rho_bits, (void*)eagg, (void*)first})
+    for (void* q : {(void*)dF, (void*)rho_bits, (void*)eagg, (void*)key})
         if (q) dfree(q, s);
 }
 

@@ -38,8 +38,8 @@ __device__ __forceinline__ void raise_max(int* p, int v) {
 // LDS (open addressing, integer compare-and-swap).  Two passes: k_sym_count counts the
 // row's entries and terms; k_sym_fill collects them again, ranks the distinct columns (the
 // rank is the place in the sorted row), and writes the columns and, term by term, the
-// positions, which is the same walk once more.  Bound by the gathers of the B rows, read
-// three times; nothing per term is written but its one- or two-byte position.  The former
+// positions.  Bound by the gathers of the B rows, read twice; nothing per term is written but
+// its one- or two-byte position.  The former
 // form wrote a 64-bit (row, column) key per term, radix-sorted the keys, kept the unique
 // ones and found each term's position by a binary search in the finished row: 16.5 ms of
 // a 128^3 setup (108 M terms at level 0).
@@ -49,16 +49,17 @@ constexpr size_t SYM_SMEM = 32768;               // LDS per workgroup aimed at
 
 __device__ __forceinline__ unsigned sym_hash(int c, int shift) { return ((unsigned)c * 2654435761u) >> shift; }
 
-// Inserts column c; 1 when it was not there, -1 when the table is full.
-__device__ __forceinline__ int sym_insert(int* tab, int H, int shift, int c) {
+// Inserts column c; its slot (fresh: it was not there), or -1 when the table is full.
+__device__ __forceinline__ int sym_insert(int* tab, int H, int shift, int c, bool& fresh) {
     unsigned h = sym_hash(c, shift);
+    fresh = false;
     for (int p = 0; p < H; ++p, h = (h + 1) & (unsigned)(H - 1)) {
         int cur = __hip_atomic_load(&tab[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        if (cur == c) return 0;
+        if (cur == c) return (int)h;
         if (cur == -1) {
             cur = atomicCAS(&tab[h], -1, c);
-            if (cur == -1) return 1;
-            if (cur == c) return 0;
+            fresh = cur == -1;
+            if (fresh || cur == c) return (int)h;
         }
     }
     return -1;
@@ -140,9 +141,9 @@ __global__ __launch_bounds__(TPB) void k_sym_count(int n, int lg, int H, int shi
     const int nterm = sym_walk<G>(lane, lg, Aptr[row], Aptr[row + 1], Acol, Bptr, Bcol,
                                   [&](int, int, int, int len) { mb = max(mb, len); },
                                   [&](int, int, int, int c) {
-                                      const int r = sym_insert(tab, H, shift, c);
-                                      u += r > 0;
-                                      full |= r < 0;
+                                      bool fresh;
+                                      full |= sym_insert(tab, H, shift, c, fresh) < 0;
+                                      u += fresh;
                                   });
     u = group_sum_i<G>(u);
     full = group_sum_i<G>(full);
@@ -187,13 +188,22 @@ __global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shif
     for (int s = lane; s < H; s += G) tab[s] = -1;
     wave_fence();
     const int b = Aptr[row], e = Aptr[row + 1];
-    sym_walk<G>(
+    PT* prow = pos != nullptr ? pos + off[row] : nullptr;
+    // where a slot number fits a position's type the first walk leaves each term's slot in its
+    // place, and the ranks replace them in a pass over contiguous memory; else the row is
+    // walked again
+    const bool by_slot = prow != nullptr && (sizeof(PT) > 1 || H <= 256);
+    const int nterm = sym_walk<G>(
         lane, lg, b, e, Acol, Bptr, Bcol,
         [&](int k, int to, int b0, int) {
             if (bst != nullptr) bst[k] = b0;
             if (tof != nullptr) tof[k] = (uint16_t)to;
         },
-        [&](int, int, int, int c) { sym_insert(tab, H, shift, c); });
+        [&](int, int, int t, int c) {
+            bool fresh;
+            const int slot = sym_insert(tab, H, shift, c, fresh);
+            if (by_slot) prow[t] = (PT)slot;
+        });
     wave_fence();
     int u = 0;
     const int shiftg = (threadIdx.x & 63) & ~(G - 1);
@@ -223,7 +233,11 @@ __global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shif
     }
     if (pos == nullptr && inv == nullptr) return;
     wave_fence();
-    PT* prow = pos != nullptr ? pos + off[row] : nullptr;
+    if (by_slot) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // (the slots other lanes wrote)
+        for (int t = lane; t < nterm; t += G) prow[t] = (PT)rank[prow[t]];
+        return;
+    }
     sym_walk<G>(lane, lg, b, e, Acol, Bptr, Bcol, [](int, int, int, int) {}, [&](int k, int q, int t, int c) {
         unsigned h = sym_hash(c, shift);
         for (int p = 0; p < H && tab[h] != c; ++p) h = (h + 1) & (unsigned)(H - 1);
@@ -451,12 +465,19 @@ static_assert(RB_THREADS == 256, "one workgroup reads the rows of the largest bl
 __global__ __launch_bounds__(TPB) void k_row_blocks(int n, const int* __restrict__ ptr, int* __restrict__ most) {
     __shared__ int sp[RB_THREADS + 1];
     __shared__ int sm[TPB / 64];
-    const int r0 = blockIdx.x * RB_THREADS;
-    for (int i = threadIdx.x; i <= RB_THREADS; i += TPB) sp[i] = ptr[min(r0 + i, n)];
-    __syncthreads();
+    int w[ROW_BLOCK_SIZES] = {};
+    const int nblk = (n + RB_THREADS - 1) / RB_THREADS;
+    for (int k = blockIdx.x; k < nblk; k += gridDim.x) {
+        const int64_t r0 = (int64_t)k * RB_THREADS;
+        for (int i = threadIdx.x; i <= RB_THREADS; i += TPB) sp[i] = ptr[r0 + i < n ? r0 + i : n];
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < ROW_BLOCK_SIZES; ++b)
+            if ((int)threadIdx.x < (RB_THREADS >> b)) w[b] = max(w[b], sp[(threadIdx.x + 1) << b] - sp[threadIdx.x << b]);
+        __syncthreads();
+    }
     for (int b = 0; b < ROW_BLOCK_SIZES; ++b) {
-        const int nbk = RB_THREADS >> b;
-        int v = (int)threadIdx.x < nbk ? sp[(threadIdx.x + 1) << b] - sp[threadIdx.x << b] : 0;
+        int v = w[b];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
         if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
@@ -470,8 +491,8 @@ __global__ __launch_bounds__(TPB) void k_row_blocks(int n, const int* __restrict
 }
 
 void launch_row_blocks(const Csr& A, int* most, hipStream_t s) {
-    k_row_blocks<<<(unsigned)std::max<int64_t>(1, ((int64_t)A.nrows + RB_THREADS - 1) / RB_THREADS), TPB, 0, s>>>(
-        A.nrows, A.ptr, most);
+    const int64_t nb = ((int64_t)A.nrows + RB_THREADS - 1) / RB_THREADS;
+    k_row_blocks<<<(unsigned)std::min<int64_t>(std::max<int64_t>(1, nb), 512), TPB, 0, s>>>(A.nrows, A.ptr, most);
     HIP_LAUNCH_CHECK();
 }
 
