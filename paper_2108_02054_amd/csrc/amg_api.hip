@@ -492,6 +492,13 @@ void configure(amg_ctx* c, const std::vector<Csr*>& ms, hipStream_t s) {
         Csr& A = *ms[k];
         A.g = lane_group(A.nrows > 0 ? (double)A.nnz / A.nrows : 1.0);
         A.rpb = lanes_only() ? 0 : pick_rows_per_block(&h[k * STAT], A.nrows);
+        // a block system's restriction keeps whole nodes together, so that it can form the next
+        // level's first sweep (up to 4 rows a row has the same 64 lanes, and the same sum)
+        const int B = c->prm.block_size;
+        if (A.rpb > 0 && A.rpb < B && (B == 2 || B == 4) && h[k * STAT + B / 2] <= RB_CAP &&
+            A.nrows > c->prm.coarse_enough)
+            for (const Level& L : c->lv)
+                if (&A == &L.R) A.rpb = B;
         release(c, A.c16);
         release(c, A.cblk);
         A.c16 = nullptr;
@@ -1361,7 +1368,7 @@ T* vcycle_level(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* ep = nu
 // Algorithm 2 with the scalar-diagonal fused forms left out; the coarse tail as for
 // scalar systems.
 template <typename T>
-T* vcycle_level_block(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* ep) {
+T* vcycle_level_block(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* ep, int ready) {
     hipStream_t s = c->stream;
     const Level& L = c->lv[(size_t)l];
     const amg_params& p = c->prm;
@@ -1372,17 +1379,17 @@ T* vcycle_level_block(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* e
     T* r = (T*)L.r;
     const T* m = L.mv<T>();
     const T* rres = f;
-    auto sweep = [&](const T* uu, T* uout) { launch_node_sweep<T>(L, B, m, f, uu, uout, s); };
+    auto sweep = [&](const T* uu, const T* uc, T* uout) { launch_node_sweep<T>(L, B, m, f, uu, uc, uout, s); };
     if (p.npre == 0) {
         HIP_CHECK(hipMemsetAsync(cur, 0, (size_t)n * sizeof(T), s));
     } else {
-        {
+        if (ready == 0) {
             Trace tr(c, AMG_K_SMOOTH0_RES, l);
             launch_block_apply<T>(n, B, m, f, (const T*)nullptr, cur, s);
         }
         for (int it = 1; it < p.npre; ++it) {
             Trace tr(c, AMG_K_JACOBI, l);
-            sweep(cur, other);
+            sweep(cur, nullptr, other);
             std::swap(cur, other);
         }
         Trace tr(c, AMG_K_SMOOTH0_RES, l);
@@ -1399,13 +1406,21 @@ T* vcycle_level_block(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* e
         run_tail<T>(c, l, rres);
         uc = (const T*)C.u;
     } else {
+        // the next level's first sweep from zero is formed by the restriction
+        int c_ready = 0;
         {
             Trace tr(c, AMG_K_RESTRICT, l);
-            launch_spmv<T>(L.R, rres, (T*)C.f, (const T*)nullptr, (T*)nullptr, s);
+            if (l + 2 < (int)c->lv.size() && p.npre > 0 &&
+                launch_spmv_nodes<T>(L.R, B, rres, (T*)C.f, C.mv<T>(), (T*)C.u, s))
+                c_ready = 1;
+            else
+                launch_spmv<T>(L.R, rres, (T*)C.f, (const T*)nullptr, (T*)nullptr, s);
         }
-        uc = vcycle_level<T>(c, l + 1, (const T*)C.f, nullptr, nullptr, 0);
+        uc = vcycle_level<T>(c, l + 1, (const T*)C.f, nullptr, nullptr, c_ready);
     }
-    {
+    // the first post-sweep adds the correction as it reads the iterate
+    const T* add = L.nagg != nullptr && p.npost > 0 ? uc : nullptr;
+    if (add == nullptr) {
         Trace tr(c, AMG_K_PROLONG, l);
         if (L.nagg != nullptr)
             launch_node_prolong<T>(L, B, uc, cur, s);
@@ -1418,14 +1433,15 @@ T* vcycle_level_block(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* e
         Trace tr(c, AMG_K_JACOBI, l);
         if constexpr (std::is_same<T, double>::value) {
             if (ep && dst == out) {  // the CG's r.z partials in the same pass
-                ep->nb = launch_node_sweep_rz(L, B, m, f, cur, dst, c->rs, s);
+                ep->nb = launch_node_sweep_rz(L, B, m, f, cur, add, dst, c->rs, s);
                 fused = true;
             } else {
-                sweep(cur, dst);
+                sweep(cur, add, dst);
             }
         } else {
-            sweep(cur, dst);
+            sweep(cur, add, dst);
         }
+        add = nullptr;
         if (dst == other)
             std::swap(cur, other);
         else
@@ -1468,7 +1484,7 @@ T* vcycle_level(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* ep, int
     const T* m = L.mv<T>();
     const T* rres = r;
     const int n = L.A.nrows;
-    if (p.block_size > 1) return vcycle_level_block<T>(c, l, f, out, ep);
+    if (p.block_size > 1) return vcycle_level_block<T>(c, l, f, out, ep, ready);
     const bool dia = l == 0 && c->dia.ndiag > 0;  // level 0 in diagonal storage
     auto residual = [&](const T* uu) {
         if (dia)
@@ -1690,7 +1706,8 @@ amg_status pcg(amg_ctx* c, const double* f, double* u, amg_solve_info* info) {
     // level 0 in CSR the first sweep; in mixed precision it stores r in FP32 for the V-cycle.
     const bool fuse_dia = !mixed(c) && c->dia.ndiag > 0 && p.npre == 1 && c->lv.size() > 1;
     const bool fuse_cast = mixed(c);
-    const bool fuse_sweep = !mixed(c) && p.npre > 0 && p.block_size == 1 && c->lv.size() > 1;  // level 0 in CSR
+    const bool fuse_sweep = !mixed(c) && p.npre > 0 && c->lv.size() > 1 &&
+                            (p.block_size & (p.block_size - 1)) == 0;  // level 0 in CSR
     precondition(1, 0);
     double* pold = c->pa;
     double* pnew = c->pb;
@@ -1727,7 +1744,7 @@ amg_status pcg(amg_ctx* c, const double* f, double* u, amg_solve_info* info) {
                 nb = launch_cg_update_cast(n, pnew, c->q, c->x, rc, (float*)L0.f, rs, s);
                 ready = 1;
             } else {
-                nb = launch_cg_update(n, pnew, c->q, c->x, rc, fuse_sweep ? L0.m : nullptr, (double*)L0.u, rs, s);
+                nb = launch_cg_update(n, p.block_size, pnew, c->q, c->x, rc, fuse_sweep ? L0.m : nullptr, (double*)L0.u, rs, s);
                 ready = fuse_sweep ? 1 : 0;
             }
         }

@@ -245,6 +245,9 @@ int red_grid_elems(int64_t n);
 // ------------------------------------------------------------------ solve kernels
 template <typename T>
 void launch_spmv(const Csr& A, const T* x, T* y, const T* m2, T* y2, hipStream_t s);
+// y = A x and, where it can (returns true), u = M y with the B x B blocks M of the row's node
+template <typename T>
+bool launch_spmv_nodes(const Csr& A, int B, const T* x, T* y, const T* m, T* u, hipStream_t s);
 template <typename T>
 void launch_residual(const Csr& A, const T* f, const T* u, T* r, hipStream_t s);
 template <typename T>
@@ -449,7 +452,8 @@ void launch_fin_rz(int nb, int flexible, int first, const RedScratch& rs, hipStr
 void launch_fin_pq(int nb, const RedScratch& rs, hipStream_t s);
 int launch_cg_pq(const Csr& A, const double* val, const double* z, const double* pold, double* pnew, double* q,
                  int first, const RedScratch& rs, hipStream_t s);
-int launch_cg_update(int n, const double* p, const double* q, double* x, double* r, const double* m, double* u,
+// with m also u = M r, M the diagonal m (B 1) or its B x B blocks (B 2, 4, 8)
+int launch_cg_update(int n, int B, const double* p, const double* q, double* x, double* r, const double* m, double* u,
                      const RedScratch& rs, hipStream_t s);
 
 // ------------------------------------------------------------------ Galerkin / smoother
@@ -521,13 +525,15 @@ void launch_block_apply(int n, int B, const T* m, const T* r, const T* uin, T* u
 int node_grid(int nn);
 template <typename T>
 void launch_node_residual(const Level& L, int B, const T* f, const T* u, T* r, hipStream_t s);
+// uout = u + M (f - A u); with uc u is uin + P uc (L.nagg set), else uin.
 template <typename T>
-void launch_node_sweep(const Level& L, int B, const T* m, const T* f, const T* uin, T* uout, hipStream_t s);
+void launch_node_sweep(const Level& L, int B, const T* m, const T* f, const T* uin, const T* uc, T* uout,
+                       hipStream_t s);
 int launch_node_cg_pq(const Level& L, int B, const double* val, const double* z, const double* pold, double* pnew,
                       double* q, int first, const RedScratch& rs, hipStream_t s);
-// z = uin + M (r - A uin) on level 0 with the r.z partials; returns their count.
-int launch_node_sweep_rz(const Level& L, int B, const double* m, const double* r, const double* uin, double* z,
-                         const RedScratch& rs, hipStream_t s);
+// z = u + M (r - A u) on level 0 with the r.z partials, u as above; returns their count.
+int launch_node_sweep_rz(const Level& L, int B, const double* m, const double* r, const double* uin, const double* uc,
+                         double* z, const RedScratch& rs, hipStream_t s);
 void launch_node_expand(const Csr& A, int B, const Csr& Nm, const uint8_t* nstrong, const int32_t* nagg,
                         uint8_t* strong, int32_t* agg, hipStream_t s);
 // Node Galerkin plan of levels L -> N (block size B; N's node pattern built): the aggregate

@@ -227,7 +227,11 @@ __device__ __forceinline__ double* rr_dest(const RedScratch& rs, bool bad) {
 
 // y = A x; with m2 given also y2 = m2 * y (the restriction forms the coarse level's first
 // smoothing sweep u = m f from zero at the same time).
-template <typename T>
+//
+// B > 1: block systems, m2 the B x B smoothing blocks of the coarse nodes; rpb is a multiple
+// of B, so that a workgroup holds whole nodes (56^3 nodes of 4 unknowns, restriction + first
+// sweep as two launches: 5.7 + 4.8 us to level 1, 4.6 + 3.9 to level 2; as one 6.5, 5.0).
+template <int B, typename T>
 __global__ __launch_bounds__(RB_THREADS) void k_rb_spmv(int n, int rpb, const int* __restrict__ ptr,
                                                         ColSrc cs, const T* __restrict__ val,
                                                         const T* __restrict__ x, T* __restrict__ y,
@@ -239,13 +243,27 @@ __global__ __launch_bounds__(RB_THREADS) void k_rb_spmv(int n, int rpb, const in
     const int row1 = min(row0 + rpb, n);
     const int tpr = rb_tpr(rpb), r = threadIdx.x / tpr, lane = threadIdx.x & (tpr - 1);
     const bool own = r < row1 - row0 && lane == 0;
-    const T mi = (own && m2 != nullptr) ? m2[row0 + r] : T(0);
+    T mi[B];
+#pragma unroll
+    for (int q = 0; q < B; ++q) mi[q] = (own && m2 != nullptr) ? m2[(size_t)(row0 + r) * B + q] : T(0);
     rb_load(row0, row1, ptr, cs, xcd_block(), val, [&](int j) { return x[j]; }, sptr, sp);
+    T v = 0;
     if (r < row1 - row0) {
-        const T v = rb_rowsum(sptr, sp, r, lane, tpr);
+        v = rb_rowsum(sptr, sp, r, lane, tpr);
         if (lane == 0) {
             y[row0 + r] = v;
-            if (m2 != nullptr) y2[row0 + r] = mi * v;
+            if (B == 1 && m2 != nullptr) y2[row0 + r] = mi[0] * v;
+        }
+    }
+    if constexpr (B > 1) {
+        __shared__ T sy[RB_THREADS];
+        if (own) sy[r] = v;
+        __syncthreads();
+        if (own) {
+            T s = 0;
+#pragma unroll
+            for (int q = 0; q < B; ++q) s = s + mi[q] * sy[r - r % B + q];
+            y2[row0 + r] = s;
         }
     }
 }
@@ -506,7 +524,7 @@ static inline unsigned ew_blocks(int64_t n) {
 template <typename T>
 void launch_spmv(const Csr& A, const T* x, T* y, const T* m2, T* y2, hipStream_t s) {
     if (A.rpb > 0) {
-        timed_launch(k_rb_spmv<T>, grid_for(A.nrows, A.rpb), RB_THREADS, 0, s, A.nrows, A.rpb, (const int*)A.ptr,
+        timed_launch(k_rb_spmv<1, T>, grid_for(A.nrows, A.rpb), RB_THREADS, 0, s, A.nrows, A.rpb, (const int*)A.ptr,
                      colsrc(A), (const T*)A.v<T>(), x, y, m2, y2);
     } else {
         AMG_WITH_G(A.g, timed_launch(k_lg<G, T, 0>, grid_for((int64_t)A.nrows * G, TPB), TPB, 0, s, A.nrows,
@@ -514,6 +532,23 @@ void launch_spmv(const Csr& A, const T* x, T* y, const T* m2, T* y2, hipStream_t
                                      x, y, y2));
     }
     HIP_LAUNCH_CHECK();
+}
+// (the row blocks hold powers of two rows: those of other block sizes cut through nodes)
+template <typename T>
+bool launch_spmv_nodes(const Csr& A, int B, const T* x, T* y, const T* m, T* u, hipStream_t s) {
+    if (A.rpb == 0 || (B != 2 && B != 4 && B != 8) || A.rpb % B != 0) return false;
+    auto go = [&](auto kern) {
+        timed_launch(kern, grid_for(A.nrows, A.rpb), RB_THREADS, 0, s, A.nrows, A.rpb, (const int*)A.ptr, colsrc(A),
+                     (const T*)A.v<T>(), x, y, m, u);
+    };
+    if (B == 2)
+        go(k_rb_spmv<2, T>);
+    else if (B == 4)
+        go(k_rb_spmv<4, T>);
+    else
+        go(k_rb_spmv<8, T>);
+    HIP_LAUNCH_CHECK();
+    return true;
 }
 template <typename T>
 void launch_residual(const Csr& A, const T* f, const T* u, T* r, hipStream_t s) {
@@ -1923,6 +1958,7 @@ void launch_vcycle_tail(const TailArgs<T>& a, hipStream_t s) {
 
 #define AMG_INST(T)                                                                                 \
     template void launch_spmv<T>(const Csr&, const T*, T*, const T*, T*, hipStream_t);              \
+    template bool launch_spmv_nodes<T>(const Csr&, int, const T*, T*, const T*, T*, hipStream_t);   \
     template void launch_residual<T>(const Csr&, const T*, const T*, T*, hipStream_t);              \
     template void launch_jacobi<T>(const Csr&, const T*, const T*, const T*, T*, hipStream_t);      \
     template void launch_smooth0_residual<T>(const Csr&, const T*, const T*, T*, T*, hipStream_t);  \
@@ -2157,7 +2193,10 @@ __global__ __launch_bounds__(RB_THREADS) void k_cg_pq(int n, int rpb, const int*
 // x += alpha p; r -= alpha q; ||r||^2 partials (bounded grid).  On breakdown nothing moves.
 // With m also the cycle's first sweep u = m r, so that the residual after it gathers one
 // vector per entry instead of m and r (masked 101x83x90: residual 19.1 -> 12.9 us, update 7.9
-// -> 9.3 us).
+// -> 9.3 us).  B > 1: M of B x B blocks, the node's other residuals from its lanes (B divides
+// the wavefront; 56^3 nodes of 4 unknowns: update + product 7.6 + 5.7 us as two launches, 10.7
+// as one).
+template <int B>
 __global__ __launch_bounds__(TPB) void k_cg_update(int n, const double* __restrict__ p, const double* __restrict__ q,
                                                    double* __restrict__ x, double* __restrict__ r,
                                                    const double* __restrict__ m, double* __restrict__ u,
@@ -2172,7 +2211,15 @@ __global__ __launch_bounds__(TPB) void k_cg_update(int n, const double* __restri
             ri = __builtin_fma(-alpha, q[i], ri);
             r[i] = ri;
         }
-        if (m != nullptr) u[i] = m[i] * ri;
+        if constexpr (B == 1) {
+            if (m != nullptr) u[i] = m[i] * ri;
+        } else {  // (n and the stride are multiples of B: a node's lanes are in the loop together)
+            const int base = (int)threadIdx.x & 63 & ~(B - 1);
+            double s = 0;
+#pragma unroll
+            for (int b = 0; b < B; ++b) s = s + m[(size_t)i * B + b] * __shfl(ri, base + b, 64);
+            u[i] = s;
+        }
         loc[0] += ri * ri;
     }
     double* const dst[1] = {rr_dest(rs, bad)};
@@ -2246,10 +2293,20 @@ int launch_cg_pq(const Csr& A, const double* val, const double* z, const double*
     HIP_LAUNCH_CHECK();
     return nb;
 }
-int launch_cg_update(int n, const double* p, const double* q, double* x, double* r, const double* m, double* u,
+int launch_cg_update(int n, int B, const double* p, const double* q, double* x, double* r, const double* m, double* u,
                      const RedScratch& rs, hipStream_t s) {
     const int nb = red_grid_elems(n);
-    timed_launch(k_cg_update, nb, TPB, 0, s, n, p, q, x, r, m, u, rs);
+    auto go = [&](auto kern) { timed_launch(kern, nb, TPB, 0, s, n, p, q, x, r, m, u, rs); };
+    if (m == nullptr || B == 1)
+        go(k_cg_update<1>);
+    else if (B == 2)
+        go(k_cg_update<2>);
+    else if (B == 4)
+        go(k_cg_update<4>);
+    else if (B == 8)
+        go(k_cg_update<8>);
+    else
+        throw Fail{AMG_ERR_ARG, "an update with the first sweep needs blocks of 1, 2, 4 or 8"};
     HIP_LAUNCH_CHECK();
     return nb;
 }
