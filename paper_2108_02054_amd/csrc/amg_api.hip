@@ -815,6 +815,7 @@ void configure_dia(amg_ctx* c) {
                        offs[0] == -offs[6];
     if (seven && std::getenv("AMGMI_NO_MARCH") == nullptr && march_blocks(A.nrows, offs[6]) <= c->rs.cap) {
         D.march_a = offs[6];
+        D.omega = c->prm.smoother == 0 ? c->prm.jacobi_omega : 0.0;
         D.march_b = offs[5];
     }
     // windowed kernels for other stencils (the kernels that read several FP64 vectors per

@@ -296,6 +296,7 @@ struct Dia {
     bool symoff = false;        // the offsets are -k..k-symmetric and include 0
     // 7-point marching kernels: offsets -a, -b, -1, 0, 1, b, a; march_a == 0: not used
     int march_a = 0, march_b = 0;
+    double omega = 0.0;         // damped Jacobi's factor (marching kernels; 0: another smoother)
     WinPlan win;                // windowed kernels for other stencils (ncl == 0: not used)
     double* val = nullptr;      // FP64 values (Krylov operator and FP64 V-cycle)
     float* val32 = nullptr;     // FP32 values (mixed-precision V-cycle)
