@@ -338,6 +338,10 @@ void launch_c16_fill(const Csr& A, const int32_t* cblk, uint16_t* c16, hipStream
 
 // Workgroups of the 7-point marching kernels for n rows with plane stride a.
 int march_blocks(int n, int a);
+// y = A x on the marching storage; dots 1: with partials of w.y, 2: and of y.y (regions P_RZ
+// and P_RZOLD; returns their count).
+int launch_march_spmv(int n, const Dia& D, const double* x, double* y, const double* w, int dots, const RedScratch& rs,
+                      hipStream_t s);
 // Window plan for the sorted offsets (clusters split at gaps wider than a workgroup), or
 // ncl = 0 when they need more clusters or LDS than the windowed kernels have.
 WinPlan win_plan(const std::vector<int>& offs);
@@ -347,20 +351,24 @@ WinPlan win_plan(const std::vector<int>& offs);
 // partials of the kernel before), so a step runs with one host round trip: the update
 // copies the slots and the r.r partials to the host mirror (host[0..nb) partials,
 // host[2 RED_BLOCKS + k] slot k).
-enum BiScal { BS_RHO = 0, BS_ALPHA = 1, BS_OMEGA = 2, BS_BETA = 3, BS_HALF = 4, BS_BAD = 5, BS_COUNT = 8 };
-// launch_bi_scal stages: RESET (rho = value, alpha = omega = 1, flags cleared); BETA (from
-// the r^.r partials: beta, then rho); ALPHA (from r^.v: alpha = rho / r^.v); HALF (from s.s:
-// the half step has converged when ||s|| <= tol); OMEGA (from t.s and t.t: omega)
-enum BiStage { BI_RESET = 0, BI_BETA = 1, BI_ALPHA = 2, BI_HALF = 3, BI_OMEGA = 4 };
+enum BiScal {
+    BS_RHO = 0, BS_ALPHA = 1, BS_OMEGA = 2, BS_BETA = 3, BS_HALF = 4, BS_BAD = 5, BS_RHO_NEW = 6, BS_COUNT = 8
+};
+// launch_bi_scal stages: RESET (rho = value, alpha = omega = 1, flags cleared); ALPHA (from
+// r^.v, nb partials: alpha = rho / r^.v); OMEGA (from t.s and t.t, nb partials each in part
+// and part2: omega; and from s.s, nb3 partials in part3: the half step has converged when
+// ||s|| <= tol).  beta and the new rho come from the direction kernel.
+enum BiStage { BI_RESET = 0, BI_ALPHA = 1, BI_OMEGA = 2 };
 // BS_BAD bits: a zero or non-finite r^.r, r^.v, t.t or omega
 enum BiBad { BI_BAD_RHO = 1, BI_BAD_RV = 2, BI_BAD_TT = 4, BI_BAD_OMEGA = 8 };
 int bi_grid(int64_t n);
 void launch_bi_residual(int64_t n, const double* f, const double* y, double* r, double* part, int nb, hipStream_t s);
 void launch_bi_dots(int64_t n, const double* a, const double* b, const double* c, const double* d, double* part,
                     int nb, hipStream_t s);
-void launch_bi_scal(int stage, double* sc, const double* part, int nb, double value, double tol, hipStream_t s);
-void launch_bi_direction(int64_t n, const double* r, const double* v, const double* sc, int first, double* p,
-                         hipStream_t s);
+void launch_bi_scal(int stage, double* sc, const double* part, const double* part2, int nb, const double* part3,
+                    int nb3, double value, double tol, hipStream_t s);
+void launch_bi_direction(int64_t n, const double* r, const double* v, double* sc, const double* part, int nb, int first,
+                         double* p, hipStream_t s);
 void launch_bi_half(int64_t n, const double* r, const double* v, const double* sc, double* sv, double* part, int nb,
                     hipStream_t s);
 void launch_bi_update(int64_t n, const double* ph, const double* sh, const double* sv, const double* t,

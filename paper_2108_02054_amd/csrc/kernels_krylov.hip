@@ -4,9 +4,10 @@
 // V-cycle; these kernels do the vector updates, the dot products and the step's scalars.
 // Every dot product is reduced deterministically: a bounded grid, each thread adding its
 // entries in index order, a fixed wavefront and workgroup tree, one partial per workgroup;
-// a one-workgroup kernel adds the partials in a fixed order into the scalars the next
-// kernels read (alpha, omega, beta), and only the ||r||^2 partials, the flags and the
-// scalars of the step reach the host, through mapped host memory, once per step.
+// they are added in a fixed order into the scalars the next kernels read (alpha, omega,
+// beta) by a one-workgroup kernel, or for beta by every workgroup of the kernel that uses it;
+// only the ||r||^2 partials, the flags and the scalars of the step reach the host, through
+// mapped host memory, once per step.
 #include "amg_internal.h"
 
 namespace amgmi {
@@ -98,14 +99,18 @@ __device__ __forceinline__ double kblock_sum(const double* __restrict__ p, int n
     return s;
 }
 
-// The scalars of one BiCGStab step, formed on the device from the partials of the kernel
-// before (one workgroup), so that the step runs with no host round trip; see BiScal.
+__device__ __forceinline__ bool bi_bad(double x) { return x == 0.0 || !isfinite(x); }
+
+// The scalars of one BiCGStab step, formed on the device from the partials of the kernels
+// before (one workgroup), so that the step runs with no host round trip; see BiScal.  part2:
+// the second product's partials, nb2 of part3: BI_OMEGA's s.s.
 __global__ __launch_bounds__(KT) void k_bi_scal(int stage, double* __restrict__ sc, const double* __restrict__ part,
-                                                 int nb, double value, double tol) {
-    auto bad = [&](double x) { return x == 0.0 || !isfinite(x); };
+                                                 const double* __restrict__ part2, int nb,
+                                                 const double* __restrict__ part3, int nb3, double value,
+                                                 double tol) {
     if (stage == BI_RESET) {
         if (threadIdx.x == 0) {
-            sc[BS_RHO] = value;
+            sc[BS_RHO] = sc[BS_RHO_NEW] = value;
             sc[BS_ALPHA] = sc[BS_OMEGA] = 1.0;
             sc[BS_BETA] = 0.0;
             sc[BS_HALF] = 0.0;
@@ -114,32 +119,43 @@ __global__ __launch_bounds__(KT) void k_bi_scal(int stage, double* __restrict__ 
         return;
     }
     const double a = kblock_sum(part, nb);
-    const double b = stage == BI_OMEGA ? kblock_sum(part + nb, nb) : 0.0;
+    const double b = stage == BI_OMEGA ? kblock_sum(part2, nb) : 0.0;
+    const double c = stage == BI_OMEGA ? kblock_sum(part3, nb3) : 0.0;
     if (threadIdx.x != 0) return;
     int flags = (int)sc[BS_BAD];
-    if (stage == BI_BETA) {  // a = r^.r of the new residual
-        if (bad(a)) flags |= BI_BAD_RHO;
-        sc[BS_BETA] = (a / sc[BS_RHO]) * (sc[BS_ALPHA] / sc[BS_OMEGA]);
-        sc[BS_RHO] = a;
-    } else if (stage == BI_ALPHA) {  // a = r^.v
-        if (bad(a)) flags |= BI_BAD_RV;
-        sc[BS_ALPHA] = sc[BS_RHO] / a;
-    } else if (stage == BI_HALF) {  // a = s.s; tol = rtol ||f||
-        sc[BS_HALF] = sqrt(a) <= tol ? 1.0 : 0.0;
-    } else if (stage == BI_OMEGA) {  // a = t.s, b = t.t
-        if (bad(b)) flags |= BI_BAD_TT;
+    if (stage == BI_ALPHA) {  // a = r^.v; the rho that the direction kernel left
+        const double rho = sc[BS_RHO_NEW];
+        if (bi_bad(a)) flags |= BI_BAD_RV;
+        sc[BS_RHO] = rho;
+        sc[BS_ALPHA] = rho / a;
+    } else if (stage == BI_OMEGA) {  // a = t.s, b = t.t; c = s.s, tol = rtol ||f||
+        sc[BS_HALF] = sqrt(c) <= tol ? 1.0 : 0.0;
+        if (bi_bad(b)) flags |= BI_BAD_TT;
         const double w = a / b;
-        if (bad(w)) flags |= BI_BAD_OMEGA;
+        if (bi_bad(w)) flags |= BI_BAD_OMEGA;
         sc[BS_OMEGA] = w;
     }
     sc[BS_BAD] = (double)flags;
 }
 
-// p = r (first step) or p = r + beta (p - omega v)
+// p = r (first step) or p = r + beta (p - omega v), beta = (rho_new / rho) (alpha / omega)
+// from the nb partials of rho_new = r^.r.  Workgroup 0 keeps rho_new for the alpha that
+// follows (in a slot of its own: the others read rho).
 __global__ __launch_bounds__(KT) void k_bi_direction(int64_t n, const double* __restrict__ r,
-                                                      const double* __restrict__ v, const double* __restrict__ sc,
-                                                      int first, double* __restrict__ p) {
-    const double beta = sc[BS_BETA], omega = sc[BS_OMEGA];
+                                                      const double* __restrict__ v, double* __restrict__ sc,
+                                                      const double* __restrict__ part, int nb, int first,
+                                                      double* __restrict__ p) {
+    double beta = 0.0;
+    const double omega = sc[BS_OMEGA];
+    if (!first) {
+        const double a = kblock_sum(part, nb);
+        beta = (a / sc[BS_RHO]) * (sc[BS_ALPHA] / omega);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if (bi_bad(a)) sc[BS_BAD] = (double)((int)sc[BS_BAD] | BI_BAD_RHO);
+            sc[BS_BETA] = beta;
+            sc[BS_RHO_NEW] = a;
+        }
+    }
     for (int64_t i = blockIdx.x * (int64_t)KT + threadIdx.x; i < n; i += (int64_t)gridDim.x * KT)
         p[i] = first ? r[i] : r[i] + beta * (p[i] - omega * v[i]);
 }
@@ -204,11 +220,6 @@ __global__ __launch_bounds__(KT) void k_bi_update(int64_t n, const double* __res
     }
 }
 
-inline unsigned vec_blocks(int64_t n) {
-    const int64_t b = (n + KT - 1) / KT;
-    return (unsigned)(b < 1 ? 1 : (b > 4096 ? 4096 : b));
-}
-
 }  // namespace
 
 int bi_grid(int64_t n) { return red_grid_elems(n); }
@@ -222,13 +233,14 @@ void launch_bi_dots(int64_t n, const double* a, const double* b, const double* c
     k_bi_dots<<<nb, KT, 0, s>>>(n, a, b, c, d, part);
     HIP_LAUNCH_CHECK();
 }
-void launch_bi_scal(int stage, double* sc, const double* part, int nb, double value, double tol, hipStream_t s) {
-    k_bi_scal<<<1, KT, 0, s>>>(stage, sc, part, nb, value, tol);
+void launch_bi_scal(int stage, double* sc, const double* part, const double* part2, int nb, const double* part3,
+                    int nb3, double value, double tol, hipStream_t s) {
+    k_bi_scal<<<1, KT, 0, s>>>(stage, sc, part, part2, nb, part3, nb3, value, tol);
     HIP_LAUNCH_CHECK();
 }
-void launch_bi_direction(int64_t n, const double* r, const double* v, const double* sc, int first, double* p,
-                         hipStream_t s) {
-    k_bi_direction<<<vec_blocks(n), KT, 0, s>>>(n, r, v, sc, first, p);
+void launch_bi_direction(int64_t n, const double* r, const double* v, double* sc, const double* part, int nb, int first,
+                         double* p, hipStream_t s) {
+    k_bi_direction<<<bi_grid(n), KT, 0, s>>>(n, r, v, sc, part, nb, first, p);
     HIP_LAUNCH_CHECK();
 }
 void launch_bi_half(int64_t n, const double* r, const double* v, const double* sc, double* sv, double* part, int nb,

@@ -1175,6 +1175,23 @@ __global__ __launch_bounds__(TPB) void k_m7_jacobi_rz32(int n, int a, int b, con
     block_store<2>(loc, dst, xcd_block());
 }
 
+// y = A x; K > 0: partials of w.y, K > 1: and of y.y
+template <bool SYM, int K>
+__global__ __launch_bounds__(TPB) void k_m7_spmv(int n, int a, int b, const double* __restrict__ v,
+                                                 const double* __restrict__ x, double* __restrict__ y,
+                                                 const double* __restrict__ w, RedScratch rs) {
+    double loc[2] = {0.0, 0.0};
+    march7<SYM, double>(n, a, b, v, [&](int j) { return x[j]; }, [&](int i, double s, double) {
+        y[i] = s;
+        if constexpr (K > 0) loc[0] += w[i] * s;
+        if constexpr (K > 1) loc[1] += s * s;
+    });
+    if constexpr (K > 0) {
+        double* const dst[2] = {rs.region(P_RZ), rs.region(P_RZOLD)};
+        block_store<2>(loc, dst, xcd_block());
+    }
+}
+
 template <bool SYM, bool FIRST>
 __global__ __launch_bounds__(TPB) void k_m7_cg_pq(int n, int a, int b, const double* __restrict__ v,
                                                   const double* __restrict__ z, const double* __restrict__ pold,
@@ -1754,6 +1771,25 @@ int launch_dia_jacobi_rz32(int n, const Dia& D, const float* m, const float* f, 
         return nbw;
     }
     return 0;
+}
+int launch_march_spmv(int n, const Dia& D, const double* x, double* y, const double* w, int dots, const RedScratch& rs,
+                      hipStream_t s) {
+    const int nb = march_blocks(n, D.march_a);
+    if (dots > 0 && nb > rs.cap) throw Fail{AMG_ERR_ARG, "reduction scratch too small"};
+    march_call(D, [&](auto S) {
+        constexpr bool SYM = decltype(S)::value;
+        auto go = [&](auto kern) {
+            timed_launch(kern, nb, TPB, 0, s, n, D.march_a, D.march_b, (const double*)D.val, x, y, w, rs);
+        };
+        if (dots == 0)
+            go(k_m7_spmv<SYM, 0>);
+        else if (dots == 1)
+            go(k_m7_spmv<SYM, 1>);
+        else
+            go(k_m7_spmv<SYM, 2>);
+    });
+    HIP_LAUNCH_CHECK();
+    return nb;
 }
 int launch_dia_cg_pq(int n, const Dia& D, const double* z, const double* pold, double* pnew, double* q, int first,
                      const RedScratch& rs, hipStream_t s) {
