@@ -364,46 +364,110 @@ void symbolic_fill(const Csr& A, const Csr& B, const Csr& C, const GalShape& gs,
 // quadratic: such a matrix is sorted as a whole.
 
 constexpr int TR_ROW_MAX = 2048;
+constexpr int64_t TR_LANES_MIN = 1 << 17;
+
+// The rows of a workgroup name few different columns (neighbouring fine rows belong to the
+// same aggregates), and one atomic per entry on a column's counter is what these two passes
+// waited for: the workgroup meets its columns in a table in LDS and adds its share of each
+// with one atomic (128^3 smoothed P,
+// 7.2 M entries: count 211 -> 85 us, scatter 295 -> 99 us).  A column finds its place
+// within TR_PROBE slots of its hash or, all of them being taken for good, stays outside the
+// table, for every thread alike.
+constexpr int TR_H = 1024, TR_PROBE = 16;
+
+__device__ __forceinline__ int tr_slot(int* key, int J) {
+    const unsigned h = ((unsigned)J * 2654435761u) >> 22;
+    for (int p = 0; p < TR_PROBE; ++p) {
+        const int q = (int)((h + p) & (TR_H - 1));
+        const int old = atomicCAS(&key[q], -1, J);
+        if (old == -1 || old == J) return q;
+    }
+    return -1;
+}
+static_assert(TR_H == 1 << 10, "the hash keeps ten bits");
+
+__device__ __forceinline__ void tr_clear(int* key, int* num) {
+    for (int q = threadIdx.x; q < TR_H; q += TPB) {
+        key[q] = -1;
+        num[q] = 0;
+    }
+    __syncthreads();
+}
 
 __global__ __launch_bounds__(TPB) void k_tr_count(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                                                   int* __restrict__ cnt) {
+    __shared__ int key[TR_H], num[TR_H];
+    tr_clear(key, num);
     const int i = xcd_block() * TPB + threadIdx.x;
-    if (i >= n) return;
-    for (int k = ptr[i]; k < ptr[i + 1]; ++k) atomicAdd(&cnt[col[k]], 1);
+    const int k0 = i < n ? ptr[i] : 0, k1 = i < n ? ptr[i + 1] : 0;
+    for (int k = k0; k < k1; ++k) {
+        const int J = col[k], q = tr_slot(key, J);
+        atomicAdd(q >= 0 ? &num[q] : &cnt[J], 1);
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < TR_H; q += TPB)
+        if (num[q] > 0) atomicAdd(&cnt[key[q]], num[q]);
 }
 
 // cnt holds each column's count and counts down to its first place.
 __global__ __launch_bounds__(TPB) void k_tr_scatter(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                                                     const int* __restrict__ Rptr, int* __restrict__ cnt,
                                                     int2* __restrict__ tmp) {
+    __shared__ int key[TR_H], num[TR_H];
+    tr_clear(key, num);
     const int i = xcd_block() * TPB + threadIdx.x;
-    if (i >= n) return;
-    for (int k = ptr[i]; k < ptr[i + 1]; ++k) {
-        const int J = col[k];
-        tmp[Rptr[J] + atomicSub(&cnt[J], 1) - 1] = make_int2(i, k);
+    const int k0 = i < n ? ptr[i] : 0, k1 = i < n ? ptr[i + 1] : 0;
+    for (int k = k0; k < k1; ++k) {
+        const int q = tr_slot(key, col[k]);
+        if (q >= 0) atomicAdd(&num[q], 1);
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < TR_H; q += TPB)  // num: from the count to the first place
+        if (num[q] > 0) num[q] = Rptr[key[q]] + atomicSub(&cnt[key[q]], num[q]) - num[q];
+    __syncthreads();
+    for (int k = k0; k < k1; ++k) {
+        const int J = col[k], q = tr_slot(key, J);
+        tmp[q >= 0 ? atomicAdd(&num[q], 1) : Rptr[J] + atomicSub(&cnt[J], 1) - 1] = make_int2(i, k);
     }
 }
+
+// Puts each row of R in order by the rank of its row indices: a group of G lanes per row
+// stages them in LDS (at most TR_KEYS G of them) and every lane counts, for two of its own at
+// a time, the smaller ones, four per LDS read (27-point 72x61x50: 174 -> 32 us on level
+// 0, 104 -> 6 on the 496 rows of level 1, against a shuffle per comparison).
+constexpr int TR_KEYS = TR_ROW_MAX / TPB;
 
 template <int G>
 __global__ __launch_bounds__(TPB) void k_tr_order(int nc, const int* __restrict__ Rptr, const int2* __restrict__ tmp,
                                                   const double* __restrict__ v, int* __restrict__ Rcol,
                                                   double* __restrict__ Rval) {
+    __shared__ __align__(16) int keys[TPB / G][TR_KEYS * G];
     const int lane = threadIdx.x & (G - 1);
     const int row = (xcd_block() * TPB + (int)threadIdx.x) / G;
-    if (row >= nc) return;
-    const int b = Rptr[row], u = Rptr[row + 1] - b;
-    for (int x0 = 0; x0 < u; x0 += G) {
-        const int x = x0 + lane;
-        const int2 t = x < u ? tmp[b + x] : make_int2(-1, 0);
-        int r = 0;
-        for (int y0 = 0; y0 < u; y0 += G) {
-            const int w = y0 + lane < u ? tmp[b + y0 + lane].x : 0x7fffffff;
-            const int ny = min(G, u - y0);
-            for (int k = 0; k < ny; ++k) r += __shfl(w, k, G) < t.x;
+    int* mine = keys[threadIdx.x / G];
+    const int b = row < nc ? Rptr[row] : 0, u = row < nc ? Rptr[row + 1] - b : 0;
+    for (int x = lane; x < ((u + 3) & ~3); x += G) mine[x] = x < u ? tmp[b + x].x : 0x7fffffff;
+    if constexpr (G > 64) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    for (int x = lane; x < u; x += 2 * G) {
+        const int x2 = x + G < u ? x + G : x;
+        const int t1 = mine[x], t2 = mine[x2];
+        int r1 = 0, r2 = 0;
+        for (int y = 0; y < u; y += 4) {
+            const int4 w = *reinterpret_cast<const int4*>(mine + y);
+            r1 += (w.x < t1) + (w.y < t1) + (w.z < t1) + (w.w < t1);
+            r2 += (w.x < t2) + (w.y < t2) + (w.z < t2) + (w.w < t2);
         }
-        if (x < u) {
-            Rcol[b + r] = t.x;
-            Rval[b + r] = v[t.y];
+        Rcol[b + r1] = t1;
+        Rval[b + r1] = v[tmp[b + x].y];
+        if (x2 != x) {
+            Rcol[b + r2] = t2;
+            Rval[b + r2] = v[tmp[b + x2].y];
         }
     }
 }
@@ -448,10 +512,24 @@ void build_transpose(const Csr& P, Csr& R, hipStream_t s) {
     }
     int2* tmp = dnew<int2>((size_t)nnz, s);
     k_tr_scatter<<<nb, TPB, 0, s>>>(P.nrows, P.ptr, P.col, R.ptr, cnt, tmp);
+    // lanes per row: about half its entries, enough LDS for the longest, and with few rows
+    // more, so that the long rows of a small level don't leave the chip to a few wavefronts
     const double mean = R.nrows > 0 ? (double)nnz / R.nrows : 0.0;
-    const int g = mean <= 12.0 ? 8 : mean <= 24.0 ? 16 : 32;
-    AMG_WITH_SYM_G(g, (k_tr_order<G><<<(unsigned)std::max<int64_t>(1, ((int64_t)R.nrows * G + TPB - 1) / TPB), TPB, 0,
-                                       s>>>(R.nrows, R.ptr, tmp, P.val, R.col, R.val)));
+    int g = mean <= 12.0 ? 8 : mean <= 24.0 ? 16 : 32;
+    while (g < TPB && (TR_KEYS * g < longest || (int64_t)R.nrows * g < TR_LANES_MIN)) g <<= 1;
+    auto order = [&](auto G) {
+        constexpr int W = decltype(G)::value;
+        k_tr_order<W><<<(unsigned)std::max<int64_t>(1, ((int64_t)R.nrows * W + TPB - 1) / TPB), TPB, 0, s>>>(
+            R.nrows, R.ptr, tmp, P.val, R.col, R.val);
+    };
+    switch (g) {
+        case 8: order(std::integral_constant<int, 8>{}); break;
+        case 16: order(std::integral_constant<int, 16>{}); break;
+        case 32: order(std::integral_constant<int, 32>{}); break;
+        case 64: order(std::integral_constant<int, 64>{}); break;
+        case 128: order(std::integral_constant<int, 128>{}); break;
+        default: order(std::integral_constant<int, 256>{}); break;
+    }
     HIP_LAUNCH_CHECK();
     dfree(cnt, s);
     dfree(tmp, s);
@@ -460,11 +538,12 @@ void build_transpose(const Csr& P, Csr& R, hipStream_t s) {
 // ------------------------------------------------------------------ launch shapes
 
 // most[b] is raised to the largest number of entries in 2^b consecutive rows (aligned at
-// multiples of 2^b), for b = 0 .. 8.
+// multiples of 2^b), for b = 0 .. 8.  (A thread per maximum: one thread raising them one after
+// the other waited 25 to 55 us for memory, 5 to 20 now.)
 static_assert(RB_THREADS == 256, "one workgroup reads the rows of the largest block");
 __global__ __launch_bounds__(TPB) void k_row_blocks(int n, const int* __restrict__ ptr, int* __restrict__ most) {
     __shared__ int sp[RB_THREADS + 1];
-    __shared__ int sm[TPB / 64];
+    __shared__ int sm[TPB / 64][ROW_BLOCK_SIZES];
     int w[ROW_BLOCK_SIZES] = {};
     const int nblk = (n + RB_THREADS - 1) / RB_THREADS;
     for (int k = blockIdx.x; k < nblk; k += gridDim.x) {
@@ -476,17 +555,18 @@ __global__ __launch_bounds__(TPB) void k_row_blocks(int n, const int* __restrict
             if ((int)threadIdx.x < (RB_THREADS >> b)) w[b] = max(w[b], sp[(threadIdx.x + 1) << b] - sp[threadIdx.x << b]);
         __syncthreads();
     }
+#pragma unroll
     for (int b = 0; b < ROW_BLOCK_SIZES; ++b) {
         int v = w[b];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-        if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            for (int k = 1; k < TPB / 64; ++k) v = max(v, sm[k]);
-            raise_max(&most[b], v);
-        }
-        __syncthreads();
+        if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6][b] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < ROW_BLOCK_SIZES) {  // side by side: each waits for memory on its own
+        int v = sm[0][threadIdx.x];
+        for (int k = 1; k < TPB / 64; ++k) v = max(v, sm[k][threadIdx.x]);
+        raise_max(&most[threadIdx.x], v);
     }
 }
 

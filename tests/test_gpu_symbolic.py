@@ -158,3 +158,31 @@ def test_v_cycle_of_long_restriction_rows():
     # condition of the coarse operator below 1e4: its solve is good to 1e4 eps
     assert rel_max(g.vcycle(T(f)).cpu().numpy(), u) <= 1e-10
     g.close()
+
+
+@pytest.mark.parametrize("n,nc,per_row", [
+    (5000, 4000, 2),    # rows of R of a few entries
+    (20000, 300, 1),    # ... of about 70, in more rows than lanes are short of
+    (4000, 40, 6),      # ... of hundreds, in few rows
+    (2400, 5, 4),       # ... up to the longest that is ranked
+    (3000, 1500, 30),   # more distinct columns under a workgroup than its table holds
+    (255, 70, 3), (257, 33, 5)])
+def test_transpose_by_ranks(n, nc, per_row):
+    """R = P^T through the product that reads it: pattern exact, values to rounding."""
+    from paper_2108_02054_amd import AMG
+    A = spd_from(n, np.arange(n - 1), np.arange(1, n), 6)
+    P = transfer(n, nc, per_row, 21, empty=2)
+    P2 = transfer(nc, min(nc, 30), 1, 22)
+    print(f"case transpose n={n} nc={nc} longest row of R {np.bincount(P.indices).max()}", flush=True)
+    args = [(T(M.indptr.astype(np.int32)), T(M.indices.astype(np.int32)), T(M.data), M.shape[1]) for M in (P, P2)]
+    g = AMG(T(A.indptr.astype(np.int32)), T(A.indices.astype(np.int32)), T(A.data), transfer=args)
+    one = lambda M: sp.csr_matrix((np.ones(M.nnz), M.indices, M.indptr), shape=M.shape)  # noqa: E731
+    S = (one(P).T @ one(A) @ one(P)).tocsr()
+    S.sort_indices()
+    C = (P.T @ A @ P).tocsr()
+    got = g.level(1)["A"]
+    assert np.array_equal(got[0], S.indptr) and np.array_equal(got[1], S.indices)
+    D = sp.csr_matrix((got[2], got[1], got[0]), shape=C.shape)
+    # at most 2400 * 3 products per entry, rounded one by one
+    assert abs(D - C).max() <= 1e-12 * abs(C).max()
+    g.close()
