@@ -160,18 +160,54 @@ __global__ void k_mis_init(int n, const uint8_t* __restrict__ isolated, uint8_t*
     c1[i] = 0;
 }
 
+// The round's kernels take G lanes per row: one where rows are short (most rows of a round
+// return at once; four lanes on 128^3 7-point rows 35 -> 58 us), and where they are long
+// enough to be a serial chain of reads 8, or 32 on the small levels that leave the chip idle
+// (27-point 72x61x50, rows of 27 and 64 entries: the rounds of both levels 767 -> 338 us).
+template <int G>
+__device__ __forceinline__ uint64_t group_max(uint64_t v) {
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) {
+        const uint64_t w = (uint64_t)__shfl_xor((unsigned long long)v, o, G);
+        v = w > v ? w : v;
+    }
+    return v;
+}
+template <typename F>
+void with_round_lanes(const Csr& A, F f) {
+    const double mean = A.nrows > 0 ? (double)A.nnz / (double)A.nrows : 1.0;
+    if (mean < 12.0)
+        f(std::integral_constant<int, 1>{});
+    else if (A.nrows >= 65536)
+        f(std::integral_constant<int, 8>{});
+    else
+        f(std::integral_constant<int, 32>{});
+}
+template <int G>
+struct RowLanes {
+    int i, lane;
+    __device__ __forceinline__ RowLanes() {
+        const int t = xcd_block() * TPB + (int)threadIdx.x;
+        i = t / G;
+        lane = t & (G - 1);
+    }
+};
+
 // m1[i] = max priority of an undecided node among i and its strong neighbours (0: none, and
 // then none in any later round either: the row is not read again, which leaves a few rounds'
 // worth of work in six or seven).
-__global__ void k_mis_max1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+template <int G>
+__global__ __launch_bounds__(TPB) void k_mis_max1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                            const uint8_t* __restrict__ strong, const uint8_t* __restrict__ state,
                            uint64_t* __restrict__ m1,
                            const int* __restrict__ go) {
     if (go != nullptr && *go == 0) return;
-    const int i = xcd_block() * TPB + threadIdx.x;
+    const RowLanes<G> t;
+    const int i = t.i;
     if (i >= n || m1[i] == 0) return;
     uint64_t m = state[i] == ST_UNDECIDED ? mix64((uint64_t)i) : 0;
-    for (int k = ptr[i]; k < ptr[i + 1]; ++k) {
+    const int e = ptr[i + 1];
+    for (int k = ptr[i] + t.lane; k < e; k += G) {
         if (!strong[k]) continue;
         const int j = col[k];
         if (state[j] == ST_UNDECIDED) {
@@ -179,55 +215,68 @@ __global__ void k_mis_max1(int n, const int* __restrict__ ptr, const int* __rest
             m = p > m ? p : m;
         }
     }
-    m1[i] = m;
+    m = group_max<G>(m);
+    if (t.lane == 0) m1[i] = m;
 }
 
 // An undecided node whose priority is the largest among undecided nodes within strong
 // distance 2 becomes a root.  (Repeating this round by round yields exactly the set a
 // sequential greedy pass in decreasing priority order builds: every node of higher
 // priority nearby has been decided before.)
-__global__ void k_mis_max2(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+template <int G>
+__global__ __launch_bounds__(TPB) void k_mis_max2(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                            const uint8_t* __restrict__ strong, const uint64_t* __restrict__ m1,
                            uint8_t* __restrict__ state,
                            const int* __restrict__ go) {
     if (go != nullptr && *go == 0) return;
-    const int i = xcd_block() * TPB + threadIdx.x;
+    const RowLanes<G> t;
+    const int i = t.i;
     if (i >= n || state[i] != ST_UNDECIDED) return;
     uint64_t m = m1[i];
-    for (int k = ptr[i]; k < ptr[i + 1]; ++k) {
+    const int e = ptr[i + 1];
+    for (int k = ptr[i] + t.lane; k < e; k += G) {
         if (!strong[k]) continue;
         const uint64_t p = m1[col[k]];
         m = p > m ? p : m;
     }
-    if (m == mix64((uint64_t)i)) state[i] = ST_ROOT;
+    m = group_max<G>(m);
+    if (t.lane == 0 && m == mix64((uint64_t)i)) state[i] = ST_ROOT;
 }
 
 // c1[i] = i is a root or has a strong root neighbour: a new root (a root outside c1, since a
 // node next to an earlier one has been removed) marks itself and its neighbours; strength is
 // symmetric, and no other root is near enough to write the same marks.
-__global__ void k_mis_cover1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+template <int G>
+__global__ __launch_bounds__(TPB) void k_mis_cover1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                              const uint8_t* __restrict__ strong, const uint8_t* __restrict__ state,
                              uint8_t* __restrict__ c1, const int* __restrict__ go) {
     if (go != nullptr && *go == 0) return;
-    const int i = xcd_block() * TPB + threadIdx.x;
-    if (i >= n || state[i] != ST_ROOT || c1[i]) return;
-    c1[i] = 1;
-    for (int k = ptr[i]; k < ptr[i + 1]; ++k)
+    const RowLanes<G> t;
+    const int i = t.i;
+    if (i >= n || state[i] != ST_ROOT || c1[i]) return;  // (a group's lanes read before one writes)
+    if (t.lane == 0) c1[i] = 1;
+    const int e = ptr[i + 1];
+    for (int k = ptr[i] + t.lane; k < e; k += G)
         if (strong[k]) c1[col[k]] = 1;
 }
 
 // Undecided nodes within strong distance 2 of a root are removed; any node still
 // undecided raises the flag for another round.
-__global__ void k_mis_cover2(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+template <int G>
+__global__ __launch_bounds__(TPB) void k_mis_cover2(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                              const uint8_t* __restrict__ strong, const uint8_t* __restrict__ c1,
                              uint8_t* __restrict__ state, int* __restrict__ left,
                              const int* __restrict__ go) {
     if (go != nullptr && *go == 0) return;
-    const int i = xcd_block() * TPB + threadIdx.x;
+    const RowLanes<G> t;
+    const int i = t.i;
     if (i >= n || state[i] != ST_UNDECIDED) return;
-    bool c = c1[i] != 0;
-    for (int k = ptr[i]; k < ptr[i + 1] && !c; ++k)
-        if (strong[k] && c1[col[k]]) c = true;
+    uint64_t c = c1[i];
+    const int e = ptr[i + 1];
+    for (int k = ptr[i] + t.lane; k < e && !c; k += G)
+        if (strong[k] && c1[col[k]]) c = 1;
+    c = group_max<G>(c);
+    if (t.lane != 0) return;
     if (c)
         state[i] = ST_REMOVED;
     else
@@ -250,13 +299,17 @@ void run_mis2(const Csr& A, const uint8_t* strong, const uint8_t* isolated, uint
     int h_left = 0;
     for (int round = 0;; round += MIS_BATCH) {
         HIP_CHECK(hipMemsetAsync(left, 0, MIS_BATCH * sizeof(int), s));
-        for (int r = 0; r < MIS_BATCH; ++r) {
-            const int* go = r == 0 ? nullptr : left + r - 1;
-            k_mis_max1<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, m1, go);
-            k_mis_max2<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, m1, state, go);
-            k_mis_cover1<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, c1, go);
-            k_mis_cover2<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, c1, state, left + r, go);
-        }
+        with_round_lanes(A, [&](auto L) {
+            constexpr int G = decltype(L)::value;
+            const unsigned nbg = blocks_for((int64_t)n * G);
+            for (int r = 0; r < MIS_BATCH; ++r) {
+                const int* go = r == 0 ? nullptr : left + r - 1;
+                k_mis_max1<G><<<nbg, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, m1, go);
+                k_mis_max2<G><<<nbg, TPB, 0, s>>>(n, A.ptr, A.col, strong, m1, state, go);
+                k_mis_cover1<G><<<nbg, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, c1, go);
+                k_mis_cover2<G><<<nbg, TPB, 0, s>>>(n, A.ptr, A.col, strong, c1, state, left + r, go);
+            }
+        });
         HIP_LAUNCH_CHECK();
         HIP_CHECK(hipMemcpyAsync(&h_left, left + MIS_BATCH - 1, sizeof(int), hipMemcpyDeviceToHost, s));
         HIP_CHECK(hipStreamSynchronize(s));
@@ -272,19 +325,23 @@ void run_mis2(const Csr& A, const uint8_t* strong, const uint8_t* isolated, uint
 
 // Pass 1: roots and their strong neighbours take the root's id (roots are at least 3
 // apart, so at most one root is adjacent).
-__global__ void k_agg_pass1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
+template <int G>
+__global__ __launch_bounds__(TPB) void k_agg_pass1(int n, const int* __restrict__ ptr, const int* __restrict__ col,
                             const uint8_t* __restrict__ strong, const uint8_t* __restrict__ state,
                             const int* __restrict__ root_id, int* __restrict__ agg1) {
-    const int i = xcd_block() * TPB + threadIdx.x;
+    const RowLanes<G> t;
+    const int i = t.i;
     if (i >= n) return;
-    int a = -1;
+    uint64_t a = 0;  // id + 1
     if (state[i] == ST_ROOT) {
-        a = root_id[i];
+        a = (uint64_t)root_id[i] + 1;
     } else if (state[i] != ST_ISOLATED) {
-        for (int k = ptr[i]; k < ptr[i + 1]; ++k)
-            if (strong[k] && state[col[k]] == ST_ROOT) a = root_id[col[k]];
+        const int e = ptr[i + 1];
+        for (int k = ptr[i] + t.lane; k < e; k += G)
+            if (strong[k] && state[col[k]] == ST_ROOT) a = (uint64_t)root_id[col[k]] + 1;
     }
-    agg1[i] = a;
+    a = group_max<G>(a);
+    if (t.lane == 0) agg1[i] = (int)a - 1;
 }
 
 // Pass 2: a node left over joins the pass-1 aggregate of its strong neighbour j with the
@@ -358,7 +415,10 @@ int32_t run_aggregate(const Csr& A, const uint8_t* strong, const int32_t* tpos, 
     HIP_LAUNCH_CHECK();
     HIP_CHECK(hipMemsetAsync(isr + n, 0, sizeof(int), s));
     scan_exclusive<int, int>(isr, id, n + 1, s);
-    k_agg_pass1<<<nb, TPB, 0, s>>>(n, A.ptr, A.col, strong, state, id, agg1);
+    with_round_lanes(A, [&](auto L) {
+        constexpr int G = decltype(L)::value;
+        k_agg_pass1<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, A.col, strong, state, id, agg1);
+    });
     AMG_ROW_LANES(A, (k_agg_pass2<G><<<blocks_for((int64_t)n * G), TPB, 0, s>>>(n, A.ptr, A.col, A.val, strong, tpos,
                                                                               state, agg1, agg, flags)));
     HIP_LAUNCH_CHECK();

@@ -186,3 +186,22 @@ def test_transpose_by_ranks(n, nc, per_row):
     # at most 2400 * 3 products per entry, rounded one by one
     assert abs(D - C).max() <= 1e-12 * abs(C).max()
     g.close()
+
+
+@pytest.mark.parametrize("kind,n", [("27pt", 41), ("27pt", 40), ("27pt", 19), ("7pt", 41), ("dense", 1500)])
+def test_aggregates_by_row_lanes(kind, n):
+    """MIS-2 and the aggregation passes with 8 lanes per row (68921 rows of 27 entries), 32 (as
+    many as 64000, and few long rows) and one: aggregates as the oracle's, on every level."""
+    from tests.gpu_util import both, compare_levels
+    from workloads import lognormal_27pt, two_fluid_7pt
+    if kind == "dense":
+        g = np.random.default_rng(8)
+        A = spd_from(n, g.integers(0, n, 60 * n), g.integers(0, n, 60 * n), 9)
+        p, c, v = A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data
+    else:
+        p, c, v = lognormal_27pt(n, 1) if kind == "27pt" else two_fluid_7pt(n, 0.4)
+    print(f"case row lanes {kind} {n}", flush=True)
+    g, o = both(p, c, v, coarse_enough=20)
+    compare_levels(g, o, tol=1e-10, values=False)
+    g.close()
+    o.close()
