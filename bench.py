@@ -171,7 +171,11 @@ class ByteModel:
     entry plus one 4 B base per row block when the level keeps two-byte column offsets)
     and their values (8 B FP64, 4 B FP32); an operator in diagonal storage counts its
     values only, with symmetric values only the main and upper diagonals; an operator of
-    full B x B blocks one index per block and one pointer per node (its Krylov SpMV)."""
+    full B x B blocks one index per block and one pointer per node (its Krylov SpMV).
+    post: the levels whose prolongation and post-sweep are one pass over Q_l = (I - M A) P
+    (A_l P_l's pattern), traced as "prolong" with no "jacobi" launches."""
+
+    post = frozenset()
 
     def __init__(self, dims, storage, ndiag=0, nread=0, block=1):
         self.L = len(dims)
@@ -248,7 +252,9 @@ class ByteModel:
                 return self.krylov_A() + 16 * n
             return self.krylov_A() + 32 * n      # z, p_old read; p_new, q written
         if cls == "cg_update" and l == 0:
-            if self.ndiag > 0 and s == 8:        # fused with the first sweep and its residual
+            # fused with the first sweep and its residual (the marching kernels read no m: they
+            # form damped Jacobi's from the main diagonal, and move 8 n bytes fewer)
+            if self.ndiag > 0 and s == 8:
                 return 8 * self.a0_entries() + 72 * n
             return 48 * n if s == 8 else None
         if cls == "cg_rz" and l == 0:
@@ -262,6 +268,8 @@ class ByteModel:
         if cls == "restrict" and l < last:
             smooths = (l + 2 < self.L) and not self.st[l + 1]["tail"]
             return self.R(l) + s * n + s * nc + (2 * s * nc if smooths else 0)
+        if cls == "prolong" and l in self.post:   # u + m r + Q u_c: u, m, r read, u written
+            return self._csr(n, self.dims[l][4], self.st[l]["P_c16"], self.st[l]["P_rpb"], s) + s * nc + 4 * s * n
         if cls == "prolong" and l < last:
             return self.P(l) + s * nc + 2 * s * n
         if cls == "coarse_gemv" and l == last:
@@ -284,13 +292,19 @@ def roof(name, ms, launches, alg_bytes_total, traffic_rec=None):
             "traffic_source": (f"profiles/{os.path.basename(traffic_rec['_path'])}" if traffic_rec else None)}
 
 
+def fused_levels(kt_levels):
+    """Levels whose correction and post-sweep ran as one pass (see ByteModel.post)."""
+    return frozenset(l for l, lv in enumerate(kt_levels)
+                     if lv.get("prolong", (0.0, 0))[1] and not lv.get("jacobi", (0.0, 0))[1])
+
+
 def kernel_groups(L, bm, plane, block, bicg):
     """The kernels of a step as (name, class, levels): a traced class restricted to the
     levels on which one kernel function runs it, so that times compare with a kernel
     trace's per-kernel statistics."""
     up = set(range(1, L))
     if bicg:
-        pq = "k_m7_cg_pq (BiCGStab products)" if plane else "k_rb_spmv (BiCGStab products)"
+        pq = "k_m7_spmv (BiCGStab products)" if plane else "k_rb_spmv (BiCGStab products)"
     elif plane:
         pq = "k_m7_cg_pq"
     elif bm.ndiag:
@@ -309,7 +323,8 @@ def kernel_groups(L, bm, plane, block, bicg):
          (post + " (level-0 post-sweep)", "jacobi", {0}),
          ("k_rb_jacobi" if block == 1 else "k_node_sweep / k_rb_jacobi", "jacobi", up),
          ("k_rb_residual", "smooth0_res", up), ("k_rb_spmv (restriction R_l)", "restrict", set(range(L))),
-         ("k_rb_prolong_add (prolongation P_l)", "prolong", set(range(L))),
+         ("k_rb_prolong_add (prolongation P_l)", "prolong", set(range(L)) - bm.post),
+         ("k_rb_correct (correction and post-sweep Q_l)", "prolong", set(bm.post)),
          ("k_vcycle_tail", "tail", set(range(L))), ("k_coarse_gemv", "coarse_gemv", set(range(L)))]
     return g
 
@@ -370,8 +385,9 @@ def run_config(cfg_id, N, K, W, args, headline_prec=None, compare=True, legs_mod
     u = torch.zeros(n, dtype=torch.float64, device=dev)
     spmv_cls = "bicg_spmv" if bicg else "cg_pq"
 
-    def groups_of(amg):
+    def groups_of(amg, kt_levels):
         bm_ = ByteModel.of(amg, block)
+        bm_.post = fused_levels(kt_levels)
         return kernel_groups(bm_.L, bm_, amg.march_plane(0), block, bicg)
 
     def dominant(ktl, groups):
@@ -456,7 +472,7 @@ def run_config(cfg_id, N, K, W, args, headline_prec=None, compare=True, legs_mod
             # the timed steps bracket only every TRACE_EVERY-th launch of the dominant
             # kernel class per level with events: each bracketed launch holds the stream for
             # its timestamps (tracing all launches of four classes cost 0.8 ms per 128^3 step)
-            dom = dominant(kt_levels, groups_of(amg))
+            dom = dominant(kt_levels, groups_of(amg, kt_levels))
             traced = [dom[1]]
             amg.trace(traced, level=-1, every=TRACE_EVERY)
             amg.trace_read()
@@ -509,6 +525,7 @@ def run_config(cfg_id, N, K, W, args, headline_prec=None, compare=True, legs_mod
 
     # kernel table of one partial step, per level and class
     ktl = info_p["kt_levels"]
+    bm.post = fused_levels(ktl)
     totals = {}
     for l, lv in enumerate(ktl):
         for k, (ms, cnt) in lv.items():
@@ -568,14 +585,15 @@ def run_config(cfg_id, N, K, W, args, headline_prec=None, compare=True, legs_mod
     rap_all_bytes = sum(bm.galerkin(l) * gal_cnt(l) for l in range(L - 1))
 
     if plane:
-        pq_kernel = "k_m7_cg_pq"
+        pq_kernel = "k_m7_spmv" if bicg else "k_m7_cg_pq"
     elif bm.ndiag:
         pq_kernel = "k_w_cg_pq" if bm.ndiag != 7 else "k_dia_cg_pq"
     elif block > 1:
         pq_kernel = "k_rb_spmv" if bicg else "k_node_cg_pq"
     else:
         pq_kernel = "k_rb_spmv" if bicg else "k_cg_pq"
-    first_kernel = pq_kernel if not pq_kernel.startswith("k_rb") else "k_cg_pq"
+    first_kernel = pq_kernel if pq_kernel not in ("k_rb_spmv", "k_m7_spmv") else \
+        "k_m7_cg_pq" if plane else "k_cg_pq"
     spmv_first_bytes = (bm.bytes("cg_pq", 0) - 8 * n) if not block > 1 else bm.bytes("cg_pq", 0)
 
     plain = args.aggregation == 1 and cfg_id != 7
