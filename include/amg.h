@@ -250,8 +250,8 @@ amg_status amg_level_dims(const amg_ctx* c, int l, int64_t* dims);
  * refreshed from the CSR copy after every rebuild), or 0 when the CSR kernels are used.
  * *nread (host, may be NULL) receives the number of diagonals the solve kernels read per
  * row: (ndiag+1)/2 when the offsets are symmetric and the values last refreshed were
- * found symmetric (the solve reads each sub-diagonal entry as its mirror; known from the
- * first solve after a rebuild on), else ndiag.  *plane (host, may be NULL) receives the
+ * found symmetric (the solve reads each sub-diagonal entry as its mirror; known from a
+ * setup on, and from the first solve after a rebuild on), else ndiag.  *plane (host, may be NULL) receives the
  * plane stride a when the level-0 kernels of a 7-point operator (offsets -a, -b, -1, 0,
  * 1, b, a) walk the grid plane by plane (two planes per workgroup, neighbours within a
  * plane from LDS), else 0.
@@ -287,9 +287,9 @@ typedef enum {
     AMG_K_CG_RZ = 6,         /* r.z */
     AMG_K_CG_INIT = 7,       /* r = f - A x, r.r, f.f */
     AMG_K_SMOOTH0_RES = 8,   /* first pre-smoothing sweep fused with the residual */
-    AMG_K_JACOBI = 9,        /* one smoothing sweep */
+    AMG_K_JACOBI = 9,        /* one smoothing sweep (a block system's first post-sweep: with u_l += P_l u_{l+1}) */
     AMG_K_RESTRICT = 10,     /* f_{l+1} = R_l r_l */
-    AMG_K_PROLONG = 11,      /* u_l += P_l u_{l+1} */
+    AMG_K_PROLONG = 11,      /* u_l += P_l u_{l+1}; where a level runs both in one pass, with the first post-sweep */
     AMG_K_COARSE_GEMV = 12,  /* u_L = A_L^{-1} f_L */
     AMG_K_CAST = 13,         /* FP64 <-> FP32 conversions of the mixed-precision form */
     AMG_K_TAIL = 14,         /* restriction into the coarse tail and Algorithm 2 on all its levels */
