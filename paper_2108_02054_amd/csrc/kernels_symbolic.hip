@@ -65,16 +65,44 @@ __device__ __forceinline__ int sym_insert(int* tab, int H, int shift, int c, boo
     return -1;
 }
 
-// Walks the terms of the A row [b, e): the group's lanes take 1 << lg lanes per B row, so
+// A row belongs to a group of G lanes or, on small levels of long rows, to W wavefronts
+// (G = 64) that share its table and take a W-th of its A entries each: one wavefront per row
+// left most of the chip idle (27-point 72x61x50, level 1 of 496 rows: count 64 -> 35 us, fill
+// 176 -> 57).
+template <int W>
+__device__ __forceinline__ void row_fence() {
+    if constexpr (W > 1)
+        __syncthreads();
+    else
+        wave_fence();
+}
+
+// Sum of one value per wavefront of the row, and of those before this one (tmp: W ints).
+template <int W>
+__device__ __forceinline__ int row_prefix(int v, int w, int* tmp, int& before) {
+    before = 0;
+    if constexpr (W == 1) return v;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) tmp[w] = v;
+    __syncthreads();
+    int t = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        if (q == w) before = t;
+        t += tmp[q];
+    }
+    return t;
+}
+
+// Walks the terms of the A row [b, e) (the first at offset carry): the group's lanes take 1 << lg lanes per B row, so
 // several B rows at a time, the first term of four such steps in flight together.
 // f(A entry, term within its B row, term within the row, column); entry(A entry, first
 // term's offset, B row start, B row length) once per A entry, before its terms.  Returns the
-// row's terms.
+// offset after the last.
 template <int G, class E, class F>
-__device__ __forceinline__ int sym_walk(int lane, int lg, int b, int e, const int* __restrict__ Acol,
+__device__ __forceinline__ int sym_walk(int lane, int lg, int b, int e, int carry, const int* __restrict__ Acol,
                                         const int* __restrict__ Bptr, const int* __restrict__ Bcol, E entry, F f) {
     const int per = G >> lg, sub = lane >> lg, q0 = lane & ((1 << lg) - 1), step = 1 << lg;
-    int carry = 0;
     for (int c0 = b; c0 < e; c0 += G) {
         const int k = c0 + lane;
         int b0 = 0, len = 0;
@@ -118,27 +146,29 @@ __device__ __forceinline__ int sym_walk(int lane, int lg, int b, int e, const in
 
 // cnt[i], terms[i] (both with a zero at n, so that exclusive scans end in the totals);
 // stat: {overflow, most terms in a row, longest row, longest B row met}.
-template <int G>
+template <int G, int W>
 __global__ __launch_bounds__(TPB) void k_sym_count(int n, int lg, int H, int shift, const int* __restrict__ Aptr,
                                                    const int* __restrict__ Acol, const int* __restrict__ Bptr,
                                                    const int* __restrict__ Bcol, int* __restrict__ cnt,
                                                    int64_t* __restrict__ terms, int* __restrict__ stat) {
     extern __shared__ __align__(16) unsigned char sym_smem[];
-    const int lane = threadIdx.x & (G - 1), gi = threadIdx.x / G;
+    __shared__ int tmp[W];
+    const int lane = threadIdx.x & (G - 1), gi = threadIdx.x / (G * W), w = (threadIdx.x / G) % W;
     int* tab = reinterpret_cast<int*>(sym_smem) + (size_t)gi * H;
-    const int row = xcd_block() * ((int)blockDim.x / G) + gi;
-    if (row > n) return;  // groups leave whole
+    const int row = xcd_block() * ((int)blockDim.x / (G * W)) + gi;
+    if (row > n) return;  // rows leave whole
     if (row == n) {
-        if (lane == 0) {
+        if (lane == 0 && w == 0) {
             cnt[n] = 0;
             terms[n] = 0;
         }
         return;
     }
-    for (int s = lane; s < H; s += G) tab[s] = -1;
-    wave_fence();
-    int u = 0, full = 0, mb = 0;
-    const int nterm = sym_walk<G>(lane, lg, Aptr[row], Aptr[row + 1], Acol, Bptr, Bcol,
+    for (int s = w * G + lane; s < H; s += G * W) tab[s] = -1;
+    row_fence<W>();
+    const int b = Aptr[row], e = Aptr[row + 1], per = (e - b + W - 1) / W;
+    int u = 0, full = 0, mb = 0, before;
+    int nterm = sym_walk<G>(lane, lg, min(b + w * per, e), min(b + (w + 1) * per, e), 0, Acol, Bptr, Bcol,
                                   [&](int, int, int, int len) { mb = max(mb, len); },
                                   [&](int, int, int, int c) {
                                       bool fresh;
@@ -149,13 +179,16 @@ __global__ __launch_bounds__(TPB) void k_sym_count(int n, int lg, int H, int shi
     full = group_sum_i<G>(full);
 #pragma unroll
     for (int o = G / 2; o > 0; o >>= 1) mb = max(mb, __shfl_xor(mb, o, G));
-    if (lane == 0) {
+    u = row_prefix<W>(u, w, tmp, before);
+    full = row_prefix<W>(full, w, tmp, before);
+    nterm = row_prefix<W>(nterm, w, tmp, before);
+    if (lane == 0) raise_max(&stat[3], mb);
+    if (lane == 0 && w == 0) {
         cnt[row] = u;
         terms[row] = nterm;
         raise_max(&stat[0], full ? 1 : 0);
         raise_max(&stat[1], nterm);
         raise_max(&stat[2], u);
-        raise_max(&stat[3], mb);
     }
 }
 
@@ -168,33 +201,41 @@ __global__ void k_sym_totals(int n, const int* __restrict__ ptr, const int64_t* 
 
 // Columns of row i of C in order, and the plan: per A entry its B row start (bst) and, with
 // pos, its first term's offset and per term its column's position in the C row; with inv,
-// per A entry k and position p of the C row the B row's entry there, inv[k W + p] = entry + 1
+// per A entry k and position p of the C row the B row's entry there, inv[k iw + p] = entry + 1
 // (inv cleared by the caller: 0 for none).
-template <int G, typename PT>
+template <int G, int W, typename PT>
 __global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shift, const int* __restrict__ Aptr,
                                                   const int* __restrict__ Acol, const int* __restrict__ Bptr,
                                                   const int* __restrict__ Bcol, const int* __restrict__ Cptr,
                                                   int* __restrict__ Ccol, const int64_t* __restrict__ off,
                                                   int* __restrict__ bst, uint16_t* __restrict__ tof,
-                                                  PT* __restrict__ pos, uint8_t* __restrict__ inv, int W) {
+                                                  PT* __restrict__ pos, uint8_t* __restrict__ inv, int iw) {
     extern __shared__ __align__(16) unsigned char sym_smem[];
-    const int lane = threadIdx.x & (G - 1), gi = threadIdx.x / G;
+    __shared__ int tmp[W];
+    const int lane = threadIdx.x & (G - 1), gi = threadIdx.x / (G * W), w = (threadIdx.x / G) % W;
     unsigned char* base = sym_smem + (size_t)gi * 8 * H;
     int* tab = reinterpret_cast<int*>(base);
     uint16_t* rank = reinterpret_cast<uint16_t*>(base + (size_t)4 * H);  // of the column in each slot
     uint16_t* list = reinterpret_cast<uint16_t*>(base + (size_t)6 * H);  // the occupied slots
-    const int row = xcd_block() * ((int)blockDim.x / G) + gi;
+    const int row = xcd_block() * ((int)blockDim.x / (G * W)) + gi;
     if (row >= n) return;
-    for (int s = lane; s < H; s += G) tab[s] = -1;
-    wave_fence();
-    const int b = Aptr[row], e = Aptr[row + 1];
+    for (int s = w * G + lane; s < H; s += G * W) tab[s] = -1;
+    row_fence<W>();
+    const int rb = Aptr[row], re = Aptr[row + 1], per = (re - rb + W - 1) / W;
+    const int b = min(rb + w * per, re), e = min(rb + (w + 1) * per, re);  // this wavefront's entries
+    int first = 0;  // its first term's offset
+    if constexpr (W > 1) {
+        int mine = 0;
+        for (int k = b + lane; k < e; k += G) mine += Bptr[Acol[k] + 1] - Bptr[Acol[k]];
+        row_prefix<W>(group_sum_i<G>(mine), w, tmp, first);
+    }
     PT* prow = pos != nullptr ? pos + off[row] : nullptr;
     // where a slot number fits a position's type the first walk leaves each term's slot in its
     // place, and the ranks replace them in a pass over contiguous memory; else the row is
     // walked again
     const bool by_slot = prow != nullptr && (sizeof(PT) > 1 || H <= 256);
-    const int nterm = sym_walk<G>(
-        lane, lg, b, e, Acol, Bptr, Bcol,
+    const int last = sym_walk<G>(
+        lane, lg, b, e, first, Acol, Bptr, Bcol,
         [&](int k, int to, int b0, int) {
             if (bst != nullptr) bst[k] = b0;
             if (tof != nullptr) tof[k] = (uint16_t)to;
@@ -204,19 +245,27 @@ __global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shif
             const int slot = sym_insert(tab, H, shift, c, fresh);
             if (by_slot) prow[t] = (PT)slot;
         });
-    wave_fence();
+    row_fence<W>();
     int u = 0;
+    const int s_lo = W > 1 ? (H / W) * w : 0, s_hi = W > 1 ? s_lo + H / W : H;  // (H / W: a multiple of G)
+    if constexpr (W > 1) {
+        int occ = 0, before;
+        for (int s0 = s_lo; s0 < s_hi; s0 += G) occ += __popcll(__ballot(tab[s0 + lane] != -1));
+        row_prefix<W>(occ, w, tmp, before);
+        u = before;
+    }
     const int shiftg = (threadIdx.x & 63) & ~(G - 1);
     const unsigned long long mine = G == 64 ? ~0ull : ((1ull << G) - 1);
-    for (int s0 = 0; s0 < H; s0 += G) {  // H is a multiple of 64
+    for (int s0 = s_lo; s0 < s_hi; s0 += G) {  // H is a multiple of 64
         const bool occ = tab[s0 + lane] != -1;
         const unsigned long long m = (__ballot(occ) >> shiftg) & mine;
         if (occ) list[u + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)(s0 + lane);
         u += __popcll(m);
     }
-    wave_fence();
+    row_fence<W>();
     const int cb = Cptr[row], len = Cptr[row + 1] - cb;
-    for (int x0 = 0; x0 < u; x0 += G) {
+    if constexpr (W > 1) u = len;
+    for (int x0 = w * G; x0 < u; x0 += G * W) {
         const int x = x0 + lane;
         const int slot = x < u ? list[x] : 0;
         const int c = x < u ? tab[slot] : -1;
@@ -232,19 +281,19 @@ __global__ __launch_bounds__(TPB) void k_sym_fill(int n, int lg, int H, int shif
         }
     }
     if (pos == nullptr && inv == nullptr) return;
-    wave_fence();
+    row_fence<W>();
     if (by_slot) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // (the slots other lanes wrote)
-        for (int t = lane; t < nterm; t += G) prow[t] = (PT)rank[prow[t]];
+        for (int t = first + lane; t < last; t += G) prow[t] = (PT)rank[prow[t]];
         return;
     }
-    sym_walk<G>(lane, lg, b, e, Acol, Bptr, Bcol, [](int, int, int, int) {}, [&](int k, int q, int t, int c) {
+    sym_walk<G>(lane, lg, b, e, first, Acol, Bptr, Bcol, [](int, int, int, int) {}, [&](int k, int q, int t, int c) {
         unsigned h = sym_hash(c, shift);
         for (int p = 0; p < H && tab[h] != c; ++p) h = (h + 1) & (unsigned)(H - 1);
         if (prow != nullptr)
             prow[t] = (PT)rank[h];
         else
-            inv[(size_t)k * W + rank[h]] = (uint8_t)(q + 1);
+            inv[(size_t)k * iw + rank[h]] = (uint8_t)(q + 1);
     });
 }
 
@@ -271,6 +320,14 @@ static int sym_group(double mean_terms, int H) {
             default: { constexpr int G = 64; __VA_ARGS__; } break;          \
         }                                                                   \
     } while (0)
+
+// Products of at most SYM_W_ROWS rows get SYM_W wavefronts per row where a row has at least
+// SYM_W_TERMS terms (fewer don't keep them busy) and a wavefront of table slots for each; the
+// largest table leaves no LDS beside it.
+constexpr int SYM_W = 4, SYM_W_ROWS = 2048, SYM_W_TERMS = 1024;
+static bool sym_wide(int n, int g, int H, double mean_terms) {
+    return g == 64 && n <= SYM_W_ROWS && H >= 64 * SYM_W && H < SYM_H_MAX && mean_terms >= SYM_W_TERMS;
+}
 
 // Threads per workgroup: whole wavefronts, as many rows as SYM_SMEM holds.
 static int sym_threads(int g, size_t row_bytes) {
@@ -300,8 +357,12 @@ bool symbolic_count(const Csr& A, const Csr& B, Csr& C, int64_t* off, SymSizes& 
         const int g = sym_group(z.mean_terms, H), lg = std::min(lg_b, log2_ceil(g));
         const int t = sym_threads(g, (size_t)4 * H), rows = t / g, shift = 32 - log2_ceil(H);
         HIP_CHECK(hipMemsetAsync(stat, 0, 4 * sizeof(int), s));
-        AMG_WITH_SYM_G(g, (k_sym_count<G><<<(unsigned)(n / rows + 1), t, (size_t)rows * 4 * H, s>>>(
-                              n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, cnt, terms, stat)));
+        if (sym_wide(n, g, H, z.mean_terms))
+            k_sym_count<64, SYM_W><<<(unsigned)n + 1, 64 * SYM_W, (size_t)4 * H, s>>>(n, lg, H, shift, A.ptr, A.col, B.ptr,
+                                                                                     B.col, cnt, terms, stat);
+        else
+            AMG_WITH_SYM_G(g, (k_sym_count<G, 1><<<(unsigned)(n / rows + 1), t, (size_t)rows * 4 * H, s>>>(
+                                  n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, cnt, terms, stat)));
         HIP_LAUNCH_CHECK();
         exclusive_scan_i32(cnt, C.ptr, (int64_t)n + 1, s);
         exclusive_scan_i64(terms, off, (int64_t)n + 1, s);
@@ -345,14 +406,21 @@ void symbolic_fill(const Csr& A, const Csr& B, const Csr& C, const GalShape& gs,
     const int g = sym_group(z.mean_terms, H), lg = std::min(std::min(log2_ceil(z.mean_b), 6), log2_ceil(g));
     const int t = sym_threads(g, (size_t)8 * H), rows = t / g, shift = 32 - log2_ceil(H);
     const unsigned nb = (unsigned)((n + rows - 1) / rows);
+    auto fill = [&](auto* pos) {
+        using PT = std::remove_pointer_t<decltype(pos)>;
+        auto go = [&](auto kern, unsigned blocks, int threads, size_t bytes) {
+            kern<<<blocks, threads, bytes, s>>>(n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, C.ptr, C.col, off, gs.bst,
+                                                gs.tof, pos, gs.inv, gs.inv_w);
+        };
+        if (sym_wide(n, g, H, z.mean_terms))
+            go(k_sym_fill<64, SYM_W, PT>, (unsigned)n, 64 * SYM_W, (size_t)8 * H);
+        else
+            AMG_WITH_SYM_G(g, go(k_sym_fill<G, 1, PT>, nb, t, (size_t)rows * 8 * H));
+    };
     if (gs.wide)
-        AMG_WITH_SYM_G(g, (k_sym_fill<G, uint16_t><<<nb, t, (size_t)rows * 8 * H, s>>>(
-                              n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, C.ptr, C.col, off, gs.bst, gs.tof,
-                              (uint16_t*)gs.pos, gs.inv, gs.inv_w)));
+        fill((uint16_t*)gs.pos);
     else
-        AMG_WITH_SYM_G(g, (k_sym_fill<G, uint8_t><<<nb, t, (size_t)rows * 8 * H, s>>>(
-                              n, lg, H, shift, A.ptr, A.col, B.ptr, B.col, C.ptr, C.col, off, gs.bst, gs.tof,
-                              (uint8_t*)gs.pos, gs.inv, gs.inv_w)));
+        fill((uint8_t*)gs.pos);
     HIP_LAUNCH_CHECK();
 }
 

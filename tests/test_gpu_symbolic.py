@@ -205,3 +205,36 @@ def test_aggregates_by_row_lanes(kind, n):
     compare_levels(g, o, tol=1e-10, values=False)
     g.close()
     o.close()
+
+
+@pytest.mark.parametrize("n,nc,couplings,per_row", [
+    (3000, 2048, 25, 3), (3000, 2049, 25, 3),  # the most rows that share wavefronts, and one more
+    (900, 70, 20, 2),                           # C rows of fewer columns than a byte holds
+    (1500, 1200, 60, 1),                        # rows of R of one or two entries: idle wavefronts
+    (700, 500, 120, 6)])
+def test_product_rows_by_several_wavefronts(n, nc, couplings, per_row):
+    """Products of few rows with many terms each: patterns exact, values to rounding, as set up
+    and after a partial update (which walks the plan)."""
+    from paper_2108_02054_amd import AMG
+    g = np.random.default_rng(n + nc)
+    A = spd_from(n, g.integers(0, n, couplings * n), g.integers(0, n, couplings * n), 12)
+    P, P2 = transfer(n, nc, per_row, 31, empty=1), transfer(nc, min(nc, 40), 1, 32)
+    args = [(T(M.indptr.astype(np.int32)), T(M.indices.astype(np.int32)), T(M.data), M.shape[1]) for M in (P, P2)]
+    print(f"case several wavefronts n={n} nc={nc} couplings={couplings}", flush=True)
+    h = AMG(T(A.indptr.astype(np.int32)), T(A.indices.astype(np.int32)), T(A.data), transfer=args)
+    one = lambda M: sp.csr_matrix((np.ones(M.nnz), M.indices, M.indptr), shape=M.shape)  # noqa: E731
+    S1 = (one(P).T @ one(A) @ one(P)).tocsr()
+    S2 = (one(P2).T @ one(S1) @ one(P2)).tocsr()
+    for scale in (1.0, 1.5):
+        if scale != 1.0:
+            h.rebuild(T(scale * A.data))
+        B = (scale * A).tocsr()
+        for l, (Q, S) in enumerate(((P, S1), (P2, S2))):
+            S.sort_indices()
+            C = (Q.T @ B @ Q).tocsr()
+            got = h.level(l + 1)["A"]
+            assert np.array_equal(got[0], S.indptr) and np.array_equal(got[1], S.indices)
+            B = sp.csr_matrix((got[2], got[1], got[0]), shape=C.shape)
+            # sums of at most 1e6 rounded products: well below 1e-11 of the largest entry
+            assert abs(B - C).max() <= 1e-11 * abs(C).max()
+    h.close()
