@@ -807,6 +807,7 @@ void configure_dia(amg_ctx* c) {
     if (nd == 0) return;  // not a well-filled stencil
     Dia D;
     D.ndiag = nd;
+    D.rows = A.nrows;
     for (int d = 0; d < nd; ++d) D.off.off[d] = offs[(size_t)d];
     D.symoff = (nd & 1) == 1 && offs[(size_t)nd / 2] == 0;
     for (int d = 0; d < nd / 2 && D.symoff; ++d) D.symoff = offs[(size_t)d] == -offs[(size_t)(nd - 1 - d)];

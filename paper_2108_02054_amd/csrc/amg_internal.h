@@ -292,6 +292,7 @@ struct WinPlan {
 };
 struct Dia {
     int ndiag = 0;              // 0: not used
+    int rows = 0;
     DiaOff off{};
     bool symoff = false;        // the offsets are -k..k-symmetric and include 0
     // 7-point marching kernels: offsets -a, -b, -1, 0, 1, b, a; march_a == 0: not used
