@@ -544,8 +544,8 @@ void launch_diag_index(const Csr& A, int32_t* dpos, hipStream_t s) {
 
 // Launch shape of the position-map form for C = L B from its sizes (rows and entries of L,
 // terms, the longest C row): cap = the longest C row rounded up to a multiple of 8; TPL =
-// 2 terms per lane and entry for products of at least TPL2_MIN_ROWS rows (more rows per
-// wavefront, fewer B rows left to a second round trip; measured at 128^3: level-0 A P
+// 2 terms per lane and entry for products of at least TPL2_MIN_ROWS rows, half as many where
+// the L rows are long (more rows per wavefront, fewer B rows left to a second round trip; measured at 128^3: level-0 A P
 // 286 against 315 us, R (A P) 215 against 241 us), else 1 (small products want every lane
 // on few rows); G = the power of two in [4, 64] nearest above the mean number of terms
 // per L entry over TPL (the mean referenced B row length, so that most B rows take one
@@ -554,7 +554,11 @@ void launch_diag_index(const Csr& A, int32_t* dpos, hipStream_t s) {
 // WF_SMEM_MAX.  {0, ...}: the rows are too long for the form (lane-group kernels).
 // gforce and tforce force G and TPL where the LDS allows.  The position map itself is
 // built by the caller.
+// Long L rows gain from half as many rows on (27-point 112^3, rows of 50 entries: R (A P) of
+// 49888 rows 421 -> 371 us, A_1 P_1 123 -> 96), shorter ones don't (two-fluid 72^3, 34137 rows
+// of 38 and 33: 52 -> 55, 40 -> 42).
 constexpr int32_t TPL2_MIN_ROWS = 1 << 16;
+constexpr double TPL2_LONG = 44.0;
 // Products of fewer rows (and L rows of more than a chunk) take at least 8 lanes per row: 4
 // leave the device half empty (A P of 24078 rows 40 -> 25 us; of 46669 rows 47 us both ways).
 constexpr int32_t LANES8_ROWS = 1 << 15;
@@ -566,7 +570,8 @@ GalShape pick_galerkin_shape(int32_t nrows, int64_t nnzL, int64_t terms, int max
     const double mean_b = nnzL > 0 ? (double)terms / (double)nnzL : 1.0;
     const int cap = std::max(8, (maxlen + 7) / 8 * 8);
     const double mean_l = nrows > 0 ? (double)nnzL / (double)nrows : 1.0;
-    const int tpl = (tforce == 1 || tforce == 2) ? tforce : (nrows >= TPL2_MIN_ROWS ? 2 : 1);
+    const int tpl = (tforce == 1 || tforce == 2) ? tforce
+                    : nrows >= TPL2_MIN_ROWS || (nrows >= TPL2_MIN_ROWS / 2 && mean_l >= TPL2_LONG) ? 2 : 1;
     int G = 4;
     while (G < 64 && G * tpl < mean_b) G <<= 1;
     while (G < 64 && 8 * G <= mean_l) G <<= 1;  // long L rows: wider groups, fewer chunks

@@ -238,3 +238,24 @@ def test_product_rows_by_several_wavefronts(n, nc, couplings, per_row):
             # sums of at most 1e6 rounded products: well below 1e-11 of the largest entry
             assert abs(B - C).max() <= 1e-11 * abs(C).max()
     h.close()
+
+
+@pytest.mark.parametrize("N", [97, 98, 104])  # 32633, 33633 and 39929 rows on level 1
+def test_products_of_long_rows_two_terms_per_lane(monkeypatch, N):
+    """Two B terms per lane and entry from 32768 rows of 44 entries on: the coarse operators of
+    an update equal those of one term per lane bit for bit."""
+    from paper_2108_02054_amd import AMG
+    from workloads import lognormal_27pt
+    p, c, v = lognormal_27pt(N, 0)
+    v1 = 1.25 * v
+    print(f"case two terms per lane N={N}", flush=True)
+    got = []
+    for form in (None, "pos:16:1"):
+        if form:
+            monkeypatch.setenv("AMGMI_GALERKIN", form)
+        g = AMG(T(p), T(c), T(v), eps_strong=0.02)
+        g.rebuild(T(v1))
+        got.append([g.level(l)["A"][2] for l in range(1, g.num_levels)])
+        g.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
