@@ -2312,6 +2312,21 @@ amg_status amg_solve_bicgstab(amg_ctx* c, const double* f, double* u, amg_solve_
     return st;
 }
 
+namespace {
+// The diagonal storage as the operator's entry points read it.  A call that is being captured
+// into a graph reads every stored entry: replays see the values of later updates, which need
+// not be symmetric as those of the capture were.
+Dia operator_storage(const amg_ctx* c) {
+    Dia D = c->dia;
+    if (D.off.sym) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        HIP_CHECK(hipStreamIsCapturing(c->stream, &st));
+        if (st != hipStreamCaptureStatusNone) D.off.sym = 0;
+    }
+    return D;
+}
+}  // namespace
+
 amg_status amg_apply_operator(amg_ctx* c, const double* x, double* y) {
     if (!c || !x || !y || x == y) return AMG_ERR_ARG;
     return guard(c, [&] {
@@ -2321,7 +2336,7 @@ amg_status amg_apply_operator(amg_ctx* c, const double* x, double* y) {
         const int n = L0.A.nrows;
         double* w = c->pb;
         if (c->dia.ndiag > 0 && c->outer_val == L0.A.val)
-            launch_dia_cg_pq(n, c->dia, x, x, w, y, 1, c->rs, c->stream);
+            launch_dia_cg_pq(n, operator_storage(c), x, x, w, y, 1, c->rs, c->stream);
         else if (c->prm.block_size > 1)
             launch_node_cg_pq(L0, c->prm.block_size, c->outer_val, x, x, w, y, 1, c->rs, c->stream);
         else
@@ -2386,7 +2401,7 @@ amg_status amg_apply_operator_noalloc(amg_ctx* c, const double* x, double* y) {
         rs.host = nullptr;
         double* w = sp;  // the p copy
         if (c->dia.ndiag > 0 && c->outer_val == L0.A.val)
-            launch_dia_cg_pq(n, c->dia, x, x, w, y, 1, rs, c->stream);
+            launch_dia_cg_pq(n, operator_storage(c), x, x, w, y, 1, rs, c->stream);
         else if (c->prm.block_size > 1)
             launch_node_cg_pq(L0, c->prm.block_size, c->outer_val, x, x, w, y, 1, rs, c->stream);
         else
