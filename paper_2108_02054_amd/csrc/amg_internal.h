@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "amg.h"
+#include "rules.h"
 
 namespace amgmi {
 
@@ -507,8 +508,9 @@ void transpose_sorted(const Csr& P, Csr& R, hipStream_t s);
 // Pattern of C = A B: symbolic_count writes C's row pointers, the offset of each row's first
 // term (off, nrows + 1) and the sizes, and allocates C.col; symbolic_fill writes the
 // columns and, when gs.pos is allocated, the plan gs.pos, gs.bst, gs.tof.  symbolic_count
-// returns false (C freed) when a row has more entries than its tables hold: then
-// symbolic_sorted forms the pattern, without a plan.
+// returns false (C freed) when a row has more entries than its tables hold, or the rows
+// take more threads than a launch has: then symbolic_sorted forms the pattern, without a
+// plan.
 struct SymSizes {
     int64_t terms = 0, max_terms = 0;  // all, and the most in a row
     int maxlen = 0;                    // longest row of C

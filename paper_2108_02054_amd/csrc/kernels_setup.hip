@@ -46,7 +46,7 @@ __global__ __launch_bounds__(TPB) void k_validate(int n, int ncols, int64_t nnz,
                                                   const double* __restrict__ val, int* __restrict__ diag_pos,
                                                   int* __restrict__ flags) {
     const int lane = threadIdx.x & (G - 1);
-    const int i = (int)((blockIdx.x * (int64_t)TPB + threadIdx.x) / G);
+    const int i = lane_row(blockIdx.x, TPB, threadIdx.x, G);
     if (i == 0 && lane == 0 && (ptr[0] != 0 || (int64_t)ptr[n] != nnz)) atomicOr(&flags[F_ARG], 1);
     if (i >= n) return;
     const int b = ptr[i], e = ptr[i + 1];
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(TPB) void k_strength(int n, const int* __restrict__
                                                   double eps2, uint8_t* __restrict__ strong, int* __restrict__ tpos,
                                                   uint8_t* __restrict__ isolated, int* __restrict__ flags) {
     const int lane = threadIdx.x & (G - 1);
-    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    const int i = lane_row(xcd_block(), TPB, threadIdx.x, G);
     if (i >= n) return;
     const double aii = val[diag_pos[i]];
     int any = 0;
@@ -187,9 +187,8 @@ template <int G>
 struct RowLanes {
     int i, lane;
     __device__ __forceinline__ RowLanes() {
-        const int t = xcd_block() * TPB + (int)threadIdx.x;
-        i = t / G;
-        lane = t & (G - 1);
+        i = lane_row(xcd_block(), TPB, threadIdx.x, G);
+        lane = threadIdx.x & (G - 1);
     }
 };
 
@@ -353,7 +352,7 @@ __global__ __launch_bounds__(TPB) void k_agg_pass2(int n, const int* __restrict_
                                                    const int* __restrict__ agg1, int* __restrict__ agg,
                                                    int* __restrict__ flags) {
     const int lane = threadIdx.x & (G - 1);
-    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    const int i = lane_row(xcd_block(), TPB, threadIdx.x, G);
     if (i >= n) return;
     const int a1 = agg1[i];
     if (a1 >= 0 || state[i] == ST_ISOLATED) {
@@ -545,7 +544,7 @@ __global__ __launch_bounds__(TPB) void k_filter(int n, const int* __restrict__ p
                                                 double* __restrict__ dF, unsigned long long* __restrict__ rho_bits) {
     __shared__ unsigned long long sm[TPB / 64];
     const int lane = threadIdx.x & (G - 1);
-    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    const int i = lane_row(xcd_block(), TPB, threadIdx.x, G);
     unsigned long long bits = 0;
     if (i < n) {
         const bool iso = agg[i] < 0;
@@ -600,7 +599,7 @@ __global__ __launch_bounds__(TPB) void k_entry_agg(int n, const int* __restrict_
                                                    const uint8_t* __restrict__ strong, const int* __restrict__ agg,
                                                    int* __restrict__ eagg) {
     const int lane = threadIdx.x & (G - 1);
-    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    const int i = lane_row(xcd_block(), TPB, threadIdx.x, G);
     if (i >= n) return;
     const bool iso = agg[i] < 0;
     const int e = ptr[i + 1];
@@ -617,7 +616,7 @@ template <int G>
 __global__ __launch_bounds__(TPB) void k_pcount(int n, const int* __restrict__ ptr, const int* __restrict__ eagg,
                                                 int* __restrict__ key, int* __restrict__ cnt) {
     const int lane = threadIdx.x & (G - 1);
-    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    const int i = lane_row(xcd_block(), TPB, threadIdx.x, G);
     if (i >= n) return;
     const int b = ptr[i], e = ptr[i + 1];
     int c = 0;
@@ -653,7 +652,7 @@ __global__ __launch_bounds__(TPB) void k_pfill(int n, const int* __restrict__ pt
                                                const int* __restrict__ Pptr, int* __restrict__ Pcol,
                                                double* __restrict__ Pval) {
     const int lane = threadIdx.x & (G - 1);
-    const int i = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    const int i = lane_row(xcd_block(), TPB, threadIdx.x, G);
     if (i >= n) return;
     const int ai = agg[i];
     if (ai < 0) return;

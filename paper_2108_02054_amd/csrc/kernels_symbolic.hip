@@ -338,6 +338,7 @@ static int sym_threads(int g, size_t row_bytes) {
 
 bool symbolic_count(const Csr& A, const Csr& B, Csr& C, int64_t* off, SymSizes& z, hipStream_t s) {
     const int n = A.nrows;
+    if (!lanes_fit_grid((int64_t)n + 1, 8)) return false;
     C.nrows = n;
     C.ncols = B.ncols;
     C.ptr = dnew<int32_t>((size_t)n + 1, s);
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(TPB) void k_tr_order(int nc, const int* __restrict_
                                                   double* __restrict__ Rval) {
     __shared__ __align__(16) int keys[TPB / G][TR_KEYS * G];
     const int lane = threadIdx.x & (G - 1);
-    const int row = (xcd_block() * TPB + (int)threadIdx.x) / G;
+    const int row = lane_row(xcd_block(), TPB, threadIdx.x, G);
     int* mine = keys[threadIdx.x / G];
     const int b = row < nc ? Rptr[row] : 0, u = row < nc ? Rptr[row + 1] - b : 0;
     for (int x = lane; x < ((u + 3) & ~3); x += G) mine[x] = x < u ? tmp[b + x].x : 0x7fffffff;
@@ -650,7 +651,7 @@ void launch_row_blocks(const Csr& A, int* most, hipStream_t s) {
 __global__ __launch_bounds__(TPB) void k_c16_bases(int n, int rpb, const int* __restrict__ ptr,
                                                    const int* __restrict__ col, int* __restrict__ cblk,
                                                    int* __restrict__ wide) {
-    const int b = (blockIdx.x * TPB + threadIdx.x) >> 6, lane = threadIdx.x & 63;
+    const int b = lane_row(blockIdx.x, TPB, threadIdx.x, 64), lane = threadIdx.x & 63;
     const int r0 = b * rpb, r1 = min(r0 + rpb, n);
     if (r0 >= n) return;
     int lo = 0x7fffffff, hi = -1;

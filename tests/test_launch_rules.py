@@ -1,0 +1,50 @@
+"""Index and size rules of the launches (csrc/rules.h), checked by the host compiler: every
+expression below is a constant expression, in which an overflow does not compile."""
+import os
+import re
+import subprocess
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2108_02054_amd", "csrc")
+
+
+def holds(lines, tmp_path):
+    """None if every constant expression holds, else the compiler's first error."""
+    src = tmp_path / "rules.cpp"
+    src.write_text('#include "rules.h"\nusing namespace amgmi;\n'
+                   + "\n".join(f"static_assert({x}, \"\");" for x in lines) + "\n")
+    r = subprocess.run(["g++", "-std=c++17", "-fsyntax-only", "-I", CSRC, str(src)], capture_output=True, text=True)
+    return None if r.returncode == 0 else r.stderr
+
+
+def test_lane_rows_of_the_largest_systems(tmp_path):
+    """The rows of a 7-point operator of 2^31 - 1 entries with eight lanes each, and of every
+    number of lanes at the most rows whose threads a launch can count."""
+    lines = []
+    for lanes in (1, 4, 8, 16, 32, 64, 128, 256):
+        most = min(2**31 - 257, (2**32 - 1024) // lanes)
+        for row in {0, 1, 2**31 // 7 // lanes, 2**31 // lanes - 1, 2**31 // lanes, most - 1}:
+            if row > most - 1:
+                continue
+            block, first = divmod(row, 256 // lanes)
+            for lane in {0, lanes - 1}:
+                lines.append(f"lane_row({block}, 256, {first * lanes + lane}, {lanes}) == {row}")
+    lines.append(f"lane_row({(2**31 // 7) // 32}, 256, 255, 8) >= {2**31 // 7 - 32}")
+    assert holds(lines, tmp_path) is None
+
+
+def test_former_index_leaves_32_bits(tmp_path):
+    """The check can fail: the thread's number in the whole grid does not fit."""
+    row = 2**28
+    assert holds([f"({row // 32} * 256 + 0) / 8 == {row}"], tmp_path) is not None
+
+
+def test_rows_that_fit_one_launch(tmp_path):
+    assert holds(["lanes_fit_grid(1ll << 28, 8)", "lanes_fit_grid((1ll << 29) - 128, 8)",
+                  "!lanes_fit_grid(1ll << 29, 8)", "lanes_fit_grid(2147483647ll, 1)"], tmp_path) is None
+
+
+def test_setup_kernels_use_the_rule():
+    """No kernel of the setup divides the thread's number in the whole grid."""
+    for name in ("kernels_setup.hip", "kernels_symbolic.hip"):
+        text = open(os.path.join(CSRC, name)).read()
+        assert not re.search(r"\*\s*\(?(int64_t\))?\s*TPB\s*\+\s*(\(int\))?threadIdx\.x\)\s*(/|>>)", text), name
