@@ -597,6 +597,14 @@ __device__ inline int xcd_block() {
     return x * per + (x < rem ? x : rem) + i;
 }
 
+// Orders a wavefront's own LDS accesses (they complete in program order; this keeps the
+// compiler from moving them).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ------------------------------------------------------------------ CG scalars
 //
 // beta and alpha come from partials that the kernel before wrote.  On a large grid a

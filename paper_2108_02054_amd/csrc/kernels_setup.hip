@@ -1065,6 +1065,7 @@ __device__ void gj_invert_lds(double* D, int nt, double* X2, int* bad) {
         const int N = S + 1;  // the next pivot block, wavefront 0's
         if (N < nt && w == 0) {
             update(N, N);
+            wave_fence();  // stored in the product's lane layout, read back in another
             gj_inv16(tile(N, N), LD, Xn, bad);
         } else {
             const int m = nt - 1;

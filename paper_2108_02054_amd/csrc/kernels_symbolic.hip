@@ -9,14 +9,6 @@ namespace amgmi {
 
 constexpr int TPB = 256;
 
-// Orders a wavefront's own LDS accesses (they complete in program order; this keeps the
-// compiler from moving them).
-__device__ __forceinline__ void wave_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int G>
 __device__ __forceinline__ int group_sum_i(int v) {
 #pragma unroll
@@ -519,9 +511,7 @@ __global__ __launch_bounds__(TPB) void k_tr_order(int nc, const int* __restrict_
     if constexpr (G > 64) {
         __syncthreads();
     } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_fence();
     }
     for (int x = lane; x < u; x += 2 * G) {
         const int x2 = x + G < u ? x + G : x;
