@@ -609,6 +609,26 @@ __global__ __launch_bounds__(TPB) void k_entry_agg(int n, const int* __restrict_
     }
 }
 
+// Rows of more than LONG_ROW entries per lane go through their aggregates one by one, in a pass
+// over the row for each: comparing every entry with every earlier one, as short rows do, grows
+// with the square of the length, while a long row (a hub: a node coupled to most others) meets
+// few aggregates or, being isolated, none (a star of 8000 nodes: setup 2337 -> 18 ms).
+constexpr int LONG_ROW = 16;
+
+// The smallest v of the G lanes with its entry k, the earlier one where several lanes have it.
+template <int G>
+__device__ __forceinline__ void group_first(int& v, int& k) {
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) {
+        const int w = __shfl_xor(v, o, G), q = __shfl_xor(k, o, G);
+        if (w < v || (w == v && q < k)) {
+            v = w;
+            k = q;
+        }
+    }
+}
+constexpr int NO_AGG = 0x7fffffff;
+
 // Number of distinct aggregates among the columns of row i of A_F; that is the length of
 // row i of A_F P_tent and of the smoothed P.  key[k] = 2 * aggregate + 1 for an aggregate's
 // first entry, 2 * aggregate for its others, -1 for entries A_F drops.
@@ -619,6 +639,26 @@ __global__ __launch_bounds__(TPB) void k_pcount(int n, const int* __restrict__ p
     const int i = lane_row(xcd_block(), TPB, threadIdx.x, G);
     if (i >= n) return;
     const int b = ptr[i], e = ptr[i + 1];
+    if (e - b > LONG_ROW * G) {
+        for (int k = b + lane; k < e; k += G) key[k] = eagg[k] < 0 ? -1 : 2 * eagg[k];
+        int c = 0;
+        for (int last = -1;; ++c) {
+            int J = NO_AGG, first = NO_AGG;
+            for (int k = b + lane; k < e; k += G) {
+                const int a = eagg[k];
+                if (a > last && a < J) {
+                    J = a;
+                    first = k;
+                }
+            }
+            group_first<G>(J, first);
+            if (J == NO_AGG) break;
+            if ((first - b) % G == lane) key[first] = 2 * J + 1;  // (by the lane that wrote it above)
+            last = J;
+        }
+        if (lane == 0) cnt[i] = c;
+        return;
+    }
     int c = 0;
     for (int c0 = b; c0 < e; c0 += G) {
         const int k = c0 + lane;
@@ -662,6 +702,38 @@ __global__ __launch_bounds__(TPB) void k_pfill(int n, const int* __restrict__ pt
     const double di = dF[i];
     const double scale = omega / di;
     const int b = ptr[i], e = ptr[i + 1];
+    if (e - b > LONG_ROW * G) {
+        const int shift = (threadIdx.x & 63) & ~(G - 1);
+        const unsigned mask = G == 32 ? ~0u : (1u << G) - 1;
+        int last = -1;
+        for (int p = p0;; ++p) {
+            int J = NO_AGG, first = NO_AGG;
+            for (int k = b + lane; k < e; k += G) {
+                const int kk = key[k];
+                if (kk > 0 && (kk & 1) && (kk >> 1) > last && (kk >> 1) < J) {
+                    J = kk >> 1;
+                    first = k;
+                }
+            }
+            group_first<G>(J, first);
+            if (J == NO_AGG) break;
+            double sJ = 0.0;  // of the entries from the first on, in order
+            for (int c1 = first - (first - b) % G; c1 < e; c1 += G) {
+                const int q = c1 + lane;
+                const bool hit = q < e && key[q] >= 0 && (key[q] >> 1) == J;
+                const double vq = hit ? (col[q] == i ? di : val[q]) : 0.0;
+                for (unsigned m = (unsigned)(__ballot(hit) >> shift) & mask; m != 0; m &= m - 1)
+                    sJ += __shfl(vq, __ffs(m) - 1, G);
+            }
+            if (lane == 0) {
+                const double pt = (J == ai) ? 1.0 : 0.0;
+                Pcol[p] = J;
+                Pval[p] = pt - scale * sJ;
+            }
+            last = J;
+        }
+        return;
+    }
     for (int c0 = b; c0 < e; c0 += G) {
         const int kk = c0 + lane < e ? key[c0 + lane] : -1;
         const bool mine = kk >= 0 && (kk & 1);
