@@ -163,6 +163,7 @@ __global__ __launch_bounds__(TPB) void k_sym_count(int n, int lg, int H, int shi
     int nterm = sym_walk<G>(lane, lg, min(b + w * per, e), min(b + (w + 1) * per, e), 0, Acol, Bptr, Bcol,
                                   [&](int, int, int, int len) { mb = max(mb, len); },
                                   [&](int, int, int, int c) {
+                                      if (full) return;  // (a full table is probed whole)
                                       bool fresh;
                                       full |= sym_insert(tab, H, shift, c, fresh) < 0;
                                       u += fresh;

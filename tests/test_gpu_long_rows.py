@@ -80,3 +80,23 @@ def test_star_setup_time():
         g.close()
     print(f"case star of {n} nodes: {1e3 * min(took):.1f} ms", flush=True)
     assert min(took) < 0.4
+
+
+@pytest.mark.parametrize("n", [6000, 9000])
+def test_hub_product_pattern_time(n):
+    """A chain whose nodes all have a weak link to one: the hub's rows of the Galerkin products
+    overflow the tables of the short rows.  (6000 nodes: symbolic phase about 9 ms; 80 ms with
+    every term probing a full table.)"""
+    from paper_2108_02054_amd import AMG
+    g = np.random.default_rng(2)
+    i = np.r_[np.arange(n - 1), np.zeros(n - 2, int)]
+    j = np.r_[np.arange(1, n), np.arange(2, n)]
+    A = laplacian(n, i, j, np.r_[g.uniform(0.5, 1.5, n - 1), np.full(n - 2, 1e-6)])
+    p, c, v = T(A.indptr.astype(np.int32)), T(A.indices.astype(np.int32)), T(A.data)
+    took = []
+    for _ in range(2):
+        h = AMG(p, c, v, aggregation=1)
+        took.append(h.phase_times()["symbolic"])
+        h.close()
+    print(f"case hub product of {n} nodes: symbolic {min(took):.1f} ms", flush=True)
+    assert min(took) < 40.0
