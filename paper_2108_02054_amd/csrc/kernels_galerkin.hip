@@ -412,8 +412,8 @@ __global__ __launch_bounds__(TPB) void k_galerkin_own(int nrows, int W, int last
                                                       const int* __restrict__ dpos, int kind, T omega,
                                                       T* __restrict__ m, T* __restrict__ Qval) {
     constexpr int S = TPB / G, E = S * U;  // groups, entries per chunk
-    extern __shared__ __align__(16) unsigned char own_smem[];
-    T* prod = reinterpret_cast<T*>(own_smem);  // two chunks of products, then of L values
+    extern __shared__ __align__(16) unsigned char own_lds[];
+    T* prod = reinterpret_cast<T*>(own_lds);  // two chunks of products, then of L values
     T* elv = prod + (size_t)2 * E * W;
     const int g = threadIdx.x & (G - 1), sub = threadIdx.x / G;
     const int row = blockIdx.x;
@@ -563,7 +563,7 @@ constexpr double TPL2_LONG = 44.0;
 // leave the device half empty (A P of 24078 rows 40 -> 25 us; of 46669 rows 47 us both ways).
 constexpr int32_t LANES8_ROWS = 1 << 15;
 constexpr int64_t OWN_BYTES = 64 << 20;
-constexpr int OWN_LEN_MAX = 248;  // two chunks of 16 products per position within 64 KiB
+constexpr int OWN_LEN_MAX = 248;  // (own_smem with four entries per group: 63744 bytes in FP64)
 constexpr int64_t OWN_ROWS_WG = 1024, OWN_ROWS = 4096;
 GalShape pick_galerkin_shape(int32_t nrows, int64_t nnzL, int64_t terms, int maxlen, int gforce, int tforce) {
     if (maxlen > WF_CAP_MAX) return {};
@@ -652,14 +652,16 @@ static void launch_own(const Csr& L, const Csr& B, const Csr& C, const GalShape&
                                     C.v<T>(), gs.inv, dp, kind, (T)omega, m, q);
     };
     if (gs.own_rows == TPB) {
-        const int u = k > 2 ? 4 : 8;
-        const size_t sm = (size_t)2 * (TPB / gs.own) * u * (gs.inv_w + 1) * sizeof(T);
+        const int u = own_entries(gs.own, gs.inv_w, sizeof(T));
+        const size_t sm = (size_t)own_smem(gs.own, gs.inv_w, u, sizeof(T));
+        if (sm > OWN_SMEM_MAX) throw Fail{AMG_ERR_ARG, "row too long for the owner form"};
         const unsigned nbk = (unsigned)L.nrows;
         if (gs.own == 8) go(k_galerkin_own<T, 8, 1, 8>, nbk, sm);
         else if (gs.own == 16) go(k_galerkin_own<T, 16, 1, 8>, nbk, sm);
         else if (gs.own == 32) go(k_galerkin_own<T, 32, 1, 8>, nbk, sm);
         else if (k == 1) go(k_galerkin_own<T, 64, 1, 8>, nbk, sm);
-        else if (k == 2) go(k_galerkin_own<T, 64, 2, 8>, nbk, sm);
+        else if (k == 2 && u == 8) go(k_galerkin_own<T, 64, 2, 8>, nbk, sm);
+        else if (k == 2) go(k_galerkin_own<T, 64, 2, 4>, nbk, sm);
         else go(k_galerkin_own<T, 64, 4, 4>, nbk, sm);
     } else {
         const unsigned nbk = row_blocks(L.nrows, gs.own);
