@@ -1054,6 +1054,7 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
     c->lv[0].A = A0;
     c->outer_val = A0.val;
     c->phase_pending = false;
+    c->node_sweeps = std::getenv("AMGMI_NO_NODE_SWEEPS") == nullptr;
     std::vector<char> smoothed;  // levels whose A P kernel formed the smoother diagonal
 
     for (int l = 0;; ++l) {
@@ -1412,7 +1413,7 @@ T* vcycle_level_block(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* e
         int c_ready = 0;
         {
             Trace tr(c, AMG_K_RESTRICT, l);
-            if (l + 2 < (int)c->lv.size() && p.npre > 0 &&
+            if (l + 2 < (int)c->lv.size() && p.npre > 0 && c->node_sweeps &&
                 launch_spmv_nodes<T>(L.R, B, rres, (T*)C.f, C.mv<T>(), (T*)C.u, s))
                 c_ready = 1;
             else
@@ -1709,7 +1710,7 @@ amg_status pcg(amg_ctx* c, const double* f, double* u, amg_solve_info* info) {
     const bool fuse_dia = !mixed(c) && c->dia.ndiag > 0 && p.npre == 1 && c->lv.size() > 1;
     const bool fuse_cast = mixed(c);
     const bool fuse_sweep = !mixed(c) && p.npre > 0 && c->lv.size() > 1 &&
-                            (p.block_size & (p.block_size - 1)) == 0;  // level 0 in CSR
+                            (p.block_size == 1 || (c->node_sweeps && (p.block_size & (p.block_size - 1)) == 0));  // level 0 in CSR
     precondition(1, 0);
     double* pold = c->pa;
     double* pnew = c->pb;

@@ -749,6 +749,9 @@ struct amg_ctx {
     // mixed precision: the last level-0 sweep writes z in FP64 with r.z (off with
     // AMGMI_NO_RZ32: a separate widening pass)
     bool rz32 = true;
+    // block systems: the restriction and the CG update form the next first sweep u = M f (off
+    // with AMGMI_NO_NODE_SWEEPS: a pass of its own, the same sums)
+    bool node_sweeps = true;
     // the cycles of this solve keep the coarse correction and the post-sweep apart (BiCGStab)
     bool post_sweeps = false;
     bool broken = false;

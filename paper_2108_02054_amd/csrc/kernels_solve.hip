@@ -260,6 +260,7 @@ __global__ __launch_bounds__(RB_THREADS) void k_rb_spmv(int n, int rpb, const in
         if (own) sy[r] = v;
         __syncthreads();
         if (own) {
+#pragma clang fp contract(off)  // the sum of the block product's own pass, bit for bit
             T s = 0;
 #pragma unroll
             for (int q = 0; q < B; ++q) s = s + mi[q] * sy[r - r % B + q];
@@ -2293,6 +2294,7 @@ __global__ __launch_bounds__(TPB) void k_cg_update(int n, const double* __restri
         if constexpr (B == 1) {
             if (m != nullptr) u[i] = m[i] * ri;
         } else {  // (n and the stride are multiples of B: a node's lanes are in the loop together)
+#pragma clang fp contract(off)  // as in k_rb_spmv
             const int base = (int)threadIdx.x & 63 & ~(B - 1);
             double s = 0;
 #pragma unroll

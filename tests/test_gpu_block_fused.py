@@ -67,3 +67,27 @@ def test_block_cycle_fused(monkeypatch, bs, opts, isolated):
             assert np.linalg.norm(f - A @ ug.cpu().numpy()) <= 2e-8 * np.linalg.norm(f)
     g.close()
     h.close()
+
+
+# the sweep that a restriction (levels below 0) and a CG update (level 0) form, and the pass
+# that forms it where they cannot, add the same products in the same order, each rounded
+@pytest.mark.parametrize("bs", [2, 4, 8])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_first_sweeps_bit_for_bit(monkeypatch, bs, precision):
+    from paper_2108_02054_amd import AMG
+    p, c, v = system(bs, True)
+    n = len(p) - 1
+    f = np.random.default_rng(8).uniform(-1.0, 1.0, n)
+    print(f"case first sweeps bs={bs} precision={precision}", flush=True)
+    got = []
+    for apart in (False, True):
+        if apart:
+            monkeypatch.setenv("AMGMI_NO_NODE_SWEEPS", "1")
+        g = AMG(T(p), T(c), T(v), block_size=bs, aggregation=1, coarse_enough=12 * bs, precision=precision)
+        assert g.num_levels >= 3
+        z = g.vcycle(T(f)).cpu().numpy()
+        u, i = g.solve(T(f))
+        got.append((z, u.cpu().numpy(), i))
+        g.close()
+    assert np.array_equal(got[0][0], got[1][0])
+    assert got[0][2] == got[1][2] and np.array_equal(got[0][1], got[1][1])
