@@ -753,6 +753,8 @@ void configure_tail(amg_ctx* c) {
         c->tail = t;
     }
     if (c->tail == nlev - 1 && c->lv.back().A.nrows > solo) c->tail = 0;
+    // the tail's own cycle prolongs and sweeps in LDS
+    for (int t = c->tail; t > 0 && t < nlev; ++t) release_correction(c, c->lv[(size_t)t]);
 }
 
 // Diagonal storage of A_0 when its pattern has at most DIA_MAX distinct column offsets

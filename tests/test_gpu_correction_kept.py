@@ -1,0 +1,60 @@
+"""Q_l = (I - M_l A_l) P_l is kept and formed only where a V-cycle reads it."""
+import gc
+
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import T
+from workloads import two_fluid_7pt
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def no_garbage():
+    """Device memory held by reference cycles of an earlier test is given back first."""
+    gc.collect()
+    yield
+    gc.collect()
+
+
+def live_sizes():
+    from paper_2108_02054_amd.amg import ALLOC_FN, FREE_FN
+    live = {}
+
+    def a(nbytes, stream, user):
+        p = torch.cuda.caching_allocator_alloc(int(nbytes), device=0, stream=int(stream or 0))
+        live[p] = int(nbytes)
+        return p
+
+    def f(ptr, nbytes, stream, user):
+        del live[int(ptr)]
+        torch.cuda.caching_allocator_delete(int(ptr))
+    return live, (ALLOC_FN(a), FREE_FN(f))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("changed", [False, True])
+def test_not_in_the_coarse_tail(precision, changed):
+    """Levels of the one-workgroup tail hold A P's values once, the others twice (with Q's)."""
+    from paper_2108_02054_amd import AMG
+    p, c, v = two_fluid_7pt(23, 0.4)
+    live, cb = live_sizes()
+    print(f"case correction outside the tail precision={precision} changed={changed}", flush=True)
+    g = AMG(T(p), T(c), T(v), allocator=cb, coarse_enough=20, precision=precision)
+    if changed:
+        g.set_pattern(T(p), T(c))
+        g.rebuild(T(v), pattern_changed=True)
+    torch.cuda.synchronize()
+    size = 4 if precision else 8
+    levels = [(g.level_storage(l)["tail"], g.dims(l)[4]) for l in range(g.num_levels - 1)]
+    assert {t for t, _ in levels} == {0, 1}
+    for tail, nnz in levels:
+        # A P's values (in FP32 also its columns are of that size), and Q's
+        assert sum(b == size * nnz for b in live.values()) == 1 + precision + (0 if tail else 1), (tail, nnz)
+    f = T(np.random.default_rng(1).uniform(-1, 1, len(p) - 1))
+    g.rebuild(T(1.5 * v))
+    u, info = g.solve(f)
+    assert info["converged"]
+    g.close()
