@@ -862,6 +862,10 @@ void partial_rebuild(amg_ctx* c, const double* val) {
     const int nlev = (int)c->lv.size();
     std::vector<char> smoothed((size_t)nlev, 0);
     const bool blocked = c->prm.block_size > 1;
+    // Q_l is formed unless all that ran since the last update were solves that read none
+    if (c->q_read || c->q_swept) c->q_keep = c->q_read;
+    c->q_read = c->q_swept = false;
+    c->q_formed = c->q_keep;
     // Ingest: the level-0 staged A P kernel takes the new values straight from the caller's
     // array and stores the hierarchy's copies (FP64, and FP32 in mixed precision) as it
     // reads them; otherwise they are copied first.
@@ -893,7 +897,7 @@ void partial_rebuild(amg_ctx* c, const double* val) {
                                                      c->prm.jacobi_omega, blocked ? nullptr : L.mv<T>(),
                                                      (l == 0 && !ingested) ? val : nullptr, s,
                                                      (l == 0 && direct) ? &c->dia : nullptr,
-                                                     blocked ? nullptr : L.Q.v<T>());
+                                                     blocked || !c->q_formed ? nullptr : L.Q.v<T>());
             smoothed[(size_t)l] = fused && !blocked;
         }
         Trace tr(c, AMG_K_GALERKIN_RAP, l);
@@ -934,6 +938,29 @@ void partial_rebuild(amg_ctx* c, const double* val) {
         c->cinv_pending = true;
     }
     c->phase_pending = true;
+}
+
+// For cycles that read Q_l after an update that left it out: A_l P_l is formed once more with
+// Q_l beside it, bit for bit what the update writes.
+template <typename T>
+void form_corrections(amg_ctx* c) {
+    for (const Level& L : c->lv) {
+        if (L.Q.nrows == 0) continue;
+        if (&L == &c->lv[0]) ensure_a0_csr(c);
+        Trace tr(c, AMG_K_GALERKIN_AP, (int)(&L - &c->lv[0]));
+        launch_galerkin_ap<T>(L.A, L.P, L.AP, L.gAP, L.galAP, c->prm.smoother, c->prm.jacobi_omega, L.mv<T>(),
+                              nullptr, c->stream, nullptr, L.Q.v<T>());
+    }
+}
+
+void want_corrections(amg_ctx* c) {
+    c->q_read = true;
+    if (c->q_formed) return;
+    if (mixed(c))
+        form_corrections<float>(c);
+    else
+        form_corrections<double>(c);
+    c->q_formed = true;
 }
 
 void partial_any(amg_ctx* c, const double* val) {
@@ -1051,6 +1078,7 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
     c->cwork = nullptr;
     c->dia = Dia{};  // its arrays were hierarchy allocations
     c->a0_csr_stale = false;
+    c->q_formed = true;
     c->tail = 0;
     c->lv.emplace_back();
     c->lv[0].A = A0;
@@ -1646,6 +1674,7 @@ amg_status pcg(amg_ctx* c, const double* f, double* u, amg_solve_info* info) {
     const int n = L0.A.nrows;
     const amg_params& p = c->prm;
     amg_solve_info inf{0, 0, 0.0};
+    want_corrections(c);
     // the CG residual; the fused update writes the new one to the other buffer
     double* rc = c->r;
     double* ra = c->r2;
@@ -1844,6 +1873,10 @@ amg_status bicgstab(amg_ctx* c, const double* f, double* u, amg_solve_info* info
         ~Post() { c->post_sweeps = false; }
     } post{c};
     c->post_sweeps = mixed(c) || prm.aggregation == 1;
+    if (c->post_sweeps)
+        c->q_swept = true;
+    else
+        want_corrections(c);
     Csr Aout = L0.A;  // the Krylov operator: the hierarchy's pattern, the outer values
     Aout.val = c->outer_val;
     // y = A x: on the diagonal storage when it holds the Krylov operator (the Krylov SpMV
@@ -2379,6 +2412,7 @@ double* scratch_on(int dev) {
 amg_status amg_vcycle(amg_ctx* c, const double* r, double* z) {
     if (!c || !r || !z) return AMG_ERR_ARG;
     return guard(c, [&] {
+        want_corrections(c);
         vcycle_apply(c, r, z);
         return AMG_OK;
     });

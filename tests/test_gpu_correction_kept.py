@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from tests.dense import random_spd_graph
 from tests.gpu_util import T
 from workloads import two_fluid_7pt
 
@@ -58,3 +59,51 @@ def test_not_in_the_coarse_tail(precision, changed):
     u, info = g.solve(f)
     assert info["converged"]
     g.close()
+
+
+# a stencil (level 0 in diagonal storage, its CSR values formed again on demand), and a general
+# matrix; plain aggregation and an FP32 hierarchy, whose BiCGStab sweeps apart
+@pytest.mark.parametrize("stencil", [True, False])
+@pytest.mark.parametrize("opts", [dict(aggregation=1), dict(precision=1), dict(aggregation=1, precision=1, npost=2),
+                                  dict(aggregation=1, smoother=1), dict(precision=1, aggregation=1, smoother=1)])
+def test_updates_between_bicgstab_solves(stencil, opts):
+    """They leave Q out; the first V-cycle or CG after them forms it, and what follows is bit for
+    bit that of a handle that has run no BiCGStab."""
+    from paper_2108_02054_amd import AMG
+    p, c, v = two_fluid_7pt(21, 0.4) if stencil else random_spd_graph(4000, 5, 3)
+    n = len(p) - 1
+    f = T(np.random.default_rng(2).uniform(-1, 1, n))
+    print(f"case corrections between BiCGStab solves stencil={stencil} {opts}", flush=True)
+    a = AMG(T(p), T(c), T(v), coarse_enough=60, **opts)
+    b = AMG(T(p), T(c), T(v), coarse_enough=60, **opts)
+    products = lambda: a.trace_read().get("galerkin_ap", (0, 0))[1]  # noqa: E731
+    levels = a.num_levels - 1
+    tails = sum(a.level_storage(l)["tail"] for l in range(levels))
+    a.trace(["galerkin_ap"], level=-1)
+    for step in range(1, 4):
+        w = T((1.0 + 0.3 * step) * v)
+        a.rebuild(T((1.0 + 0.2 * step) * v))
+        products()
+        _, info = a.solve_bicgstab(f)
+        assert info["converged"] and products() == 0
+        a.rebuild(w)
+        b.rebuild(w)
+        assert products() == levels
+        if step == 2:  # straight to CG
+            ua, ia = a.solve(f)
+            assert products() == levels - tails
+            ub, ib = b.solve(f)
+            assert ia == ib and torch.equal(ua, ub)
+        else:
+            assert torch.equal(a.vcycle(f), b.vcycle(f))
+            assert products() == levels - tails
+        assert torch.equal(a.vcycle(f), b.vcycle(f)) and products() == 0
+        w = T((1.0 + 0.4 * step) * v)  # an update after such a cycle brings Q itself
+        a.rebuild(w)
+        b.rebuild(w)
+        assert torch.equal(a.vcycle(f), b.vcycle(f)) and products() == levels
+        a.solve_bicgstab(f)  # both kinds of solve on the same values: the update brings Q
+        a.rebuild(w)
+        assert torch.equal(a.vcycle(f), b.vcycle(f)) and products() == levels
+    a.close()
+    b.close()
