@@ -172,25 +172,29 @@ class ByteModel:
     and their values (8 B FP64, 4 B FP32); an operator in diagonal storage counts its
     values only, with symmetric values only the main and upper diagonals; an operator of
     full B x B blocks one index per block and one pointer per node (its Krylov SpMV).
-    post: the levels whose prolongation and post-sweep are one pass over Q_l = (I - M A) P
-    (A_l P_l's pattern), traced as "prolong" with no "jacobi" launches."""
+    march: level 0 runs the marching kernels with damped Jacobi, whose diagonal they form from
+    the main diagonal of A_0 and do not read.  post: the levels whose prolongation and
+    post-sweep are one pass over Q_l = (I - M A) P (A_l P_l's pattern), traced as "prolong"
+    with no "jacobi" launches."""
 
     post = frozenset()
 
-    def __init__(self, dims, storage, ndiag=0, nread=0, block=1):
+    def __init__(self, dims, storage, ndiag=0, nread=0, block=1, march=False):
         self.L = len(dims)
         self.dims = dims
         self.st = storage
         self.ndiag = ndiag
         self.nread = nread
         self.block = block
+        self.march = march
         self.s = self.st[0]["value_bytes"]
 
     @classmethod
     def of(cls, amg, block=1):
         L = amg.num_levels
         return cls([amg.dims(l) for l in range(L)], [amg.level_storage(l) for l in range(L)],
-                   amg.level_format(0), amg.diagonals_read(0), block)
+                   amg.level_format(0), amg.diagonals_read(0), block,
+                   march=amg.march_plane(0) > 0 and amg.params.smoother == 0)
 
     def _csr(self, rows, nnz, c16, rpb, s):
         cols = 2 * nnz + (4 * ((rows + rpb - 1) // rpb) if rpb > 0 else 0) if c16 else 4 * nnz
@@ -223,7 +227,7 @@ class ByteModel:
         if self.block > 1:
             B = self.block
             return 4 * (n // B + 1) + 4 * (nnz // (B * B)) + 8 * nnz
-        return 4 * (n + 1) + 4 * nnz + 8 * nnz
+        return self._csr(n, nnz, self.st[0]["A_c16"], self.st[0]["A_rpb"], 8)
 
     def galerkin(self, l):
         """A_l, P_l, R_l read once, A_{l+1} written once with its cached columns read once
@@ -252,19 +256,19 @@ class ByteModel:
                 return self.krylov_A() + 16 * n
             return self.krylov_A() + 32 * n      # z, p_old read; p_new, q written
         if cls == "cg_update" and l == 0:
-            # fused with the first sweep and its residual (the marching kernels read no m: they
-            # form damped Jacobi's from the main diagonal, and move 8 n bytes fewer)
+            # fused with the first sweep and its residual: p, q, x, r and m read, x, r, u and
+            # the residual written
             if self.ndiag > 0 and s == 8:
-                return 8 * self.a0_entries() + 72 * n
+                return 8 * self.a0_entries() + (64 if self.march else 72) * n
             return 48 * n if s == 8 else None
         if cls == "cg_rz" and l == 0:
             return 16 * n
         if cls == "jacobi" and l < last:          # u' = u + m (f - A u); level 0: + r.z
-            return self.A(l) + 4 * s * n
+            return self.A(l) + (3 if l == 0 and self.march else 4) * s * n
         if cls == "smooth0_res" and l < last:
             # level 0: u = m f and r = f - A u; below, the restriction formed u and the
             # kernel forms the residual (f, u read, r written)
-            return self.A(l) + (4 if l == 0 else 3) * s * n
+            return self.A(l) + (4 if l == 0 and not self.march else 3) * s * n
         if cls == "restrict" and l < last:
             smooths = (l + 2 < self.L) and not self.st[l + 1]["tail"]
             return self.R(l) + s * n + s * nc + (2 * s * nc if smooths else 0)

@@ -66,6 +66,34 @@ def test_transfer_and_level_bytes():
     assert m.bytes("tail", 3) is None
 
 
+def test_marching_kernels_read_no_smoother_array():
+    """Damped Jacobi on the marching kernels: omega / a_ii comes from the main diagonal that the
+    operator's entries count already."""
+    b = _bench()
+    n, a0 = N0, 8 * ((NNZ0 + N0) // 2)
+    m = b.ByteModel(DIMS, [_st() for _ in DIMS], ndiag=7, nread=4, march=True)
+    # p, q, x, r read; x, r, u and the residual written
+    assert m.bytes("cg_update", 0) == a0 + 64 * n
+    assert abs(m.bytes("cg_update", 0) / 1e6 - 200.9) < 0.1
+    assert m.bytes("jacobi", 0) == a0 + 24 * n        # r, u read; z written
+    assert m.bytes("smooth0_res", 0) == a0 + 24 * n   # f read; u, r written
+    assert m.bytes("cg_pq", 0) == a0 + 32 * n
+    # the levels below and other smoothers read their array
+    plain = b.ByteModel(DIMS, [_st() for _ in DIMS], ndiag=7, nread=4)
+    assert m.bytes("jacobi", 1) == plain.bytes("jacobi", 1)
+    assert plain.bytes("jacobi", 0) == a0 + 32 * n
+    half = b.ByteModel(DIMS, [_st(s=4) for _ in DIMS], ndiag=7, nread=4, march=True)
+    assert half.bytes("smooth0_res", 0) == a0 // 2 + 12 * n
+
+
+def test_general_krylov_operator_with_two_byte_columns():
+    """The Krylov SpMV of a level 0 in CSR reads two-byte columns where the level keeps them."""
+    b = _bench()
+    st = [_st(c16=(1, 0, 0), rpb=(64, 256, 32))] + [_st() for _ in DIMS[1:]]
+    m = b.ByteModel(DIMS, st)
+    assert m.bytes("cg_pq", 0) == 4 * (N0 + 1) + 2 * NNZ0 + 4 * (N0 // 64) + 8 * NNZ0 + 32 * N0
+
+
 def test_galerkin_bytes():
     b = _bench()
     m = b.ByteModel(DIMS, [_st() for _ in DIMS], ndiag=7, nread=4)
