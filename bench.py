@@ -896,7 +896,7 @@ def main():
         "config": {"workload": res["work"],
                    "grid": N, "n": n, "nnz": nnz, "levels": res["levels"], "level_rows": [d[0] for d in dims],
                    "level_nnz": [d[1] for d in dims],
-                   "level0_storage": ((f"{res['ndiag']} diagonals, {res['nread']} read per row"
+                   "level0_storage": ((f"{res['ndiag']} diagonals, {res['nread']} of them hold all values"
                                        + (f", marching planes of {res['plane']} rows" if res["plane"] else ""))
                                       if res["ndiag"] else "CSR"),
                    "parallelism": "single GPU"},

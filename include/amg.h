@@ -248,11 +248,12 @@ amg_status amg_level_dims(const amg_ctx* c, int l, int64_t* dims);
  * stored diagonals when the level is kept in diagonal storage (the finest level of a
  * stencil operator: at most 32 distinct column offsets, well filled; the values are
  * refreshed from the CSR copy after every rebuild), or 0 when the CSR kernels are used.
- * *nread (host, may be NULL) receives the number of diagonals the solve kernels read per
- * row: (ndiag+1)/2 when the offsets are symmetric and the values last refreshed were
- * found symmetric (the solve reads each sub-diagonal entry as its mirror; known from a
- * setup on, and from the first solve after a rebuild on; the windowed kernels of grids
- * whose diagonals fit in the L2 caches read the stored entries all the same), else ndiag.
+ * *nread (host, may be NULL) receives the number of diagonals that hold all its values:
+ * (ndiag+1)/2 when the offsets are symmetric and the values last refreshed were found
+ * symmetric (known from a setup on, and from the first solve after a rebuild on), else
+ * ndiag.  The solve kernels then read that many per row, each sub-diagonal entry as its
+ * mirror; the windowed kernels of grids whose diagonals fit in the L2 caches (27-point: up to
+ * 51^3 rows in FP64, 64^3 in FP32) and captured calls of the operator read all ndiag stored ones.
  * *plane (host, may be NULL) receives the plane stride a when the level-0 kernels of a
  * 7-point operator (offsets -a, -b, -1, 0, 1, b, a) walk the grid plane by plane (two planes
  * per workgroup, neighbours within a plane from LDS), else 0.

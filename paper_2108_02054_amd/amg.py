@@ -332,8 +332,9 @@ class AMG:
         return nd.value
 
     def diagonals_read(self, l: int) -> int:
-        """Diagonals the solve kernels read per row of level l's diagonal storage: half of
-        them (plus the main one) once a solve has seen symmetric values."""
+        """Diagonals that hold all values of level l's diagonal storage: half of them (plus the
+        main one) where the values were found symmetric, by the setup or by the first solve
+        after an update.  The solve kernels read as many, except on small windowed grids."""
         nd, nr = C.c_int(), C.c_int()
         self._check(lib().amg_level_format(self.ctx, l, C.byref(nd), C.byref(nr), None))
         return nr.value

@@ -1582,12 +1582,7 @@ inline unsigned win_bytes(const Dia& D) {
 // FP32 first sweep + residual 89 against 106 us, FP32 sweep 82 against 96, FP64 last
 // sweep + r.z 157 against 172), so the windows are then used for all.
 //
-// With symmetric values half of the diagonals are read, twice each, the mirrored time at an
-// odd offset.  Where all of them fit in the L2s (8 x 4 MB) the full read, bit for bit the same
-// sums, is faster: 27-point Krylov SpMV 7.5 against 8.5 us at 44^3 and 9.6 against 9.2 at
-// 52^3 (30 MB); update and solve 1.29 against 1.31 ms at 44^3, with an FP32 hierarchy 1.70
-// against 1.73 at 56^3 and 1.97 against 1.96 at 64^3 (28 MB).
-constexpr int64_t WIN_FULL_BYTES = 28 << 20;
+// Symmetric values on a large grid: half of the diagonals are read (window_reads_half).
 template <typename T, typename F>
 inline bool win_call(const Dia& D, F&& f, bool gains = false) {
     const int rows = win_rows_per_thread<T>(D);
@@ -1602,7 +1597,7 @@ inline bool win_call(const Dia& D, F&& f, bool gains = false) {
             f(std::integral_constant<int, 0>{}, S, std::integral_constant<int, 1>{});
         }
     };
-    if (D.off.sym && (int64_t)D.rows * D.ndiag * (int64_t)sizeof(T) > WIN_FULL_BYTES)
+    if (D.off.sym && window_reads_half(D.rows, D.ndiag, sizeof(T)))
         with_nd(std::true_type{});
     else
         with_nd(std::false_type{});

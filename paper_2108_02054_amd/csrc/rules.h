@@ -29,4 +29,14 @@ constexpr int own_entries(int lanes, int w, int bytes) {
     return w <= 128 && own_smem(lanes, w, 8, bytes) <= OWN_SMEM_MAX ? 8 : 4;
 }
 
+// Windowed kernels, symmetric values: whether half of the diagonals are read, twice each, the
+// mirrored time at an odd offset.  Where all of them fit in the L2s (8 x 4 MB) the full read,
+// bit for bit the same sums, is faster: 27-point Krylov SpMV 7.5 against 8.5 us at 44^3 and 9.6
+// against 9.2 at 52^3 (30 MB); update and solve 1.29 against 1.31 ms at 44^3, with an FP32
+// hierarchy 1.70 against 1.73 at 56^3 and 1.97 against 1.96 at 64^3 (28 MB).
+constexpr long long WIN_FULL_BYTES = 28 << 20;
+constexpr bool window_reads_half(int rows, int ndiag, int bytes) {
+    return (long long)rows * ndiag * bytes > WIN_FULL_BYTES;
+}
+
 }  // namespace amgmi

@@ -62,3 +62,14 @@ def test_owner_form_fits_its_lds(tmp_path):
             if w > 128:
                 lines.append(f"own_entries({lanes}, {w}, {size}) == 4")  # four positions per lane: four entries
     assert holds(lines, tmp_path) is None
+
+
+def test_window_reads_half_above_the_caches(tmp_path):
+    """27 diagonals: all read up to 51^3 rows in FP64 and 63^3 in FP32, half of a symmetric
+    operator's from 52^3 and 65^3 on; the products leave 32 bits."""
+    lines = []
+    for bytes_, last, first in ((8, 51, 52), (4, 63, 65)):
+        lines += [f"!window_reads_half({last**3}, 27, {bytes_})", f"window_reads_half({first**3}, 27, {bytes_})",
+                  f"window_reads_half({2**31 // 27}, 27, {bytes_})"]
+    lines += ["!window_reads_half(135926, 27, 8)", "window_reads_half(135927, 27, 8)"]
+    assert holds(lines, tmp_path) is None
