@@ -451,6 +451,7 @@ struct GalForce {
     int lanes = 0;  // 1: lane-group kernels
     int wide = 0;   // 1: two-byte positions
     int pos = 0;    // 1: position-map form also for small products
+    int own = 0;    // 1: a small product that does not take the owner form is an error
     int g = 0;
     int t = 0;      // B terms per lane and entry (1 or 2)
 };
@@ -461,6 +462,7 @@ GalForce galerkin_force() {
     if (std::strncmp(e, "lanes", 5) == 0) f.lanes = 1;
     if (std::strncmp(e, "pos16", 5) == 0) f.wide = 1;
     if (std::strncmp(e, "pos", 3) == 0) f.pos = 1;
+    if (std::strncmp(e, "own", 3) == 0) f.own = 1;
     if (const char* c = std::strchr(e, ':')) {
         f.g = std::atoi(c + 1);
         if (const char* c2 = std::strchr(c + 1, ':')) f.t = std::atoi(c2 + 1);
@@ -642,6 +644,8 @@ GalShape plan_product(amg_ctx* c, const Csr& L, const Csr& B, Csr& C, bool diag,
         gs.terms = z.terms;
         gs.inv = halloc<uint8_t>(c, (size_t)L.nnz * gs.inv_w);
         gs.bst = halloc<int32_t>(c, (size_t)std::max<int64_t>(L.nnz, 1));
+    } else if (f.own && own) {
+        throw Fail{AMG_ERR_ARG, "a product of " + std::to_string(L.nrows) + " rows does not take the owner form"};
     } else if (plan && galerkin_terms_fit(z.max_terms)) {
         gs = pick_galerkin_shape(L.nrows, L.nnz, z.terms, z.maxlen, f.g, f.t);
     }

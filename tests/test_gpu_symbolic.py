@@ -6,6 +6,7 @@ import gc
 import numpy as np
 import pytest
 import scipy.sparse as sp
+import torch
 
 from tests.gpu_util import T, rel_max
 
@@ -259,3 +260,59 @@ def test_products_of_long_rows_two_terms_per_lane(monkeypatch, N):
         g.close()
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+# on level 1 a workgroup per row up to 1024 rows, G lanes per row up to 4096; rows of 8 to 248
+# columns (8, 16, 32 and 64 lanes; one, two and four positions per lane)
+@pytest.mark.parametrize("rows,per_row,couplings,span", [
+    (60, 2, 6, 9), (300, 3, 6, 20), (300, 12, 40, 120), (300, 30, 60, 240), (1024, 2, 5, 30),
+    (1025, 2, 5, 30), (2000, 12, 30, 130), (4096, 3, 4, 40)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_owner_form_correction(monkeypatch, rows, per_row, couplings, span, precision):
+    """Q = (I - M A) P as the owner form writes it, through the V-cycle that reads it: bit for
+    bit the position-map form's.  (The form is demanded: another one would be an error.)"""
+    from paper_2108_02054_amd import AMG
+    g = np.random.default_rng(rows + span)
+    n, mid = 6 * rows, rows
+    near = lambda a, d, m: np.clip(a + g.integers(-d, d + 1, len(a)), 0, m - 1)  # noqa: E731
+    A = spd_from(n, np.repeat(np.arange(n), 3), near(np.repeat(np.arange(n), 3), 8, n), 3)
+
+    def spread(n, nc, per_row, reach):
+        agg = np.arange(n) * nc // n
+        r = np.repeat(np.arange(n), per_row)
+        P = sp.coo_matrix((np.ones(len(r) + n), (np.r_[r, np.arange(n)], np.r_[near(agg[r], reach, nc), agg])),
+                          shape=(n, nc)).tocsr()
+        P.data[:] = g.uniform(0.2, 1.0, P.nnz)
+        P.sort_indices()
+        return P
+
+    Ps = [spread(n, mid, per_row, span // 4), spread(mid, max(2, mid // 3), 2, max(1, span // 8))]
+    f = T(g.uniform(-1, 1, n))
+    monkeypatch.setenv("AMGMI_POST", "fused")
+    print(f"case owner form correction rows={rows} span={span} precision={precision}", flush=True)
+    got = []
+    for form in ("own", "pos"):
+        monkeypatch.setenv("AMGMI_GALERKIN", form)
+        h = AMG(T(A.indptr.astype(np.int32)), T(A.indices.astype(np.int32)), T(A.data), precision=precision,
+                smoother=rows % 2, transfer=[(T(P.indptr.astype(np.int32)), T(P.indices.astype(np.int32)), T(P.data),
+                                              P.shape[1]) for P in Ps])
+        z0 = h.vcycle(f)
+        h.rebuild(T(1.25 * A.data))
+        got.append((z0, h.vcycle(f)))
+        h.close()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert bool(torch.isfinite(got[0][1]).all())
+
+
+def test_owner_form_is_demanded(monkeypatch):
+    """One row more than the form takes."""
+    from paper_2108_02054_amd import AMG, AmgError
+    n = 3 * 4097
+    A = spd_from(n, np.arange(n - 1), np.arange(1, n), 4)
+    P = sp.csr_matrix((np.ones(n), np.arange(n) // 3, np.arange(n + 1)), shape=(n, 4097))
+    P2 = sp.csr_matrix((np.ones(4097), np.arange(4097) // 9, np.arange(4098)), shape=(4097, 456))
+    monkeypatch.setenv("AMGMI_GALERKIN", "own")
+    with pytest.raises(AmgError, match="owner form"):
+        AMG(T(A.indptr.astype(np.int32)), T(A.indices.astype(np.int32)), T(A.data),
+            transfer=[(T(M.indptr.astype(np.int32)), T(M.indices.astype(np.int32)), T(M.data), M.shape[1])
+                      for M in (P, P2)])
