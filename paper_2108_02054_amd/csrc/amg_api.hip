@@ -84,6 +84,8 @@ bool reclaim(DevMem& m, int round) {
     }
     return false;
 }
+
+bool give_back(DevMem& m) { return m.give_back != nullptr && m.give_back(m.give_back_arg); }
 }  // namespace
 
 MemScope::MemScope(DevMem* m) : prev(g_mem) { g_mem = m; }
@@ -151,6 +153,7 @@ void* dalloc(size_t bytes, hipStream_t s) {
     }
     if (m->hook_alloc) {
         void* p = m->hook_alloc(bytes, (void*)m->s, m->hook_user);
+        while (!p && give_back(*m)) p = m->hook_alloc(bytes, (void*)m->s, m->hook_user);
         if (!p) throw Fail{AMG_ERR_OOM, "the caller's allocator returned no block of " + std::to_string(bytes) + " bytes"};
         std::lock_guard<std::mutex> lk(m->mu);
         m->live.emplace(p, bytes);
@@ -176,6 +179,11 @@ void* dalloc(size_t bytes, hipStream_t s) {
     hipError_t e = pool_alloc(*m, &p, bytes);
     for (int round = 0; e == hipErrorOutOfMemory && reclaim(*m, round); ++round) {
         (void)hipGetLastError();
+        e = pool_alloc(*m, &p, bytes);
+    }
+    while (e == hipErrorOutOfMemory && give_back(*m)) {
+        (void)hipGetLastError();
+        reclaim(*m, 0);
         e = pool_alloc(*m, &p, bytes);
     }
     if (e == hipErrorOutOfMemory) {
@@ -672,6 +680,18 @@ void release_correction(amg_ctx* c, Level& L) {
     L.Q = Csr{};
 }
 
+// What the context can do without when memory runs out: the levels then prolong and sweep
+// apart, and a system that fits without Q_l is not refused because of it.
+bool drop_corrections(void* ctx) {
+    amg_ctx* c = (amg_ctx*)ctx;
+    bool any = false;
+    for (Level& L : c->lv) {
+        any = any || L.Q.nrows > 0;
+        release_correction(c, L);
+    }
+    return any;
+}
+
 // The column offsets of A_0 when its pattern is a well-filled stencil (at most DIA_MAX
 // offsets): level 0 is then kept in diagonal storage.  Empty otherwise.
 void find_stencil(amg_ctx* c) {
@@ -720,16 +740,27 @@ void configure_level(amg_ctx* c, size_t l, Csr& next, hipStream_t s) {
     Q.val32 = nullptr;
     Q.c16 = nullptr;
     Q.cblk = nullptr;
-    std::vector<Csr*> ms{&L.P, &L.R, &next};
-    const bool corr = correction_pays(c, l);
-    if (corr) ms.push_back(&Q);
-    configure(c, ms, s);
-    if (!corr || Q.rpb == 0) return;
-    if (mixed(c))
-        Q.val32 = halloc<float>(c, (size_t)Q.nnz);
-    else
-        Q.val = halloc<double>(c, (size_t)Q.nnz);
-    L.Q = Q;
+    const std::vector<Csr*> ms{&L.P, &L.R, &next};
+    if (!correction_pays(c, l)) {
+        configure(c, ms, s);
+        return;
+    }
+    try {
+        std::vector<Csr*> with = ms;
+        with.push_back(&Q);
+        configure(c, with, s);
+        if (Q.rpb == 0) return;
+        if (mixed(c))
+            Q.val32 = halloc<float>(c, (size_t)Q.nnz);
+        else
+            Q.val = halloc<double>(c, (size_t)Q.nnz);
+        L.Q = Q;
+    } catch (const Fail& e) {  // no memory for Q_l: without it
+        if (e.st != AMG_ERR_OOM) throw;
+        release(c, Q.c16);
+        release(c, Q.cblk);
+        configure(c, ms, s);
+    }
 }
 
 // The fused coarse tail starts at the first level t >= 1 from which every level down to
@@ -1063,6 +1094,7 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
     const auto t_all = Clock::now();
     double ph[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 
+    drop_corrections(c);  // (their memory serves the copy, which the old arrays still stand beside)
     // Copy the input first: it may be the current hierarchy's own level-0 arrays.
     std::vector<void*> old = std::move(c->hier_allocs);
     c->hier_allocs.clear();
@@ -2091,6 +2123,8 @@ amg_ctx* create_ctx(const amg_params& p, void* stream) {
     try {
         HIP_CHECK(hipGetDevice(&c->device));
         mem_init(c->mem, c->stream, p.alloc, p.dealloc, p.alloc_user);
+        c->mem.give_back = drop_corrections;
+        c->mem.give_back_arg = c;
         MemScope scope(&c->mem);
         c->d_flags = oalloc<int>(c, F_COUNT);
         HIP_CHECK(hipHostMalloc((void**)&c->h_flags, F_COUNT * sizeof(int), hipHostMallocDefault));

@@ -56,6 +56,10 @@ struct DevMem {
     std::map<size_t, std::vector<void*>> kept;  // freed blocks by size class
     size_t live_bytes = 0, kept_bytes = 0, peak_bytes = 0;
     std::mutex mu;
+    // called when an allocation fails: frees what the context can do without, false when there
+    // is nothing (more)
+    bool (*give_back)(void*) = nullptr;
+    void* give_back_arg = nullptr;
 };
 
 // Allocations made between the construction and destruction of a MemScope use its DevMem

@@ -107,3 +107,60 @@ def test_updates_between_bicgstab_solves(stencil, opts):
         assert torch.equal(a.vcycle(f), b.vcycle(f)) and products() == levels
     a.close()
     b.close()
+
+
+def budget(limit):
+    """The caller's allocator with at most `limit` bytes out at a time; the most that were."""
+    from paper_2108_02054_amd.amg import ALLOC_FN, FREE_FN
+    st = dict(live=0, peak=0, refused=0)
+
+    def a(nbytes, stream, user):
+        if st["live"] + nbytes > limit:
+            st["refused"] += 1
+            return None
+        st["live"] += nbytes
+        st["peak"] = max(st["peak"], st["live"])
+        return torch.cuda.caching_allocator_alloc(int(nbytes), device=0, stream=int(stream or 0))
+
+    def f(ptr, nbytes, stream, user):
+        st["live"] -= nbytes
+        torch.cuda.caching_allocator_delete(int(ptr))
+    return st, (ALLOC_FN(a), FREE_FN(f))
+
+
+@pytest.mark.parametrize("kind,opts", [
+    ("stencil", dict()), ("stencil", dict(aggregation=1)), ("stencil", dict(precision=1, aggregation=1)),
+    ("graph", dict()), ("graph", dict(precision=1))])
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("bicgstab", [False, True])
+def test_not_refused_for_its_memory(monkeypatch, kind, opts, bicgstab, full):
+    """A series that fits in the memory of a hierarchy without Q is set up, updated and solved in
+    that memory, by a first setup and by a full rebuild."""
+    from paper_2108_02054_amd import AMG, FULL
+    p, c, v = two_fluid_7pt(40, 0.4) if kind == "stencil" else random_spd_graph(30000, 5, 3)
+    f = T(np.random.default_rng(4).uniform(-1, 1, len(p) - 1))
+    print(f"case memory without corrections {kind} {opts} bicgstab={bicgstab} full={full}", flush=True)
+
+    def series(limit):
+        st, cb = budget(limit)
+        g = AMG(T(p), T(c), T(v), allocator=cb, coarse_enough=200, **opts)
+        solve = lambda: (g.solve_bicgstab(f) if bicgstab else g.solve(f))[1]  # noqa: E731
+        g.rebuild(T(1.5 * v))
+        one = solve()
+        if full:
+            g.rebuild_ex(T(v), FULL)
+        two = solve()
+        assert bool(torch.isfinite(g.vcycle(f)).all())
+        g.close()
+        assert st["live"] == 0
+        return st, one, two
+
+    monkeypatch.setenv("AMGMI_POST", "sweep")
+    lean, one, two = series(1 << 40)
+    monkeypatch.delenv("AMGMI_POST")
+    wide = series(1 << 40)[0]
+    got, a, b = series(lean["peak"])
+    assert got["peak"] <= lean["peak"] and (got["refused"] > 0) == (wide["peak"] > lean["peak"])
+    assert full or got["refused"] > 0
+    for x, y in ((a, one), (b, two)):
+        assert x["converged"] and abs(x["iters"] - y["iters"]) <= (4 if bicgstab else 1)
