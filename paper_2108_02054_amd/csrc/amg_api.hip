@@ -451,10 +451,10 @@ bool lanes_only() {
     return e != nullptr && std::strcmp(e, "lanes") == 0;
 }
 
-// Galerkin form override (AMGMI_GALERKIN = pos | pos16 | lanes, optionally ":G" for the
+// Galerkin form override (AMGMI_GALERKIN = own | pos | pos16 | lanes, optionally ":G" for the
 // position-map form's lanes per row and ":G:T" also for its B terms per lane and entry;
-// pos16 forces two-byte positions); used to exercise every form and launch shape.
-// Default: the shape picker's choice.
+// pos16 forces two-byte positions, own makes a small product of another form an error); used
+// to exercise every form and launch shape.  Default: the shape picker's choice.
 struct GalForce {
     int lanes = 0;  // 1: lane-group kernels
     int wide = 0;   // 1: two-byte positions
@@ -804,9 +804,9 @@ void release_dia(amg_ctx* c) {
 }
 
 // The full set of diagonals is always written; when the offsets are symmetric the values
-// are checked on the device, and the solve switches to the symmetric read (half the
-// diagonals) once it has seen the result (c->dia.off.sym, set in the CG's first
-// residual read-back).
+// are checked on the device, and the kernels switch to the symmetric read (half the
+// diagonals) once the host has seen the result (c->dia.off.sym, set at the end of a setup and
+// by the CG's first residual read-back).
 // scatter = false: the values are already there (the level-0 A P kernel wrote them).
 void refresh_dia(amg_ctx* c, bool scatter = true) {
     if (c->dia.ndiag == 0) return;
@@ -1670,8 +1670,8 @@ T* vcycle_level(amg_ctx* c, int l, const T* f, T* out, const RzEpilogue* ep, int
 
 // z = B r with r, z in FP64; in mixed precision the cycle itself runs in FP32.  With an
 // epilogue, the CG scalars rho (= r.z) and beta are formed in the same pass.  `ready`:
-// what the CG update already formed -- FP64: 2 = level 0's first sweep and residual;
-// mixed: 1 = r in FP32 in level 0's f.
+// what the CG update already formed -- FP64: 1 = level 0's first sweep, 2 = also its
+// residual; mixed: 1 = r in FP32 in level 0's f.
 void vcycle_apply(amg_ctx* c, const double* r, double* z, const RzEpilogue* ep = nullptr, int ready = 0) {
     Level& L0 = c->lv[0];
     if (mixed(c)) {
@@ -1679,8 +1679,9 @@ void vcycle_apply(amg_ctx* c, const double* r, double* z, const RzEpilogue* ep =
             Trace tr(c, AMG_K_CAST, 0);
             launch_cast_d2f(L0.A.nrows, r, (float*)L0.f, c->stream);
         }
-        // the FP32 cycle forms z and r.z itself only in the level-0 diagonal-storage sweep;
-        // every other FP32 path leaves them to the widening pass below
+        // the FP32 cycle forms z and r.z itself in the level-0 diagonal-storage sweep and in
+        // level 0's correction with Q_0; every other FP32 path leaves them to the widening pass
+        // below
         const bool fuse = ep && c->rz32 && c->prm.block_size == 1 && c->lv.size() > 1 &&
                           (c->dia.ndiag > 0 || L0.Q.nrows > 0);
         RzEpilogue e32{ep ? ep->flexible : 0, 0, r, z};
@@ -1882,10 +1883,9 @@ amg_status pcg(amg_ctx* c, const double* f, double* u, amg_solve_info* info) {
 // method for its non-symmetric systems (Section 4), with the CG's stopping rule (true
 // relative residual; when the recursive ||s|| or ||r|| reaches rtol the true residual is
 // formed and, if it is not small enough, the method restarts from it with r^ = r).  Per
-// iteration: two V-cycles, two products with the Krylov operator, and three host reads
-// of dot-product partials (r^.v for alpha, ||s||, t.s and t.t for omega; r^.r and ||r||
-// come with the update).  Scalars are formed on the host from partials added in
-// workgroup order.
+// iteration: two V-cycles, two products with the Krylov operator, and one host read, of the
+// ||r||^2 partials and the step's scalars.  alpha, omega, beta and the half step's test are
+// formed on the device from partials added in a fixed order (k_bi_scal, k_bi_direction).
 amg_status bicgstab(amg_ctx* c, const double* f, double* u, amg_solve_info* info) {
     hipStream_t s = c->stream;
     const Level& L0 = c->lv[0];
