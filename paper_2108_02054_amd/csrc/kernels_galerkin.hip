@@ -652,7 +652,7 @@ static void launch_own(const Csr& L, const Csr& B, const Csr& C, const GalShape&
                                     C.v<T>(), gs.inv, dp, kind, (T)omega, m, q);
     };
     if (gs.own_rows == TPB) {
-        const int u = own_entries(gs.own, gs.inv_w, sizeof(T));
+        const int u = own_entries(gs.inv_w);
         const size_t sm = (size_t)own_smem(gs.own, gs.inv_w, u, sizeof(T));
         if (sm > OWN_SMEM_MAX) throw Fail{AMG_ERR_ARG, "row too long for the owner form"};
         const unsigned nbk = (unsigned)L.nrows;
@@ -660,8 +660,7 @@ static void launch_own(const Csr& L, const Csr& B, const Csr& C, const GalShape&
         else if (gs.own == 16) go(k_galerkin_own<T, 16, 1, 8>, nbk, sm);
         else if (gs.own == 32) go(k_galerkin_own<T, 32, 1, 8>, nbk, sm);
         else if (k == 1) go(k_galerkin_own<T, 64, 1, 8>, nbk, sm);
-        else if (k == 2 && u == 8) go(k_galerkin_own<T, 64, 2, 8>, nbk, sm);
-        else if (k == 2) go(k_galerkin_own<T, 64, 2, 4>, nbk, sm);
+        else if (k == 2) go(k_galerkin_own<T, 64, 2, 8>, nbk, sm);
         else go(k_galerkin_own<T, 64, 4, 4>, nbk, sm);
     } else {
         const unsigned nbk = row_blocks(L.nrows, gs.own);

@@ -18,16 +18,15 @@ constexpr bool lanes_fit_grid(long long rows, int lanes) { return rows * lanes <
 
 // Owner form of a Galerkin product with a workgroup of 256 threads per row of at most w columns:
 // its 256 / lanes groups take `entries` L entries each per chunk, and two chunks of products
-// (w per entry) and L values are kept in LDS, within the 64 KiB that leave room for a second
-// workgroup on the CU.
-constexpr int OWN_SMEM_MAX = 65536;
+// (w per entry) and L values are kept in LDS, within half of the CU's 160 KiB so that a second
+// workgroup has room.
+constexpr int OWN_SMEM_MAX = 81920;
 constexpr int own_smem(int lanes, int w, int entries, int bytes) {
     return 2 * (256 / lanes) * entries * (w + 1) * bytes;
 }
-// Eight entries per group where they fit (121 to 128 FP64 columns, and more than 128, take four).
-constexpr int own_entries(int lanes, int w, int bytes) {
-    return w <= 128 && own_smem(lanes, w, 8, bytes) <= OWN_SMEM_MAX ? 8 : 4;
-}
+// Eight entries per group (FP64 rows of 121 to 128 columns: 66048 bytes; four there took 18.6 us
+// per product against 16.3), four for rows of more than 128 columns.
+constexpr int own_entries(int w) { return w <= 128 ? 8 : 4; }
 
 // Windowed kernels, symmetric values: whether half of the diagonals are read, twice each, the
 // mirrored time at an odd offset.  Where all of them fit in the L2s (8 x 4 MB) the full read,

@@ -52,16 +52,15 @@ def test_setup_kernels_use_the_rule():
 
 def test_owner_form_fits_its_lds(tmp_path):
     """Rows of every width that the owner form takes (8 to 248 columns, padded to multiples of
-    8), in FP64 and FP32; eight entries per group at 121..128 FP64 columns would not."""
-    lines = ["own_smem(64, 128, 8, 8) == 66048", "own_entries(64, 120, 8) == 8", "own_entries(64, 128, 4) == 8"]
+    8), in FP64 and FP32: two workgroups fit a CU's 160 KiB."""
+    lines = ["2 * OWN_SMEM_MAX <= 160 * 1024", "own_smem(64, 128, 8, 8) == 66048"]
     for w in range(8, 249, 8):
         lanes = next(g for g in (8, 16, 32, 64) if g >= w or g == 64)
+        lines.append(f"own_entries({w}) == {8 if w <= 128 else 4}")  # four positions per lane: four entries
         for size in (4, 8):
-            lines.append(f"own_smem({lanes}, {w}, own_entries({lanes}, {w}, {size}), {size}) <= 65536")
-            lines.append(f"own_entries({lanes}, {w}, {size}) == 8 || own_entries({lanes}, {w}, {size}) == 4")
-            if w > 128:
-                lines.append(f"own_entries({lanes}, {w}, {size}) == 4")  # four positions per lane: four entries
+            lines.append(f"own_smem({lanes}, {w}, own_entries({w}), {size}) <= OWN_SMEM_MAX")
     assert holds(lines, tmp_path) is None
+    assert holds(["own_smem(64, 136, 8, 8) <= 65536"], tmp_path) is not None
 
 
 def test_window_reads_half_above_the_caches(tmp_path):
