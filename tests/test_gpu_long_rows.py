@@ -94,7 +94,7 @@ def test_hub_product_pattern_time(n):
     A = laplacian(n, i, j, np.r_[g.uniform(0.5, 1.5, n - 1), np.full(n - 2, 1e-6)])
     p, c, v = T(A.indptr.astype(np.int32)), T(A.indices.astype(np.int32)), T(A.data)
     took = []
-    for _ in range(2):
+    for _ in range(3):
         h = AMG(p, c, v, aggregation=1)
         took.append(h.phase_times()["symbolic"])
         h.close()
