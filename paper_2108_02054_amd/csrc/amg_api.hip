@@ -685,6 +685,7 @@ void release_correction(amg_ctx* c, Level& L) {
 bool drop_corrections(void* ctx) {
     amg_ctx* c = (amg_ctx*)ctx;
     bool any = false;
+    if (c->q_pinned) return false;
     for (Level& L : c->lv) {
         any = any || L.Q.nrows > 0;
         release_correction(c, L);
@@ -898,7 +899,7 @@ void partial_rebuild(amg_ctx* c, const double* val) {
     std::vector<char> smoothed((size_t)nlev, 0);
     const bool blocked = c->prm.block_size > 1;
     // Q_l is formed unless all that ran since the last update were solves that read none
-    if (c->q_read || c->q_swept) c->q_keep = c->q_read;
+    if (c->q_read || c->q_swept) c->q_keep = c->q_read || c->q_pinned;
     c->q_read = c->q_swept = false;
     c->q_formed = c->q_keep;
     // Ingest: the level-0 staged A P kernel takes the new values straight from the caller's
@@ -1094,6 +1095,7 @@ void build_hierarchy(amg_ctx* c, int32_t n, int64_t nnz, const int32_t* ptr, con
     const auto t_all = Clock::now();
     double ph[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 
+    c->q_pinned = false;  // (graphs of the old hierarchy's cycles end with it)
     drop_corrections(c);  // (their memory serves the copy, which the old arrays still stand beside)
     // Copy the input first: it may be the current hierarchy's own level-0 arrays.
     std::vector<void*> old = std::move(c->hier_allocs);
@@ -2387,16 +2389,18 @@ amg_status amg_solve_bicgstab(amg_ctx* c, const double* f, double* u, amg_solve_
 }
 
 namespace {
-// The diagonal storage as the operator's entry points read it.  A call that is being captured
-// into a graph reads every stored entry: replays see the values of later updates, which need
-// not be symmetric as those of the capture were.
+bool capturing(const amg_ctx* c) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIP_CHECK(hipStreamIsCapturing(c->stream, &st));
+    return st != hipStreamCaptureStatusNone;
+}
+
+// The diagonal storage as a call that may be captured into a graph reads it.  A captured one
+// reads every stored entry: replays see the values of later updates, which need not be
+// symmetric as those of the capture were.
 Dia operator_storage(const amg_ctx* c) {
     Dia D = c->dia;
-    if (D.off.sym) {
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        HIP_CHECK(hipStreamIsCapturing(c->stream, &st));
-        if (st != hipStreamCaptureStatusNone) D.off.sym = 0;
-    }
+    if (D.off.sym && capturing(c)) D.off.sym = 0;
     return D;
 }
 }  // namespace
@@ -2451,6 +2455,15 @@ amg_status amg_vcycle(amg_ctx* c, const double* r, double* z) {
     if (!c || !r || !z) return AMG_ERR_ARG;
     return guard(c, [&] {
         want_corrections(c);
+        struct Restore {
+            amg_ctx* c;
+            int sym;
+            ~Restore() { c->dia.off.sym = sym; }
+        } restore{c, c->dia.off.sym};
+        if (capturing(c)) {  // replays follow later updates: all stored entries, and Q_l with each
+            c->dia.off.sym = 0;
+            c->q_pinned = true;
+        }
         vcycle_apply(c, r, z);
         return AMG_OK;
     });

@@ -759,8 +759,8 @@ struct amg_ctx {
     // the cycles of this solve keep the coarse correction and the post-sweep apart (BiCGStab)
     bool post_sweeps = false;
     // Q_l: a cycle since the last update read it / swept apart instead; updates form it; it
-    // belongs to the current values
-    bool q_read = false, q_swept = false, q_keep = true, q_formed = true;
+    // belongs to the current values; a captured cycle reads it, so that updates always form it
+    bool q_read = false, q_swept = false, q_keep = true, q_formed = true, q_pinned = false;
     bool broken = false;
     std::string err;
 };

@@ -63,3 +63,45 @@ def test_captured_operator_follows_unsymmetric_values(points, N, after_solve):
         del graph
         h.close()
     torch.cuda.current_stream().wait_stream(side)
+
+
+# a hierarchy whose every pass runs on the context's own stream (a coarsest level of at most 128
+# rows): its V-cycle can be captured as well
+@pytest.mark.parametrize("opts", [dict(), dict(aggregation=1), dict(precision=1), dict(smoother=1)])
+@pytest.mark.parametrize("after_solve", [False, True])
+def test_captured_cycle_follows_updates(opts, after_solve):
+    from paper_2108_02054_amd import AMG
+    p, c, v = two_fluid_7pt(22, 0.4)
+    n = len(p) - 1
+    g = np.random.default_rng(3)
+    f = g.uniform(-1, 1, n)
+    print(f"case captured cycle {opts} after_solve={after_solve}", flush=True)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        h = AMG(T(p), T(c), T(v), coarse_enough=60, **opts)
+        F = T(f)
+        if after_solve:
+            h.solve(F)
+        h.vcycle(F)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            Z = h.vcycle(F)
+        for step in range(4):
+            # step 1: unsymmetric values; then solves that read no Q between the updates
+            w = v if step == 0 else v * (1.0 + 0.02 * g.uniform(-1, 1, len(v)))
+            h.rebuild(T(w))
+            if step >= 2:
+                h.solve_bicgstab(F)
+                w = 1.5 * w
+                h.rebuild(T(w))
+            graph.replay()
+            side.synchronize()
+            got = Z.cpu().numpy()
+            want = h.vcycle(F)
+            side.synchronize()
+            assert np.array_equal(got, want.cpu().numpy()), step
+        del graph
+        h.close()
+    torch.cuda.current_stream().wait_stream(side)
