@@ -989,14 +989,24 @@ void form_corrections(amg_ctx* c) {
     }
 }
 
+bool capturing(const amg_ctx* c) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIP_CHECK(hipStreamIsCapturing(c->stream, &st));
+    return st != hipStreamCaptureStatusNone;
+}
+
 void want_corrections(amg_ctx* c) {
     c->q_read = true;
     if (c->q_formed) return;
+    const bool stale = c->a0_csr_stale;
     if (mixed(c))
         form_corrections<float>(c);
     else
         form_corrections<double>(c);
-    c->q_formed = true;
+    if (capturing(c))  // recorded, not run: the state of the arrays is as it was
+        c->a0_csr_stale = stale;
+    else
+        c->q_formed = true;
 }
 
 void partial_any(amg_ctx* c, const double* val) {
@@ -2389,12 +2399,6 @@ amg_status amg_solve_bicgstab(amg_ctx* c, const double* f, double* u, amg_solve_
 }
 
 namespace {
-bool capturing(const amg_ctx* c) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    HIP_CHECK(hipStreamIsCapturing(c->stream, &st));
-    return st != hipStreamCaptureStatusNone;
-}
-
 // The diagonal storage as a call that may be captured into a graph reads it.  A captured one
 // reads every stored entry: replays see the values of later updates, which need not be
 // symmetric as those of the capture were.

@@ -105,3 +105,40 @@ def test_captured_cycle_follows_updates(opts, after_solve):
         del graph
         h.close()
     torch.cuda.current_stream().wait_stream(side)
+
+
+@pytest.mark.parametrize("opts", [dict(aggregation=1), dict(precision=1)])
+def test_cycle_captured_where_an_update_left_q_out(opts):
+    """The forming of Q is recorded with the cycle; an eager cycle still forms its own."""
+    from paper_2108_02054_amd import AMG
+    p, c, v = two_fluid_7pt(22, 0.4)
+    f = np.random.default_rng(3).uniform(-1, 1, len(p) - 1)
+    print(f"case captured cycle that forms Q {opts}", flush=True)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        h, o = (AMG(T(p), T(c), T(v), coarse_enough=60, **opts) for _ in range(2))
+        F = T(f)
+        h.vcycle(F)  # (every kernel of the cycle has run once before the capture)
+        h.rebuild(T(1.1 * v))
+        h.solve_bicgstab(F)
+        for x in (h, o):
+            x.rebuild(T(1.4 * v))
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            Z = h.vcycle(F)
+        want = o.vcycle(F)
+        assert torch.equal(h.vcycle(F), want)
+        graph.replay()
+        assert torch.equal(Z, want)
+        assert np.array_equal(h.level(0)["A"][2], o.level(0)["A"][2])
+        for x in (h, o):
+            x.rebuild(T(1.7 * v))
+        graph.replay()
+        assert torch.equal(Z, o.vcycle(F)) and torch.equal(h.vcycle(F), o.vcycle(F))
+        assert np.array_equal(h.level(0)["A"][2], o.level(0)["A"][2])
+        side.synchronize()
+        del graph
+        h.close()
+        o.close()
+    torch.cuda.current_stream().wait_stream(side)

@@ -137,7 +137,7 @@ def test_not_refused_for_its_memory(monkeypatch, kind, opts, bicgstab, full):
     """A series that fits in the memory of a hierarchy without Q is set up, updated and solved in
     that memory, by a first setup and by a full rebuild."""
     from paper_2108_02054_amd import AMG, FULL
-    p, c, v = two_fluid_7pt(40, 0.4) if kind == "stencil" else random_spd_graph(30000, 5, 3)
+    p, c, v = two_fluid_7pt(40, 0.4) if kind == "stencil" else random_spd_graph(8000, 5, 3)
     f = T(np.random.default_rng(4).uniform(-1, 1, len(p) - 1))
     print(f"case memory without corrections {kind} {opts} bicgstab={bicgstab} full={full}", flush=True)
 
